@@ -46,6 +46,39 @@ def test_unstructured_bit_exact_with_ties(L, d, sparsity):
         np.testing.assert_array_equal(g, ref)
 
 
+# Every workgroup shape of the in-register selection at its edges, the rows
+# beyond it, and more rows than the grid has workgroups.
+@pytest.mark.parametrize("n, d", [(2100, 5), (3, 1024), (3, 1025), (2, 4097), (2, 8192), (2, 8193),
+                                  (2, 16383), (2, 16384), (2, 16385)])
+def test_unstructured_row_shapes(L, n, d):
+    rng = np.random.default_rng(d)
+    W = rng.standard_normal((n, d)).astype(np.float32)
+    W[:, ::7] = np.round(W[:, ::7])        # ties, zeros
+    W[0, d // 2] = np.inf                  # the widest range of keys
+    W[-1, d // 3] = np.nan
+    c = np.exp(3.0 * rng.standard_normal(d))
+    c[d // 5] = -1.0
+    for sparsity in (1.0 / d, 0.5, 0.9):
+        ref = oracle.wanda_mask(W, c, "unstructured", sparsity)
+        np.testing.assert_array_equal(gpu_mask(L, W, c, L.MASK_UNSTRUCTURED, sparsity), ref)
+        if d % 4 == 0:  # rows that are not 16-byte aligned
+            Wo = torch.empty(n * d + 1, device=dev())[1:].view(n, d)
+            Wo.copy_(to_dev(W))
+            np.testing.assert_array_equal(gpu_mask(L, Wo, c, L.MASK_UNSTRUCTURED, sparsity), ref)
+
+
+@pytest.mark.parametrize("n, d", [(1, 4), (5000, 8), (3, 4 * 257)])
+def test_2to4_row_blocks(L, n, d):
+    rng = np.random.default_rng(d)
+    W = np.round(rng.standard_normal((n, d)), 1).astype(np.float32)
+    c = np.exp(rng.standard_normal(d))
+    ref = oracle.wanda_mask(W, c, "2:4")
+    np.testing.assert_array_equal(gpu_mask(L, W, c, L.MASK_2TO4), ref)
+    Wo = torch.empty(n * d + 1, device=dev())[1:].view(n, d)  # not 16-byte aligned
+    Wo.copy_(to_dev(W))
+    np.testing.assert_array_equal(gpu_mask(L, Wo, c, L.MASK_2TO4), ref)
+
+
 @pytest.mark.parametrize("d", [4, 12, 1000, 4096])
 def test_2to4_bit_exact_with_ties(L, d):
     W, c = tied_inputs(7, d, 100 + d)
