@@ -394,9 +394,9 @@ typedef struct {
   int64_t few_row_products;   /* columns multiplied by those launches */
   double few_product_ms;      /* their device time (included in timed_product_ms) */
   int64_t persistent_launches; /* blocks of few-column iterations (the iterations between two
-                                  checks) that ran as one cooperative launch keeping H's planes
-                                  in registers (d <= 4096); each counts all of its iterations in
-                                  few_launches */
+                                  checks) that opts.cooperative let run as one launch keeping
+                                  H's planes in registers (d <= 4096); each counts all of its
+                                  iterations in few_launches */
 } optima_solve_info;
 
 void optima_solver_opts_default(optima_solver_opts* opts);

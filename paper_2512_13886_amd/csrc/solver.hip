@@ -1168,6 +1168,182 @@ __global__ void __launch_bounds__(64 * kSkinnyWaves) k_few_persistent(PersistArg
   }
 }
 
+// Whole blocks of iterations (everything between two checks) in one launch,
+// for dense solves whose H fits the registers of one workgroup (dp <= 256).
+// Columns are independent, so a workgroup that holds all of H iterates its 16
+// columns without meeting any other: each of its 8 waves keeps 16
+// or 32 rows of H (split planes, or fp32) in registers and forms the products of
+// the 16 columns with them; lane (r, g) owns entry r of each 16 rows of columns
+// 4 g .. 4 g + 3, whose state stays in its registers for the whole block. Only the next x goes
+// through LDS (two buffers, one barrier an iteration).
+//
+// Bound by latency: the chain of one barrier, the LDS reads, dp / 32 dependent
+// MFMAs (one chain for each of the three bf16 products) and the update: 0.68 us
+// an iteration for 64 columns at dp = 128 (bf16x3), 1.5 us at dp = 256. As a
+// product launch per iteration, split along K and finished by a second kernel,
+// they took 9.7 and 10.9 us, nearly all of it the time of the two launches; 4096
+// columns at dp = 256 took 23 us an iteration and take 1.7 us.
+constexpr int kSmallMaxDp = 256;
+constexpr int kSmallCols = 16;
+constexpr int kSmallChunk = 64;  // iterations whose step coefficients are tabled at once
+constexpr int kSmallThreads = 512;  // 256 at dp = 128 (32 rows of H a wave): 0.87 against 0.68 us
+
+struct SmallArgs {
+  const int* rows;      // active list
+  int n_rows, d;
+  const float* H;       // [dp][dp] (kPrecF32)
+  const uint16_t* HP;   // its split planes (kPrecBf16x3)
+  float* X;             // state, in place: x, x_ag, H x, H x_ag
+  float *XA, *HX, *HA;
+  const float* HW0;
+  const uint8_t* mask;  // [n_cols][d]
+  const int* kbase;
+  const float* Lp;
+  int n_iter;
+};
+
+template <int DP, int PREC>
+__global__ void __launch_bounds__(kSmallThreads) k_block_small(SmallArgs a) {
+  constexpr bool kSplit = PREC == kPrecBf16x3;
+  constexpr int kSteps = DP / 32, kThr = kSmallThreads;
+  constexpr int NB = DP / 16 / (kThr / 64);  // 16-row blocks of H per wave
+  // An x row: fp32 values, or the hi plane and then the lo plane; 16 bytes of
+  // padding put the 16 rows of a fragment read on distinct banks.
+  constexpr int kPitch = 4 * DP + 16;
+  __shared__ __attribute__((aligned(16))) char xs[2][kSmallCols * kPitch];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, g = lane >> 4;
+  const int n0 = 16 * NB * wave + r;  // H rows n0 + 16 b
+
+  // This lane's 16-byte pieces of its H rows: planes per 32 columns (64 bytes
+  // of hi, 64 of lo), or fp32.
+  const char* hrow = (kSplit ? reinterpret_cast<const char*>(a.HP)
+                             : reinterpret_cast<const char*>(a.H)) +
+                     size_t(n0) * DP * 4 + 16 * g;
+  uint4 h[NB][kSteps][2];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      h[b][s][0] = *reinterpret_cast<const uint4*>(hrow + b * 64 * DP + s * 128);
+      h[b][s][1] = *reinterpret_cast<const uint4*>(hrow + b * 64 * DP + s * 128 + 64);
+    }
+
+  int j[4];
+  bool on[4];
+  float x[NB][4], xa[NB][4], hx[NB][4], ha[NB][4], hw[NB][4];
+  unsigned keep = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int c = int(blockIdx.x) * kSmallCols + 4 * g + e;
+    on[e] = c < a.n_rows;
+    j[e] = a.rows[on[e] ? c : a.n_rows - 1];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int n = n0 + 16 * b;
+      const size_t o = size_t(j[e]) * DP + n;
+      x[b][e] = a.X[o];
+      xa[b][e] = a.XA[o];
+      hx[b][e] = a.HX[o];
+      ha[b][e] = a.HA[o];
+      hw[b][e] = a.HW0[o];
+      keep |= unsigned(n < a.d && a.mask[size_t(j[e]) * a.d + n] != 0) << (4 * b + e);
+    }
+  }
+  const float L = *a.Lp;
+  // alpha and eta of the 16 columns for kSmallChunk iterations: two divisions
+  // an entry, which would lengthen every iteration's chain.
+  __shared__ f4 tab_alpha[kSmallChunk][kSmallCols / 4], tab_eta[kSmallChunk][kSmallCols / 4];
+  for (int i = 0; i < a.n_iter; ++i) {
+    const int ic = i % kSmallChunk;
+    if (ic == 0) {
+      __syncthreads();  // the chunk before has been read
+      for (int t = threadIdx.x; t < kSmallChunk * kSmallCols; t += kThr) {
+        const int c = min(int(blockIdx.x) * kSmallCols + t % kSmallCols, a.n_rows - 1);
+        const float k = float(a.kbase[a.rows[c]] + i + t / kSmallCols);
+        reinterpret_cast<float*>(tab_alpha)[t] = 2.f / (k + 2.f);
+        reinterpret_cast<float*>(tab_eta)[t] = (k + 1.f) / (2.f * L);
+      }
+      __syncthreads();
+    }
+    const f4 alpha = tab_alpha[ic][g], eta = tab_eta[ic][g];
+    char* xb = xs[i & 1];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int n = n0 + 16 * b;
+        const float gr = 2.f * ((1.f - alpha[e]) * ha[b][e] + alpha[e] * hx[b][e] - hw[b][e]);
+        x[b][e] = (keep >> (4 * b + e)) & 1u ? x[b][e] - eta[e] * gr : 0.f;
+        xa[b][e] = (1.f - alpha[e]) * xa[b][e] + alpha[e] * x[b][e];
+        char* q = xb + (4 * g + e) * kPitch;
+        if constexpr (kSplit) {
+          const uint32_t hi = bf16_rne_bits(x[b][e]);
+          *reinterpret_cast<uint16_t*>(q + 2 * n) = uint16_t(hi);
+          *reinterpret_cast<uint16_t*>(q + 2 * DP + 2 * n) =
+              uint16_t(bf16_rne_bits(x[b][e] - bf16_bits_value(hi)));
+        } else {
+          *reinterpret_cast<float*>(q + 4 * n) = x[b][e];
+        }
+      }
+    // Every wave is past its reads of this buffer: they precede the barrier of
+    // the iteration before.
+    __syncthreads();
+    f4 acc[NB][3];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) acc[b][q] = f4{0.f, 0.f, 0.f, 0.f};
+    const char* xr = xb + r * kPitch + 16 * g;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      if constexpr (kSplit) {
+        const bf16x8 xh = *reinterpret_cast<const bf16x8*>(xr + s * 64);
+        const bf16x8 xl = *reinterpret_cast<const bf16x8*>(xr + 2 * DP + s * 64);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const bf16x8 bh = __builtin_bit_cast(bf16x8, h[b][s][0]);
+          const bf16x8 bl = __builtin_bit_cast(bf16x8, h[b][s][1]);
+          acc[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bh, acc[b][0], 0, 0, 0);
+          acc[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bl, acc[b][1], 0, 0, 0);
+          acc[b][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, bh, acc[b][2], 0, 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          const f4 xv = *reinterpret_cast<const f4*>(xr + s * 128 + v * 64);
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+              acc[b][t & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  xv[t], __builtin_bit_cast(f4, h[b][s][v])[t], acc[b][t & 1], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float y = kSplit ? acc[b][0][e] + (acc[b][1][e] + acc[b][2][e])
+                               : acc[b][0][e] + acc[b][1][e];
+        ha[b][e] = (1.f - alpha[e]) * ha[b][e] + alpha[e] * y;
+        hx[b][e] = y;
+      }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (on[e]) {
+        const size_t o = size_t(j[e]) * DP + n0 + 16 * b;
+        a.X[o] = x[b][e];
+        a.XA[o] = xa[b][e];
+        a.HX[o] = hx[b][e];
+        a.HA[o] = ha[b][e];
+      }
+}
+
 // Sums the split partials in split order and applies the product epilogue.
 template <int MODE, int PREC>
 __global__ void __launch_bounds__(kThreads) k_split_epilogue(ProductArgs p, int splits,
@@ -2074,6 +2250,29 @@ bool launch_persistent(const PersistArgs& a, int prec, hipStream_t s) {
   return true;
 }
 
+// Whether a block of dense iterations runs in one launch of k_block_small: where
+// H fits a workgroup's registers, for any number of columns (16384 columns at
+// dp = 128: 2.1 against 30 us an iteration).
+bool small_path(int prec, int dp) { return prec != kPrecSparse && dp <= kSmallMaxDp; }
+
+optima_status launch_small(const SmallArgs& a, int dp, int prec, hipStream_t s) {
+  const dim3 grid(unsigned(ceil_div(a.n_rows, kSmallCols))), block(kSmallThreads);
+  static_assert(kSmallMaxDp == 2 * kTile, "dp is 128 or 256");
+  if (dp == kTile) {
+    if (prec == kPrecBf16x3)
+      hipLaunchKernelGGL((k_block_small<kTile, kPrecBf16x3>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_block_small<kTile, kPrecF32>), grid, block, 0, s, a);
+  } else {
+    if (prec == kPrecBf16x3)
+      hipLaunchKernelGGL((k_block_small<2 * kTile, kPrecBf16x3>), grid, block, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_block_small<2 * kTile, kPrecF32>), grid, block, 0, s, a);
+  }
+  OPTIMA_LAUNCH_CHECK();
+  return OPTIMA_OK;
+}
+
 template <int MODE, int PREC>
 optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t s) {
   if constexpr ((MODE == kFused || MODE == kStore) && PREC == kPrecSparse) {
@@ -2450,15 +2649,19 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
   int cur = 0;
   int64_t t = 0;
   const int64_t ce = o.check_every;
+  // k_block_small keeps x in one buffer and needs no planes of it.
+  const bool small = small_path(iprec, dp);
   while (t < o.max_iters && n_act > 0) {
     const int64_t t_next = std::min<int64_t>((t / ce + 1) * ce, o.max_iters);
     const int n = int(t_next - t);
-    const dim3 ug(unsigned(n_act), unsigned(ceil_div(dp, 4 * kThreads)));
-    hipLaunchKernelGGL(k_update, ug, dim3(kThreads), 0, s, rows, n_act, dp, di, xbuf[cur],
-                       xbuf[cur ^ 1], l.XA, l.HX, l.HA, l.HW0, mask, l.st.kbase, l.L,
-                       split ? xpl[cur ^ 1] : nullptr, sparse ? 1 : 0, l.SLOT);
-    OPTIMA_LAUNCH_CHECK();
-    cur ^= 1;
+    if (!small) {
+      const dim3 ug(unsigned(n_act), unsigned(ceil_div(dp, 4 * kThreads)));
+      hipLaunchKernelGGL(k_update, ug, dim3(kThreads), 0, s, rows, n_act, dp, di, xbuf[cur],
+                         xbuf[cur ^ 1], l.XA, l.HX, l.HA, l.HW0, mask, l.st.kbase, l.L,
+                         split ? xpl[cur ^ 1] : nullptr, sparse ? 1 : 0, l.SLOT);
+      OPTIMA_LAUNCH_CHECK();
+      cur ^= 1;
+    }
     p.rows = rows;
     p.n_rows = n_act;
     p.HA = l.HA;
@@ -2468,7 +2671,13 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
       if (auto e = stage_major_idx(l.XIDX, rows, n_act, l, p, s)) return e;
     if (info) OPTIMA_HIP_TRY(hipEventRecord(ev[0], s));
     bool persisted = false;
-    if (o.cooperative && persistent_path(iprec, n_act, dp) &&
+    if (small) {
+      SmallArgs sa{rows, n_act, di, Hm, l.HP, xbuf[cur], l.XA, l.HX, l.HA, l.HW0, mask,
+                   l.st.kbase, l.L, n};
+      if (auto e = launch_small(sa, dp, iprec, s)) return e;
+      if (o.cooperative && few_column_path(iprec, n_act, dp)) inf.persistent_launches += 1;
+      persisted = true;
+    } else if (o.cooperative && persistent_path(iprec, n_act, dp) &&
         size_t(nc) * size_t(dp) * 4 < (size_t(1) << 31)) {
       PersistArgs pa{};
       pa.p = p;
@@ -2518,7 +2727,7 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
     ca.rows = rows;
     ca.n_rows = n_act;
     ca.X = xbuf[cur];
-    ca.XP = split ? xpl[cur] : nullptr;
+    ca.XP = split && !small ? xpl[cur] : nullptr;
     ca.initial = 0;
     ca.final_check = t == o.max_iters;
     ca.t = t;
