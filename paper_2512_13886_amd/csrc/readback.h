@@ -130,18 +130,28 @@ inline hipError_t wait_stream(hipStream_t s) {
   return poll_event(b->ev);
 }
 
+// read_back below in two halves, for work queued between them that does not
+// depend on the outcome: begin queues the copy, end waits for it alone. The
+// host thread makes no other library call in between.
+inline hipError_t read_back_begin(const void* src, size_t bytes, hipStream_t s, HostMailbox** box) {
+  if (bytes > kMailboxBytes) return hipErrorInvalidValue;
+  hipError_t e = mailbox_for(s, box);
+  if (e != hipSuccess) return e;
+  if ((e = hipMemcpyAsync((*box)->host, src, bytes, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+  return hipEventRecord((*box)->ev, s);
+}
+inline hipError_t read_back_end(void* dst, size_t bytes, HostMailbox* box) {
+  const hipError_t e = poll_event(box->ev);
+  if (e == hipSuccess) memcpy(dst, box->host, bytes);
+  return e;
+}
+
 // Copies `bytes` (at most kMailboxBytes) of device memory at src into dst
 // once the work queued on s so far has finished.
 inline hipError_t read_back(void* dst, const void* src, size_t bytes, hipStream_t s) {
-  if (bytes > kMailboxBytes) return hipErrorInvalidValue;
   HostMailbox* b = nullptr;
-  hipError_t e = mailbox_for(s, &b);
-  if (e != hipSuccess) return e;
-  if ((e = hipMemcpyAsync(b->host, src, bytes, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-  if ((e = hipEventRecord(b->ev, s)) != hipSuccess) return e;
-  if ((e = poll_event(b->ev)) != hipSuccess) return e;
-  memcpy(dst, b->host, bytes);
-  return hipSuccess;
+  const hipError_t e = read_back_begin(src, bytes, s, &b);
+  return e != hipSuccess ? e : read_back_end(dst, bytes, b);
 }
 
 // The same two waits without the pinned mailbox, for calls that may not
