@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(Tile128::kThreads) k_forward(const char* X, in
   for (int i = 0; i < Cfg::kLoadsB; ++i)
     src.b[i] = wb + (n0 + load_row<Cfg>(i)) * pitch + load_seg_bytes<Cfg>(i);
   f4 acc[Cfg::MB][Cfg::NB];
-  gemm_tile_mainloop<Cfg, Bf16Tag>(acc, src, int(pitch / Cfg::SRB), lds0, lds1, nullptr);
+  gemm_tile_mainloop<Cfg, Bf16Tag>(acc, src, int(pitch / Cfg::SRB), lds0, lds1);
   stage_tile<Cfg>(acc, lds0, lds1);
   __syncthreads();
 

@@ -1,0 +1,102 @@
+// MFMA main loop of a 128x128 output tile of C = A B^T by 8 waves, one
+// workgroup per CU, for products with too few outputs for the 256x256 tile of
+// gemm256.h: the same two wave groups half a phase apart, on whole stages.
+//
+// Stages of 128 bytes a row (64 bf16 values, or 32 columns of split planes) go
+// through a ring of four 32-KiB LDS buffers. Wave (wm, wn) of a 2 x 4 grid owns
+// 64 x 32 outputs. A stage is a memory part (twelve 16-byte LDS reads a lane,
+// the fetch of the stage three ahead) and an MFMA part, each ended by a barrier;
+// waves 4-7 run one part behind waves 0-3, so that of the two waves of a SIMD
+// one reads while the other multiplies. A buffer is fetched again one stage
+// after it was read, by when both groups' reads have returned (each wave waits
+// for them before the barrier that ends its memory part); and each wave waits in
+// the memory part of stage s for its fetches of stage s + 1, which the group
+// behind does in the part before the group ahead first reads them.
+//
+// Bound by the loads: 32 KiB a stage, 0.56 us on a full chip (15 TB/s out of the
+// L2s), where the stage's MFMAs take 0.35. d = 4096 with 1024 columns (256 tiles
+// of 128 stages): 80 us plus 12 us of fused update, against 111 us for the
+// 4-wave tile split in two.
+#pragma once
+
+#include "gemm256.h"
+
+namespace optima {
+
+struct Ring128 {
+  static constexpr int BM = 128, BN = 128, kWaves = 8, kThreads = 512;
+  static constexpr int kSRB = 128;              // bytes per row and stage
+  static constexpr int kBufBytes = 256 * kSRB;  // A rows, then B rows
+  static constexpr int kLoads = 2;              // wave loads per stage of A, and of B
+};
+
+// Source addresses of this thread's loads at the first stage: load i of A or B
+// fetches tile row t256_load_row(i), byte t256_seg_bytes(i) of its stage.
+struct OperandsR128 {
+  const char* a[Ring128::kLoads];
+  const char* b[Ring128::kLoads];
+};
+
+struct AccR128 {
+  f4 q[4][2];  // [16-row block][16-column block]
+};
+__device__ inline int r128_row(int mi, int e) { return t256_row(0, mi, e); }
+__device__ inline int r128_col(int ni) { return t256_col(0, ni); }
+
+template <typename T>
+__device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, int64_t off, char* cur,
+                                  char* nxt) {
+  const int wm = threadIdx.x >> 8, wn = (threadIdx.x >> 6) & 3;
+  bf16x8 fa[4][2], fb[2][2];
+  t256::read<4>(fa, cur, wm * 64);
+  t256::read<2>(fb, cur + 128 * Ring128::kSRB, wn * 32);
+  t256::fetch(src.a, off, nxt);
+  t256::fetch(src.b, off, nxt + 128 * Ring128::kSRB);
+  t256::end_memory<4 * Ring128::kLoads>();
+  t256::quadrant<T>(acc.q, fa, fb);
+  t256::barrier();
+}
+
+// n stages (n >= 0). b0..b3 are distinct __shared__ arrays of
+// Ring128::kBufBytes; fetches past the last stage repeat it, into buffers that
+// nobody reads again.
+template <typename T>
+__device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, int n, char* b0,
+                                     char* b1, char* b2, char* b3) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc.q[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+  if (n <= 0) return;
+  auto at = [n](int s) { return int64_t(s < n ? s : n - 1) * Ring128::kSRB; };
+  auto fetch = [&](int s, char* buf) {
+    t256::fetch(src.a, at(s), buf);
+    t256::fetch(src.b, at(s), buf + 128 * Ring128::kSRB);
+  };
+  fetch(0, b0);
+  fetch(1, b1);
+  fetch(2, b2);
+  t256::end_memory<4 * Ring128::kLoads>();
+  const bool behind = threadIdx.x >= 256;  // waves 4-7
+  if (behind) t256::barrier();
+  int s = 0;
+  for (; s + 3 < n; s += 4) {
+    r128_stage<T>(acc, src, at(s + 3), b0, b3);
+    r128_stage<T>(acc, src, at(s + 4), b1, b0);
+    r128_stage<T>(acc, src, at(s + 5), b2, b1);
+    r128_stage<T>(acc, src, at(s + 6), b3, b2);
+  }
+  if (s < n) r128_stage<T>(acc, src, at(s + 3), b0, b3);
+  if (s + 1 < n) r128_stage<T>(acc, src, at(s + 4), b1, b0);
+  if (s + 2 < n) r128_stage<T>(acc, src, at(s + 5), b2, b1);
+  if (!behind) t256::barrier();
+  // No load may still be writing LDS when the workgroup moves on.
+  wait_vmcnt<0>();
+  __syncthreads();
+}
+
+// Epilogue staging of the tile through buffers b0 and b1: 512 bytes a row, rows
+// 0-63 in b0; 16-byte column chunk c of row r at physical chunk c ^ (r & 31).
+__device__ inline char* r128_stage_row(char* b0, char* b1, int r) {
+  return (r < 64 ? b0 : b1) + (r & 63) * 512;
+}
+
+}  // namespace optima

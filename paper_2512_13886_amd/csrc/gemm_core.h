@@ -119,7 +119,7 @@ struct TileCfg {
   static_assert(SRB == 128 || SRB == 256, "stage width");
   static_assert(BM % (kRowsPerLoad * kWaves) == 0 && BN % (kRowsPerLoad * kWaves) == 0,
                 "load rounds");
-  static_assert(NBUF == 2 || NBUF == 3, "stage buffers");
+  static_assert(NBUF == 2, "stage buffers");
   static_assert(kWaveChunks >= 2 && kWaveChunks % 2 == 0, "K slice of a wave");
 };
 
@@ -259,12 +259,12 @@ __device__ inline void ring_barrier() {
 // src.a[i] / src.b[i]: address of the 16-byte segment this thread fetches in
 // A / B tile row load_row<Cfg>(i) at the first stage (row start +
 // load_seg_bytes<Cfg>(i)); stage s adds s * Cfg::SRB. All addresses must be
-// 16-byte aligned. lds0..lds2 (lds2 only with NBUF == 3) must be distinct
-// __shared__ arrays of Cfg::kBufBytes declared by the kernel: the loop is
-// unrolled by NBUF so that no LDS read names an array with an in-flight load.
+// 16-byte aligned. lds0 and lds1 must be distinct __shared__ arrays of
+// Cfg::kBufBytes declared by the kernel: the loop is unrolled by two so that no
+// LDS read names an array with an in-flight load.
 template <typename Cfg, typename T>
 __device__ inline void gemm_tile_mainloop(f4 (&acc)[Cfg::MB][Cfg::NB], const Operands<Cfg>& src,
-                                          int n, char* lds0, char* lds1, char* lds2) {
+                                          int n, char* lds0, char* lds1) {
 #pragma unroll
   for (int mi = 0; mi < Cfg::MB; ++mi)
 #pragma unroll
@@ -272,49 +272,22 @@ __device__ inline void gemm_tile_mainloop(f4 (&acc)[Cfg::MB][Cfg::NB], const Ope
   if (n <= 0) return;
   auto cl = [n](int s) { return s < n ? s : n - 1; };
 
-  if constexpr (Cfg::NBUF == 2) {
-    issue_stage<Cfg>(src, 0, lds0);
-    int s = 0;
-    for (; s + 1 < n; s += 2) {
-      wait_vmcnt<0>();
-      __syncthreads();
-      issue_stage<Cfg>(src, s + 1, lds1);
-      compute_stage<Cfg, T>(acc, lds0);
-      wait_vmcnt<0>();
-      __syncthreads();
-      issue_stage<Cfg>(src, cl(s + 2), lds0);
-      compute_stage<Cfg, T>(acc, lds1);
-    }
-    if (s < n) {  // odd count: the last stage is in lds0
-      wait_vmcnt<0>();
-      __syncthreads();
-      compute_stage<Cfg, T>(acc, lds0);
-    }
-  } else {
-    issue_stage<Cfg>(src, 0, lds0);
-    issue_stage<Cfg>(src, cl(1), lds1);
-    int s = 0;
-    for (; s + 2 < n; s += 3) {
-      ring_barrier<Cfg::kLoads>();  // stage s landed, stage s + 1 may still fly
-      issue_stage<Cfg>(src, s + 2, lds2);
-      compute_stage<Cfg, T>(acc, lds0);
-      ring_barrier<Cfg::kLoads>();
-      issue_stage<Cfg>(src, cl(s + 3), lds0);
-      compute_stage<Cfg, T>(acc, lds1);
-      ring_barrier<Cfg::kLoads>();
-      issue_stage<Cfg>(src, cl(s + 4), lds1);
-      compute_stage<Cfg, T>(acc, lds2);
-    }
-    if (s < n) {  // one or two stages left, in lds0 and lds1
-      wait_vmcnt<Cfg::kLoads>();
-      __syncthreads();
-      compute_stage<Cfg, T>(acc, lds0);
-      if (s + 1 < n) {
-        wait_vmcnt<0>();
-        __syncthreads();
-        compute_stage<Cfg, T>(acc, lds1);
-      }
-    }
+  issue_stage<Cfg>(src, 0, lds0);
+  int s = 0;
+  for (; s + 1 < n; s += 2) {
+    wait_vmcnt<0>();
+    __syncthreads();
+    issue_stage<Cfg>(src, s + 1, lds1);
+    compute_stage<Cfg, T>(acc, lds0);
+    wait_vmcnt<0>();
+    __syncthreads();
+    issue_stage<Cfg>(src, cl(s + 2), lds0);
+    compute_stage<Cfg, T>(acc, lds1);
+  }
+  if (s < n) {  // odd count: the last stage is in lds0
+    wait_vmcnt<0>();
+    __syncthreads();
+    compute_stage<Cfg, T>(acc, lds0);
   }
   // No direct load may still be writing LDS when the workgroup moves on.
   wait_vmcnt<0>();

@@ -104,7 +104,7 @@ __global__ void __launch_bounds__(kThreads) k_syrk(const char* XT, int64_t pitch
     src.b[i] = XT + (int64_t(tj) * kTile + load_row<Cfg>(i)) * pitch_bytes + k_off +
                load_seg_bytes<Cfg>(i);
   f4 acc[Cfg::MB][Cfg::NB];
-  gemm_tile_mainloop<Cfg, T>(acc, src, s1 - s0, lds0, lds1, nullptr);
+  gemm_tile_mainloop<Cfg, T>(acc, src, s1 - s0, lds0, lds1);
   float* P = part + size_t(sp) * size_t(dp) * size_t(dp);
 #pragma unroll
   for (int mi = 0; mi < 4; ++mi)

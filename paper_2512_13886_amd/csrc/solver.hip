@@ -30,6 +30,8 @@
 
 #include "common.h"
 #include "readback.h"
+#include "gemm128.h"
+#include "gemm256.h"
 #include "gemm_core.h"
 
 namespace optima {
@@ -85,6 +87,23 @@ __device__ inline RowCoef row_coef(const ProductArgs& p, int j, float L) {
     c.eta1 = (k + 2.f) / (2.f * L);
   }
   return c;
+}
+
+// Column and step coefficients of a tile's rows, put into LDS before the main
+// loop: read in the epilogue, the active list and then the column's iteration
+// count would be two dependent loads and three divisions ahead of every update.
+struct TileRow {
+  int j;
+  RowCoef c;
+};
+template <int MODE, int BM>
+__device__ inline void load_tile_rows(const ProductArgs& p, int m0, TileRow (&info)[BM]) {
+  const float L = (MODE == kFused || MODE == kStore) ? *p.Lp : 0.f;
+  for (int t = threadIdx.x; t < BM; t += blockDim.x) {
+    const int r = min(m0 + t, p.n_rows - 1);
+    const int j = p.rows ? p.rows[r] : r;
+    info[t] = TileRow{j, row_coef<MODE>(p, j, L)};
+  }
 }
 
 __device__ inline float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -410,9 +429,9 @@ __global__ void __launch_bounds__(ProductTile::kThreads) k_product(ProductArgs p
     src.b[i] = b_base + size_t(n0 + load_row<Cfg>(i)) * p.dp * 4 + k_off + load_seg_bytes<Cfg>(i);
   f4 acc[Cfg::MB][Cfg::NB];
   if (PREC == kPrecBf16x3)
-    gemm_tile_mainloop<Cfg, Bf16x3Tag>(acc, src, s1 - s0, lds0, lds1, nullptr);
+    gemm_tile_mainloop<Cfg, Bf16x3Tag>(acc, src, s1 - s0, lds0, lds1);
   else
-    gemm_tile_mainloop<Cfg, float>(acc, src, s1 - s0, lds0, lds1, nullptr);
+    gemm_tile_mainloop<Cfg, float>(acc, src, s1 - s0, lds0, lds1);
 
   stage_tile<Cfg>(acc, lds0, lds1);
   __syncthreads();
@@ -435,68 +454,104 @@ __global__ void __launch_bounds__(ProductTile::kThreads) k_product(ProductArgs p
   }
 }
 
-// The dense products on 256 x 128 tiles of 8 waves, one workgroup per CU,
-// for long contractions or large batches (wide_tile_path): a quarter fewer
-// operand bytes per flop than the 128 x 128 tile, whose loads from L2 bound
-// it there. Three
-// 48 KiB stage buffers keep two stages loading during each stage's MFMAs.
-// The 128 KiB accumulator tile is staged for the epilogue through them (see
-// wide_stage_row). Split ranges, partial sums and the epilogue work as in
-// k_product, with partial rows padded to the 256-row tile.
-using WideTile = TileCfg<256, 128, 4, 2, 3>;
-constexpr int kWideMinDim = 8192;    // with batches of at least kWideMinRows columns
-constexpr int kWideMinRows = 256;
-constexpr int kWideMidDim = 4096;    // with batches of at least kWideMidRows columns
-constexpr int kWideMidRows = 4096;
+// The dense products on the 256 x 256 tiles of gemm256.h, one workgroup per CU.
+// Split ranges, partial sums and the epilogue work as in k_product, with
+// partial rows padded to the 256-row tile; the accumulators are staged for the
+// epilogue in two halves of 128 columns.
+template <int MODE>
+__global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p, int splits,
+                                                                  float* part) {
+  using Cfg = Tile256;
+  __shared__ __attribute__((aligned(1024))) char l0[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l1[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l2[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l3[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l4[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l5[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l6[Cfg::kHalfBytes];
+  __shared__ __attribute__((aligned(1024))) char l7[Cfg::kHalfBytes];
+  __shared__ TileRow info[Cfg::BM];
+  const int tiles_m = (p.n_rows + Cfg::BM - 1) / Cfg::BM;
+  const int tiles_n = (p.dp + Cfg::BN - 1) / Cfg::BN;
+  const int n_tiles = tiles_m * tiles_n;
+  const int lin = blockIdx.x % n_tiles;
+  const int sp = blockIdx.x / n_tiles;
+  int tm, tn;
+  tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
+  const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
+  load_tile_rows<MODE>(p, m0, info);
+  const int stages = p.dp * 4 / Cfg::kSRB;
+  const int s0 = int(int64_t(stages) * sp / splits);
+  const int s1 = int(int64_t(stages) * (sp + 1) / splits);
 
-// Where the wide tile beats the 128 x 128 tile, whose two workgroups per CU
-// overlap one's update epilogue with the other's main loop. At d = 4096 the
-// two tie at 4096 columns; the wide tile is 7 % faster over the 7600 to
-// 14336 columns of the gate/up solves and 8 % slower at 1024.
-inline bool wide_tile_path(int64_t dp, int64_t n_rows) {
-  return (dp >= kWideMinDim && n_rows >= kWideMinRows) ||
-         (dp >= kWideMidDim && n_rows >= kWideMidRows);
-}
-
-// Epilogue staging of the wide tile's 256 x 128 fp32 accumulators: tile rows
-// 32 q .. 32 q + 31 take 16 KiB region q, the (q / 3)-th 16 KiB of buffer
-// q % 3, 512 bytes per row; 16-byte column chunk c of row r sits at physical
-// chunk c ^ (r & 31), which keeps the MFMA-layout writes and the row-chunk
-// reads free of bank conflicts.
-__device__ inline char* wide_stage_row(char* lds0, char* lds1, char* lds2, int r) {
-  const int q = r >> 5;
-  char* buf = q % 3 == 0 ? lds0 : (q % 3 == 1 ? lds1 : lds2);
-  return buf + (q / 3) * 16384 + (r & 31) * 512;
-}
-__device__ inline void wide_stage_tile(const f4 (&acc)[WideTile::MB][WideTile::NB], char* lds0,
-                                       char* lds1, char* lds2) {
-  static_assert(WideTile::BM == 256 && WideTile::BN == 128, "staging covers 256 x 128 tiles");
-  static_assert(WideTile::kBufBytes >= 3 * 16384, "three 16 KiB regions per stage buffer");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / WideTile::WGN, wn = wave % WideTile::WGN;
+  Operands256 src;
+  const size_t k_off = size_t(s0) * Cfg::kSRB;
 #pragma unroll
-  for (int mi = 0; mi < WideTile::MB; ++mi)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = wm * WideTile::MB * 16 + mi * 16 + 4 * (lane >> 4) + e;
-      char* row = wide_stage_row(lds0, lds1, lds2, r);
-#pragma unroll
-      for (int ni = 0; ni < WideTile::NB; ++ni) {
-        const int col = wn * WideTile::NB * 16 + ni * 16 + (lane & 15);
-        *reinterpret_cast<float*>(row + ((col >> 2) ^ (r & 31)) * 16 + (col & 3) * 4) =
-            acc[mi][ni][e];
-      }
+    for (int i = 0; i < Cfg::kHalfLoads; ++i) {
+      const int t = 128 * h + t256_load_row(i);
+      const int r = min(m0 + t, p.n_rows - 1);
+      const int j = p.rows ? p.rows[r] : r;
+      src.a[h][i] = reinterpret_cast<const char*>(p.Ap) + size_t(j) * p.dp * 4 + k_off +
+                    t256_seg_bytes(i);
+      src.b[h][i] = reinterpret_cast<const char*>(p.Bp) + size_t(min(n0 + t, p.dp - 1)) * p.dp * 4 +
+                    k_off + t256_seg_bytes(i);
     }
+  Acc256 acc;
+  gemm256_mainloop<Bf16x3Tag>(acc, src, s1 - s0, l0, l1, l2, l3, l4, l5, l6, l7);
+
+  float* P = part + size_t(sp) * size_t(tiles_m) * Cfg::BM * size_t(p.dp);
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    if (qb) __syncthreads();
+#pragma unroll
+    for (int qa = 0; qa < 2; ++qa)
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = t256_row(qa, mi, e);
+          char* row = t256_stage_row(l0, l1, l2, l3, l4, l5, l6, l7, r);
+#pragma unroll
+          for (int ni = 0; ni < 2; ++ni) {
+            const int c = t256_col(0, ni);
+            *reinterpret_cast<float*>(row + ((c >> 2) ^ (r & 31)) * 16 + (c & 3) * 4) =
+                acc.q[qa][qb][mi][ni][e];
+          }
+        }
+    __syncthreads();
+    if (n0 + 128 * qb >= p.dp) break;  // dp % 128 == 0: a half is all in or all out
+#pragma unroll 4
+    for (int q = 0; q < Cfg::BM * 32 / Cfg::kThreads; ++q) {
+      const int c = threadIdx.x + Cfg::kThreads * q;  // 16-byte chunk of the half
+      const int r = c >> 5, ch = c & 31;
+      const int rg = m0 + r;
+      if (rg >= p.n_rows) continue;
+      const float4 y = *reinterpret_cast<const float4*>(
+          t256_stage_row(l0, l1, l2, l3, l4, l5, l6, l7, r) + ((ch ^ (r & 31)) * 16));
+      const int n = n0 + 128 * qb + 4 * ch;
+      if (splits > 1) {
+        st4(P + size_t(rg) * p.dp + n, y);
+        continue;
+      }
+      const TileRow ri = info[r];
+      epilogue4<MODE, kPrecBf16x3>(p, ri.j, n, y, ri.c);
+    }
+  }
 }
 
-template <int MODE, int PREC>
-__global__ void __launch_bounds__(WideTile::kThreads) k_product_wide(ProductArgs p, int splits,
-                                                                     float* part) {
-  using Cfg = WideTile;
-  static_assert(Cfg::NBUF == 3, "three stage buffers");
-  __shared__ __attribute__((aligned(1024))) char lds0[Cfg::kBufBytes];
-  __shared__ __attribute__((aligned(1024))) char lds1[Cfg::kBufBytes];
-  __shared__ __attribute__((aligned(1024))) char lds2[Cfg::kBufBytes];
+// The dense products on the 128 x 128 tiles of gemm128.h, one workgroup per CU.
+// Split ranges, partial sums and the epilogue work as in k_product.
+template <int MODE>
+__global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs p, int splits,
+                                                                    float* part) {
+  using Cfg = Ring128;
+  __shared__ __attribute__((aligned(1024))) char b0[Cfg::kBufBytes];
+  __shared__ __attribute__((aligned(1024))) char b1[Cfg::kBufBytes];
+  __shared__ __attribute__((aligned(1024))) char b2[Cfg::kBufBytes];
+  __shared__ __attribute__((aligned(1024))) char b3[Cfg::kBufBytes];
+  __shared__ TileRow info[Cfg::BM];
   const int tiles_m = (p.n_rows + Cfg::BM - 1) / Cfg::BM;
   const int tiles_n = p.dp / Cfg::BN;
   const int n_tiles = tiles_m * tiles_n;
@@ -505,52 +560,54 @@ __global__ void __launch_bounds__(WideTile::kThreads) k_product_wide(ProductArgs
   int tm, tn;
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
-  const int stages = p.dp * 4 / Cfg::SRB;
+  load_tile_rows<MODE>(p, m0, info);
+  const int stages = p.dp * 4 / Cfg::kSRB;
   const int s0 = int(int64_t(stages) * sp / splits);
   const int s1 = int(int64_t(stages) * (sp + 1) / splits);
 
-  Operands<Cfg> src;
-  const size_t k_off = size_t(s0) * Cfg::SRB;
-  const char* a_base = PREC == kPrecBf16x3 ? reinterpret_cast<const char*>(p.Ap)
-                                           : reinterpret_cast<const char*>(p.A);
-  const char* b_base = PREC == kPrecBf16x3 ? reinterpret_cast<const char*>(p.Bp)
-                                           : reinterpret_cast<const char*>(p.B);
+  OperandsR128 src;
+  const size_t k_off = size_t(s0) * Cfg::kSRB;
 #pragma unroll
-  for (int i = 0; i < Cfg::kLoadsA; ++i) {
-    int r = m0 + load_row<Cfg>(i);
-    r = r < p.n_rows ? r : p.n_rows - 1;
+  for (int i = 0; i < Cfg::kLoads; ++i) {
+    const int t = t256_load_row(i);
+    const int r = min(m0 + t, p.n_rows - 1);
     const int j = p.rows ? p.rows[r] : r;
-    src.a[i] = a_base + size_t(j) * p.dp * 4 + k_off + load_seg_bytes<Cfg>(i);
+    src.a[i] = reinterpret_cast<const char*>(p.Ap) + size_t(j) * p.dp * 4 + k_off + t256_seg_bytes(i);
+    src.b[i] = reinterpret_cast<const char*>(p.Bp) + size_t(n0 + t) * p.dp * 4 + k_off +
+               t256_seg_bytes(i);
   }
-#pragma unroll
-  for (int i = 0; i < Cfg::kLoadsB; ++i)
-    src.b[i] = b_base + size_t(n0 + load_row<Cfg>(i)) * p.dp * 4 + k_off + load_seg_bytes<Cfg>(i);
-  f4 acc[Cfg::MB][Cfg::NB];
-  if (PREC == kPrecBf16x3)
-    gemm_tile_mainloop<Cfg, Bf16x3Tag>(acc, src, s1 - s0, lds0, lds1, lds2);
-  else
-    gemm_tile_mainloop<Cfg, float>(acc, src, s1 - s0, lds0, lds1, lds2);
+  AccR128 acc;
+  r128_mainloop<Bf16x3Tag>(acc, src, s1 - s0, b0, b1, b2, b3);
 
-  wide_stage_tile(acc, lds0, lds1, lds2);
+#pragma unroll
+  for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = r128_row(mi, e);
+      char* row = r128_stage_row(b0, b1, r);
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni) {
+        const int c = r128_col(ni);
+        *reinterpret_cast<float*>(row + ((c >> 2) ^ (r & 31)) * 16 + (c & 3) * 4) = acc.q[mi][ni][e];
+      }
+    }
   __syncthreads();
-  const float L = (MODE == kFused || MODE == kStore) ? *p.Lp : 0.f;
   float* P = part + size_t(sp) * size_t(tiles_m) * Cfg::BM * size_t(p.dp);
-  constexpr int kChunks = Cfg::BM * Cfg::BN / 4;
 #pragma unroll 4
-  for (int q = 0; q < kChunks / Cfg::kThreads; ++q) {
+  for (int q = 0; q < Cfg::BM * 32 / Cfg::kThreads; ++q) {
     const int c = threadIdx.x + Cfg::kThreads * q;  // 16-byte chunk of the tile
     const int r = c >> 5, ch = c & 31;
     const int rg = m0 + r;
     if (rg >= p.n_rows) continue;
-    const float4 y = *reinterpret_cast<const float4*>(wide_stage_row(lds0, lds1, lds2, r) +
+    const float4 y = *reinterpret_cast<const float4*>(r128_stage_row(b0, b1, r) +
                                                        ((ch ^ (r & 31)) * 16));
     const int n = n0 + 4 * ch;
     if (splits > 1) {
       st4(P + size_t(rg) * p.dp + n, y);
       continue;
     }
-    const int j = p.rows ? p.rows[rg] : rg;
-    epilogue4<MODE, PREC>(p, j, n, y, row_coef<MODE>(p, j, L));
+    const TileRow ri = info[r];
+    epilogue4<MODE, kPrecBf16x3>(p, ri.j, n, y, ri.c);
   }
 }
 
@@ -2190,6 +2247,71 @@ int choose_splits_one_per_cu(int tiles, int stages, int rows_pad, int dp, size_t
   return best;
 }
 
+// Tile and number of K ranges of a dense bf16x3 product.
+enum class DenseTile { kSmall, kRing128, k256 };  // k_product, k_product_ring, k_product256
+struct DensePlan {
+  DenseTile tile;
+  int splits;
+};
+
+// Bytes per output that a product's epilogue moves.
+int epilogue_bytes(int mode) { return mode == kFused ? 33 : mode == kStore ? 16 : mode == kPlain ? 4 : 8; }
+
+// The cheapest by a model of the launch in microseconds: rounds of workgroups
+// over the chip, each its stages and a fixed part (start, first fetches,
+// staging), then the outputs' bytes and, for S ranges, the partial sums' and a
+// second launch. A stage takes less while part of the chip is idle (the loads
+// and the clock are shared), down to least_us. The constants are fits to 16
+// iterations of solves with d from 512 to 14336 and 256 to 14336 columns; the
+// model is within 8 % of most of them. us an iteration, and what each tile would take (k_product,
+// k_product_ring, k_product256; splits chosen for each):
+//   d = 14336, 4096 columns   4350  4090  3390
+//   d = 4096,  4096 columns    424   415   332
+//   d = 4096,  1024 columns    111    95   103
+//   d = 4096,   256 columns     39    36    48
+//   d = 2048,  4096 columns    115   119   124
+//   d = 1024,  4096 columns     53    42    62
+// k_product's two workgroups a CU make its rounds twice as wide and hide part
+// of its epilogue; the ring keeps a CU's loads busy with one workgroup, and the
+// 256 x 256 tile loads half as much for the same outputs.
+DensePlan plan_dense(int64_t n_rows, int64_t dp, int out_bytes, size_t part_cap) {
+  struct Tile {
+    DenseTile id;
+    int side, per_cu;
+    double stage_us, least_us, fixed_us;
+  };
+  static constexpr Tile kTiles[] = {{DenseTile::kSmall, 128, 2, 1.27, 1.0, 8.0},
+                                    {DenseTile::kRing128, 128, 1, 0.58, 0.45, 8.0},
+                                    {DenseTile::k256, 256, 1, 2.05, 1.45, 6.0}};
+  constexpr double kBytesPerUs = 8.5e6, kLaunchUs = 5.0;
+  const int n_cu = device_cu_count();
+  const int64_t stages = dp / 32;
+  const double outputs = double(n_rows) * double(dp);
+  DensePlan best{DenseTile::kSmall, 1};
+  double best_us = 1e30;
+  for (const Tile& t : kTiles) {
+    const int64_t tiles_m = ceil_div(n_rows, t.side);
+    const int64_t tiles = tiles_m * ceil_div(dp, t.side);
+    for (int S = 1; S <= kMaxSplits && S <= stages; ++S) {
+      if (S > 1 && (tiles * S > kMaxSplitTiles ||
+                    size_t(S) * size_t(tiles_m * t.side) * size_t(dp) > part_cap))
+        break;
+      const int64_t slots = int64_t(t.per_cu) * n_cu, full = tiles * S / slots;
+      const double part = double(tiles * S % slots) / double(slots);
+      const double per_stage =
+          full * t.stage_us + (part > 0.0 ? std::max(t.least_us, part * t.stage_us) : 0.0);
+      double us = double(ceil_div(stages, S)) * per_stage +
+                  double(full + (part > 0.0)) * t.fixed_us + outputs * out_bytes / kBytesPerUs;
+      if (S > 1) us += outputs * 8.0 * S / kBytesPerUs + kLaunchUs;
+      if (us < best_us) {
+        best_us = us;
+        best = DensePlan{t.id, S};
+      }
+    }
+  }
+  return best;
+}
+
 // Whether the iteration products (kFused / kStore) of n_rows active columns
 // run the few-column kernels.
 bool few_column_path(int prec, int n_rows, int dp) {
@@ -2292,23 +2414,27 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
     }
   }
   if constexpr (PREC == kPrecBf16x3) {
-    if (wide_tile_path(p.dp, p.n_rows)) {
-      const int tiles_m = int(ceil_div(p.n_rows, WideTile::BM));
-      const int tiles_n = p.dp / WideTile::BN;
-      const int rows_pad = tiles_m * WideTile::BM;
-      const int S = choose_splits_one_per_cu(tiles_m * tiles_n, p.dp * 4 / WideTile::SRB,
-                                             rows_pad, p.dp, l.part_elems);
-      hipLaunchKernelGGL((k_product_wide<MODE, PREC>), dim3(tiles_m * tiles_n * S),
-                         dim3(WideTile::kThreads), 0, s, p, S, l.part);
+    const DensePlan plan = plan_dense(p.n_rows, p.dp, epilogue_bytes(MODE), l.part_elems);
+    const int bm = plan.tile == DenseTile::k256 ? Tile256::BM : kTile;
+    const int tiles_m = int(ceil_div(p.n_rows, bm)), tiles_n = int(ceil_div(p.dp, bm));
+    const dim3 grid(unsigned(tiles_m * tiles_n * plan.splits));
+    if (plan.tile == DenseTile::k256)
+      hipLaunchKernelGGL((k_product256<MODE>), grid, dim3(Tile256::kThreads), 0, s, p, plan.splits,
+                         l.part);
+    else if (plan.tile == DenseTile::kRing128)
+      hipLaunchKernelGGL((k_product_ring<MODE>), grid, dim3(Ring128::kThreads), 0, s, p,
+                         plan.splits, l.part);
+    else
+      hipLaunchKernelGGL((k_product<MODE, PREC>), grid, dim3(ProductTile::kThreads), 0, s, p,
+                         plan.splits, l.part);
+    OPTIMA_LAUNCH_CHECK();
+    if (plan.splits > 1) {
+      const dim3 g(unsigned(p.n_rows), unsigned(ceil_div(p.dp, 4 * kThreads)));
+      hipLaunchKernelGGL((k_split_epilogue<MODE, PREC>), g, dim3(kThreads), 0, s, p, plan.splits,
+                         tiles_m * bm, static_cast<const float*>(l.part));
       OPTIMA_LAUNCH_CHECK();
-      if (S > 1) {
-        const dim3 g(unsigned(p.n_rows), unsigned(ceil_div(p.dp, 4 * kThreads)));
-        hipLaunchKernelGGL((k_split_epilogue<MODE, PREC>), g, dim3(kThreads), 0, s, p, S,
-                           rows_pad, static_cast<const float*>(l.part));
-        OPTIMA_LAUNCH_CHECK();
-      }
-      return OPTIMA_OK;
     }
+    return OPTIMA_OK;
   }
   const bool sparse = PREC == kPrecSparse;
   const int bm = sparse ? SpTile::BM : kTile;

@@ -1,0 +1,66 @@
+"""The dense bf16x3 products on every tile that their plan takes, at the tiles'
+and loops' remainders: ragged batches, half a 256-wide tile at the end of H,
+split contractions down to one stage a range. Columns are independent, so the
+oracle runs on a sample of them, the batch's last rows among it."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import dev, gpu_solve, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    import paper_2512_13886_amd as lib
+    return lib
+
+
+# (d, columns): the 256 x 256 tile with a half tile of H and a ragged last row
+# tile; the same split in three; the 128 x 128 ring with one, two and three
+# stages left over and split into 5 and 16 ranges; the 4-wave 128 x 128 tile.
+@pytest.mark.parametrize("d, n", [(1100, 9000), (2944, 1500), (2176, 1030), (1152, 2000),
+                                  (300, 300), (640, 700), (512, 33), (1100, 6000)])
+def test_products_match_the_oracle(L, d, n):
+    rng = np.random.default_rng(d + n)
+    A = rng.standard_normal((d + 64, d)) * np.exp(rng.normal(0.0, 0.5, d))
+    H = A.T @ A
+    H = ((H + H.T) / 2 + 0.01 * np.trace(H) / d * np.eye(d)).astype(np.float32)
+    W0 = (0.02 * rng.standard_normal((n, d))).astype(np.float32)
+    M = (rng.random((n, d)) < 0.5).astype(np.uint8)
+    M[0] = 1  # dense products
+    lam = np.float32(1.05 * np.linalg.norm(H.astype(np.float64) @ rng.standard_normal(d)))
+    W, st, info = gpu_solve(L, to_dev(H), to_dev(np.array([lam])), W0, M,
+                            L.SolverOpts.default(max_iters=6, fixed_iters=1))
+    assert info["sparse_products"] == 0
+    W = W.cpu().numpy()
+    assert np.all(W[M == 0].view(np.uint32) == 0)
+    cols = np.unique(np.concatenate([rng.choice(n, min(n, 24), replace=False),
+                                     np.arange(max(0, n - 8), n)]))
+    ref = oracle.rapdhg(H.astype(np.float64), W0[cols], M[cols], float(lam),
+                        oracle.SolverOptions(max_iters=6, fixed_iters=True))
+    # Before the first check both follow the same continuous map; bf16x3 products
+    # are off by up to 3 * 2^-16 each.
+    err = np.linalg.norm(W[cols] - ref.W, axis=1) / np.linalg.norm(ref.W, axis=1)
+    assert err.max() <= 1e-4
+    np.testing.assert_allclose(st["f_initial"][cols], ref.f_initial, rtol=1e-5, atol=1e-12)
+
+
+def test_conjugate_gradients_on_the_large_tile(L):
+    # kPlain products: 4096 columns of 1024, one range, 256 x 256 tiles.
+    d, n = 1024, 9000
+    g = torch.Generator(device=dev()).manual_seed(5)
+    A = torch.randn(2 * d, d, generator=g, device=dev(), dtype=torch.float64)
+    H = (A.t() @ A + d * torch.eye(d, device=dev(), dtype=torch.float64)).float()
+    H = torch.tril(H) + torch.tril(H, -1).t()
+    W0 = 0.02 * torch.randn(n, d, generator=g, device=dev())
+    M = (torch.rand(n, d, generator=g, device=dev()) < 0.5).to(torch.uint8)
+    W, _, _ = gpu_solve(L, H, None, W0, M,
+                        L.SolverOpts.default(method=L.METHOD_CG, max_iters=40, fixed_iters=1))
+    x = W.double()
+    r = torch.where(M != 0, (W0.double() - x) @ H.double(), 0.0)
+    b = torch.where(M != 0, W0.double() @ H.double(), 0.0)
+    assert bool((W[M == 0] == 0).all())
+    assert float((r.norm(dim=1) / b.norm(dim=1)).max()) <= 1e-4
