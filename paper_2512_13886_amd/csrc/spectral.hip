@@ -543,26 +543,39 @@ __global__ void k_copy_sub_iters(const SubState* st, int32_t* iters) { *iters = 
 // ---------------------------------------------------------------------------
 //
 // Step j (0-based) of the symmetric Lanczos process with full
-// reorthogonalisation, six launches:
-//   k_lz_matvec  q_j = w / ||w|| (w: the previous step's residual, or v0),
-//                y = H q_j (one wave per row, HBM-bound), and per workgroup
-//                the partial sums of q_i . y, i <= j;
-//   k_lz_coef    c_i = q_i . y (fixed-order sums of those partials);
-//   k_lz_orth    w = y - sum_i c_i q_i, and partial sums of q_i . w;
-//   k_lz_coef    c'_i = q_i . w;
-//   k_lz_orth    w <- w - sum_i c'_i q_i, and partial sums of ||w||^2;
-//   k_lz_finish  alpha_j = c_j + c'_j, beta_j = ||w||, and the largest
-//                eigenvalue of T = tridiag(beta; alpha; beta) by Sturm-count
-//                multisection in fp64; the stopping test.
-// In exact arithmetic c_i vanishes for i < j - 1, c_(j-1) = beta_(j-1) and
-// c_j = alpha_j: the two passes are the three-term recurrence followed by one
-// more Gram-Schmidt pass over the whole basis, in classical form. The basis
-// is kept in fp32 (pitch dp), every sum in fp64. A set `conv` makes every
-// later launch return at once.
+// reorthogonalisation, four launches:
+//   k_lz_product  the parts of H w (w: the previous step's residual, or v0),
+//                 HBM-bound; one workgroup more finishes step j - 1:
+//                 alpha, beta, the largest eigenvalue of T = tridiag(beta;
+//                 alpha; beta) by Sturm-count multisection in fp64, and the
+//                 stopping test;
+//   k_lz_gather   q_j = w / ||w||, y = H q_j from the parts, and per workgroup
+//                 the partial sums of q_i . y, i <= j;
+//   k_lz_orth     c_i = q_i . y, w = y - sum_i c_i q_i, and partial sums of
+//                 q_i . w;
+//   k_lz_orth     c'_i = q_i . w, w <- w - sum_i c'_i q_i, and partial sums of
+//                 ||w||^2;
+// then alpha_j = c_j + c'_j and beta_j = ||w||. In exact arithmetic c_i
+// vanishes for i < j - 1, c_(j-1) = beta_(j-1) and c_j = alpha_j: the two
+// passes are the three-term recurrence followed by one more Gram-Schmidt pass
+// over the whole basis, in classical form. The basis is kept in fp32 (pitch
+// dp), every sum over a vector's entries in fp64 beyond 256 of them. A set
+// `conv` makes every later launch return at once: the product of step j may run
+// beside the finish that stops at step j - 1, and is then not used.
+//
+// The small kernels are bound by latency: each workgroup sums the coefficients'
+// partials itself, which saves two launches a step, and the finish runs beside
+// the product. A step takes 26 us at d = 1000 and 110 us at d = 14336; with a
+// launch for each of the two coefficient sums and for the finish (24 us, of which
+// 512 LDS atomics on one word a round and a reciprocal in every pivot's chain
+// were most), and all of H read, it took 37 and 194 us.
 
 constexpr int kLzMax = OPTIMA_LANCZOS_MAX_STEPS;
-constexpr int kLzRows = 64;                 // rows per workgroup of k_lz_orth
-constexpr int kLzFinThreads = 512;          // multisection points per round
+constexpr int kLzThreads = 512;
+constexpr int kLzWaves = kLzThreads / 64;
+constexpr int kLzRows = 128;                // rows per workgroup of k_lz_gather and k_lz_orth
+constexpr int kLzTile = 256;                // side of a tile of k_lz_product
+constexpr int kLzFullRows = 2 * kLzWaves;   // rows per workgroup of its full-row form
 constexpr double kLzBreakdown = 1e-6;       // beta_j <= this * theta_j: K_j invariant
 constexpr double kLzWidth = 1e-12;          // relative width that ends the multisection
 constexpr int kLzRounds = 8;
@@ -571,15 +584,15 @@ constexpr double kLzGeoSpan = 44.0;         // first round: offsets W 2^-44 .. W
 struct LzState {
   double alpha[kLzMax];
   double beta[kLzMax];
-  double c[2][kLzMax];  // coefficients of the two Gram-Schmidt passes
-  double inv;           // 1 / ||w|| of the vector that becomes q_j
+  double cj[2];         // q_j's coefficient in the two Gram-Schmidt passes of the step
+  double inv0;          // 1 / ||v0||
   double theta;         // largest Ritz value after the last finished step
   double theta_lo;      // a value not above it (the final bracket's lower end)
   int conv;
   int steps;
 };
 
-// w = v0, inv = 1 / ||v0||. A zero start vector ends at once with 0; a
+// w = v0, inv0 = 1 / ||v0||. A zero start vector ends at once with 0; a
 // non-finite one with NaN.
 __global__ void __launch_bounds__(1024) k_lz_init(const float* v0, int64_t d, float* w,
                                                   LzState* st, float* lambda_out) {
@@ -597,7 +610,7 @@ __global__ void __launch_bounds__(1024) k_lz_init(const float* v0, int64_t d, fl
     double t = 0.0;
     for (int k = 0; k < 16; ++k) t += red[k];
     const bool ok = t > 0.0 && isfinite(t);
-    st->inv = ok ? 1.0 / sqrt(t) : 0.0;
+    st->inv0 = ok ? 1.0 / sqrt(t) : 0.0;
     st->theta = 0.0;
     st->theta_lo = -INFINITY;
     st->conv = ok ? 0 : 1;
@@ -606,127 +619,41 @@ __global__ void __launch_bounds__(1024) k_lz_init(const float* v0, int64_t d, fl
   }
 }
 
-template <bool VEC4>
-__global__ void __launch_bounds__(kThreads) k_lz_matvec(const float* H, int64_t d, int64_t dp,
-                                                        const float* w, float* Q, int j, float* y,
-                                                        double* part, int nblk, LzState* st) {
-  if (st->conv) return;
-  __shared__ float ys[kRowsPerBlock], qs[kRowsPerBlock];
-  const double inv = st->inv;
-  float* qj = Q + int64_t(j) * dp;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int q = 0; q < kRowsPerWave; ++q) {
-    const int lr = wv * kRowsPerWave + q;
-    const int64_t row = int64_t(blockIdx.x) * kRowsPerBlock + lr;
-    float yr = 0.f, qr = 0.f;
-    if (row < d) {
-      yr = float(double(row_dot<VEC4>(H + row * d, w, d, lane)) * inv);
-      qr = float(double(w[row]) * inv);
-      if (lane == 0) {
-        y[row] = yr;
-        qj[row] = qr;
-      }
-    }
-    if (lane == 0) {
-      ys[lr] = yr;
-      qs[lr] = qr;
-    }
+// Whether all eigenvalues of the n x n tridiagonal matrix lie below x, by
+// Givens' Sturm sequence: with r_k = (-1)^k times the k-th leading principal
+// minor of T - x I, r_k = (x - a_k) r_(k-1) - b_(k-1)^2 r_(k-2), all eigenvalues
+// are below x exactly when every r_k > 0. ab[k] holds (a_k, b_(k-1)^2),
+// b_(-1) = 0. One dependent multiply-add a step (the ratios of consecutive
+// minors, which need no scaling, take a reciprocal); every fourth step divides
+// the pair by a power of two, which keeps it in range (entries of T come from
+// fp32 matrices: below 1e43 and, off the diagonal, above 1e-6 of the largest).
+__device__ inline bool lz_all_below(const double2* ab, int n, double x) {
+  double r1 = 1.0, r2 = 0.0;
+  int sign = 0;  // an r_k of exactly 0 makes the next one negative
+  auto step = [&](double2 e) {
+    const double r = fma(x - e.x, r1, -e.y * r2);
+    sign |= __double2hiint(r);
+    r2 = r1;
+    r1 = r;
+  };
+  int k = 0;
+  double2 e0 = ab[0], e1 = ab[1], e2 = ab[2], e3 = ab[3];
+  for (; k + 4 <= n; k += 4) {
+    // The next four entries (the array goes on past n) load during the chain.
+    const double2 f0 = ab[k + 4], f1 = ab[k + 5], f2 = ab[k + 6], f3 = ab[k + 7];
+    step(e0);
+    step(e1);
+    step(e2);
+    step(e3);
+    const int ex = -__builtin_amdgcn_frexp_exp(r1);
+    r1 = __builtin_amdgcn_ldexp(r1, ex);
+    r2 = __builtin_amdgcn_ldexp(r2, ex);
+    e0 = f0, e1 = f1, e2 = f2, e3 = f3;
   }
-  __syncthreads();
-  const int64_t r0 = int64_t(blockIdx.x) * kRowsPerBlock;
-  for (int i = threadIdx.x; i <= j; i += kThreads) {
-    double sum = 0.0;
-    for (int r = 0; r < kRowsPerBlock && r0 + r < d; ++r) {
-      const float qv = i == j ? qs[r] : Q[int64_t(i) * dp + r0 + r];
-      sum += double(qv) * double(ys[r]);
-    }
-    part[int64_t(i) * nblk + blockIdx.x] = sum;
-  }
-}
-
-// c[pass][i] = sum over blocks of part[i][*] in a fixed order, one wave per i.
-__global__ void __launch_bounds__(kThreads) k_lz_coef(const double* part, int nblk, int j,
-                                                      int pass, LzState* st) {
-  if (st->conv) return;
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (i > j) return;
-  const double* p = part + int64_t(i) * nblk;
-  double s0 = 0.0, s1 = 0.0;
-  int b = lane;
-  for (; b + 64 < nblk; b += 128) {
-    s0 += p[b];
-    s1 += p[b + 64];
-  }
-  if (b < nblk) s0 += p[b];
-  double s = s0 + s1;
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (lane == 0) st->c[pass][i] = s;
-}
-
-// One Gram-Schmidt pass over kLzRows rows: w = src - sum_{i<=j} c[pass]_i q_i
-// (wave v takes the terms i = v mod 4, summed in LDS in a fixed order). Pass
-// 0 then leaves the partial sums of q_i . w in part[i][block]; pass 1 the
-// partial ||w||^2 in norm_part[block].
-__global__ void __launch_bounds__(kThreads) k_lz_orth(const float* Q, int64_t d, int64_t dp,
-                                                      int j, int pass, const float* src,
-                                                      float* w, double* part, int nblk,
-                                                      double* norm_part, LzState* st) {
-  if (st->conv) return;
-  constexpr int kW = kThreads / 64;
-  __shared__ double sum[kW][kLzRows];
-  __shared__ float ws[kLzRows];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t r0 = int64_t(blockIdx.x) * kLzRows, r = r0 + lane;
-  const bool in = r < d;
-  const double* c = st->c[pass];
-  double acc = 0.0;
-  if (in)
-    for (int i = wv; i <= j; i += kW) acc += c[i] * double(Q[int64_t(i) * dp + r]);
-  sum[wv][lane] = acc;
-  __syncthreads();
-  if (wv == 0) {
-    float wr = 0.f;
-    if (in) {
-      const double t = ((sum[0][lane] + sum[1][lane]) + sum[2][lane]) + sum[3][lane];
-      wr = float(double(src[r]) - t);
-      w[r] = wr;
-    }
-    ws[lane] = wr;
-  }
-  __syncthreads();
-  if (pass == 0) {
-    for (int i = wv; i <= j; i += kW) {
-      double s = in ? double(Q[int64_t(i) * dp + r]) * double(ws[lane]) : 0.0;
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (lane == 0) part[int64_t(i) * nblk + blockIdx.x] = s;
-    }
-  } else if (wv == 0) {
-    double s = double(ws[lane]) * double(ws[lane]);
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) norm_part[blockIdx.x] = s;
-  }
-}
-
-// Number of eigenvalues of the n x n tridiagonal matrix below x, from the
-// signs of the LDL^T pivots of T - x I (Sturm count). ab[k] holds (a_k,
-// b_(k-1)^2), b_(-1)^2 = 0. Pivots smaller than pivmin in magnitude become
-// -pivmin. Each pivot's reciprocal is the hardware estimate refined by one
-// Newton step (error a few ulps); the count tolerates relative errors of
-// that size in the pivots, since they amount to a tiny perturbation of T.
-__device__ inline int lz_count_below(const double2* ab, int n, double x, double pivmin) {
-  double p = 1.0;  // the pivot before the first one: b_(-1)^2 / p adds nothing
-  int cnt = 0;
-  for (int k = 0; k < n; ++k) {
-    const double2 e = ab[k];
-    double r = __builtin_amdgcn_rcp(p);
-    r = fma(r, fma(-p, r, 1.0), r);
-    p = fma(-e.y, r, e.x - x);
-    if (fabs(p) < pivmin) p = -pivmin;
-    cnt += p < 0.0;
-  }
-  return cnt;
+  if (k < n) step(e0);
+  if (k + 1 < n) step(e1);
+  if (k + 2 < n) step(e2);
+  return sign >= 0;
 }
 
 // Multisection point t of round `round` in [lo, hi]: the first round spaces
@@ -735,112 +662,360 @@ __device__ inline int lz_count_below(const double2* ab, int n, double x, double 
 // uniformly.
 __device__ inline double lz_point(double lo, double hi, int round, int t) {
   if (round == 0)
-    return t == kLzFinThreads - 1
+    return t == kLzThreads - 1
                ? hi
-               : lo + (hi - lo) * exp2(-kLzGeoSpan * (1.0 - double(t + 1) / kLzFinThreads));
-  return lo + (hi - lo) / double(kLzFinThreads + 1) * double(t + 1);
+               : lo + (hi - lo) * exp2(-kLzGeoSpan * (1.0 - double(t + 1) / kLzThreads));
+  return lo + (hi - lo) / double(kLzThreads + 1) * double(t + 1);
 }
 
 // alpha_j, beta_j, theta_j = lambda_max(T_(j+1)) and the stopping decision:
 // stop when |theta_j - theta_(j-1)| <= tol theta_j, when beta_j <=
 // kLzBreakdown theta_j, or after n_max steps. One workgroup; the largest
 // eigenvalue of T to a relative width of kLzWidth.
-__global__ void __launch_bounds__(kLzFinThreads) k_lz_finish(const double* norm_part, int nblk,
-                                                             int j, int n_max, float tol,
-                                                             LzState* st, float* lambda_out) {
-  if (st->conv) return;
-  constexpr int kW = kLzFinThreads / 64;
-  __shared__ double2 ab[kLzMax];
-  __shared__ double rs[kW], ramax[kW], rgmax[kW], rbmax[kW];
-  __shared__ int rbad[kW];
-  __shared__ double lo_s, hi_s;
-  __shared__ int first_all;
+__device__ inline void lz_finish(const double* norm_part, int nblk, int j, int n_max, float tol,
+                                 LzState* st, float* lambda_out) {
+  __shared__ double2 ab[kLzMax + 8];  // lz_all_below reads up to 8 entries past n
+  __shared__ double rs[kLzWaves], ramax[kLzWaves], rgmax[kLzWaves];
+  __shared__ int rbad[kLzWaves];
+  __shared__ double xs[kLzThreads];
+  __shared__ int first_w[kLzWaves];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6, n = j + 1;
-  const double alpha = st->c[0][j] + st->c[1][j];
+  // Every load goes out before the first is used: they come from other XCDs'
+  // kernels, one miss in all instead of one after the other.
+  const int conv = st->conv;
+  const double alpha0 = st->cj[0], alpha1 = st->cj[1];
+  const double theta_prev = st->theta, lo_prev = st->theta_lo;
+  const double at = t < j ? st->alpha[t] : 0.0;
+  const double bl = t > 0 && t < n ? st->beta[t - 1] : 0.0, br = t < j ? st->beta[t] : 0.0;
   // ||w||^2, and per row of T its diagonal and Gershgorin bound.
   double s = 0.0;
-  for (int k = t; k < nblk; k += kLzFinThreads) s += norm_part[k];
-  double am = -INFINITY, gm = -INFINITY, bm = 0.0;
+  for (int k = t; k < nblk; k += kLzThreads) s += norm_part[k];
+  if (conv) return;
+  const double alpha = alpha0 + alpha1;
+  double am = -INFINITY, gm = -INFINITY;
   int bad = 0;
   if (t < n) {
-    const double a = t == j ? alpha : st->alpha[t];
-    const double bl = t > 0 ? st->beta[t - 1] : 0.0, br = t < j ? st->beta[t] : 0.0;
+    const double a = t == j ? alpha : at;
     ab[t] = make_double2(a, bl * bl);
     am = a;
     gm = a + fabs(bl) + fabs(br);
-    bm = br * br;
     bad = !(isfinite(a) && isfinite(bl));
   }
   for (int o = 32; o > 0; o >>= 1) {
     s += __shfl_xor(s, o, 64);
     am = fmax(am, __shfl_xor(am, o, 64));
     gm = fmax(gm, __shfl_xor(gm, o, 64));
-    bm = fmax(bm, __shfl_xor(bm, o, 64));
     bad |= __shfl_xor(bad, o, 64);
   }
   if (lane == 0) {
     rs[wv] = s;
     ramax[wv] = am;
     rgmax[wv] = gm;
-    rbmax[wv] = bm;
     rbad[wv] = bad;
   }
   __syncthreads();
-  double beta2 = 0.0, amax = -INFINITY, gmax = -INFINITY, bmax = 0.0;
-  for (int k = 0; k < kW; ++k) {
+  double beta2 = 0.0, amax = -INFINITY, gmax = -INFINITY;
+  for (int k = 0; k < kLzWaves; ++k) {
     beta2 += rs[k];
     amax = fmax(amax, ramax[k]);
     gmax = fmax(gmax, rgmax[k]);
-    bmax = fmax(bmax, rbmax[k]);
     bad |= rbad[k];
   }
   const bool finite = !bad && isfinite(beta2);
-  double theta;
+  double theta, theta_lo = -INFINITY;
   if (!finite) {
     theta = __builtin_nan("");
   } else {
     // lambda_max(T) lies in [max(a_k, theta_lo of the previous step),
     // Gershgorin bound]: a diagonal entry is a Rayleigh quotient, and T_j
     // contains T_(j-1) as a leading block (Cauchy interlacing).
-    const double pivmin = 1e-290 * fmax(1.0, bmax);
-    if (t == 0) {
-      lo_s = fmax(amax, st->theta_lo);
-      hi_s = gmax + fmax(fabs(gmax) * 1e-14, 1e-300);
-    }
-    __syncthreads();
+    double lo = fmax(amax, lo_prev), hi = gmax + fmax(fabs(gmax) * 1e-14, 1e-300);
     for (int round = 0; round < kLzRounds; ++round) {
-      const double lo = lo_s, hi = hi_s;
       if (hi - lo <= kLzWidth * fmax(fabs(lo), fabs(hi))) break;
       const double x = lz_point(lo, hi, round, t);
-      if (t == 0) first_all = kLzFinThreads;
+      xs[t] = x;
       __syncthreads();
-      // count(x_t) is non-decreasing in t; the top eigenvalue lies between the
-      // last point with fewer than n eigenvalues below it and the first with n.
-      if (lz_count_below(ab, n, x, pivmin) == n) atomicMin(&first_all, t);
+      // The top eigenvalue lies between the last point with an eigenvalue at or
+      // above it and the first with none (one candidate a wave: 512 atomics on
+      // one word took longer than the sequences).
+      const uint64_t below = __ballot(lz_all_below(ab, n, x));
+      if (lane == 0) first_w[wv] = below ? 64 * wv + __ffsll((long long)below) - 1 : kLzThreads;
       __syncthreads();
-      if (t == 0) {
-        const int f = first_all;
-        lo_s = f == 0 ? lo : lz_point(lo, hi, round, f - 1);
-        hi_s = f == kLzFinThreads ? hi : lz_point(lo, hi, round, f);
-      }
+      int f = kLzThreads;
+#pragma unroll
+      for (int k = 0; k < kLzWaves; ++k) f = min(f, first_w[k]);
+      lo = f == 0 ? lo : xs[f - 1];
+      hi = f == kLzThreads ? hi : xs[f];
       __syncthreads();
     }
-    theta = 0.5 * (lo_s + hi_s);
+    theta_lo = lo;
+    theta = 0.5 * (lo + hi);
   }
   if (t == 0) {
     const double beta = sqrt(beta2);
     const bool done = !finite || n >= n_max ||
-                      (j >= 1 && fabs(theta - st->theta) <= double(tol) * fabs(theta)) ||
+                      (j >= 1 && fabs(theta - theta_prev) <= double(tol) * fabs(theta)) ||
                       beta <= kLzBreakdown * fabs(theta);
     st->alpha[j] = alpha;
     st->beta[j] = beta;
     st->theta = theta;
-    st->theta_lo = finite ? lo_s : -INFINITY;
+    st->theta_lo = theta_lo;
     st->steps = n;
-    st->inv = done ? 0.0 : 1.0 / beta;
     *lambda_out = float(theta);
     if (done) st->conv = 1;
   }
+}
+
+// Sums of 16 values per lane over the wave: the sum of v[i] ends in the four
+// lanes whose bits 5 to 2 are i (each exchange halves the values a lane keeps).
+__device__ inline float wave_sum16(const float (&v)[16], int lane) {
+  float a[8], b[4], c[2];
+  const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8, h2 = lane & 4;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    a[i] = (h5 ? v[8 + i] : v[i]) + __shfl_xor(h5 ? v[i] : v[8 + i], 32, 64);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    b[i] = (h4 ? a[4 + i] : a[i]) + __shfl_xor(h4 ? a[i] : a[4 + i], 16, 64);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+    c[i] = (h3 ? b[2 + i] : b[i]) + __shfl_xor(h3 ? b[i] : b[2 + i], 8, 64);
+  float r = (h2 ? c[1] : c[0]) + __shfl_xor(h2 ? c[0] : c[1], 4, 64);
+  r += __shfl_xor(r, 2, 64);
+  r += __shfl_xor(r, 1, 64);
+  return r;
+}
+
+// The parts of z = H w, ypart[slot][row] (pitch dp): z[row] is the sum of the
+// slots. Workgroup 0 finishes step j - 1 instead (j >= 1).
+//
+// Full rows (one slot, two rows a wave): the first step, which so meets a NaN or
+// Inf anywhere in H, and small matrices, where a launch is latency anyway.
+// SYM: H is symmetric, so only the 256 x 256 tiles on and below the diagonal
+// are read, half of the bytes that bound this kernel. Tile (I, J) gives rows I
+// the products with w_J (slot J) and, off the diagonal, rows J those of its
+// transpose with w_I (slot I). A wave takes 32 rows of the tile, 16 in flight
+// at a time; VEC4 loads 4 consecutive columns a lane (d % 4 == 0 and H 16-byte
+// aligned).
+template <bool VEC4, bool SYM>
+__global__ void __launch_bounds__(kLzThreads) k_lz_product(const float* H, int64_t d, int64_t dp,
+                                                           const float* w, float* ypart, int j,
+                                                           const double* norm_part, int nblk,
+                                                           int n_max, float tol, LzState* st,
+                                                           float* lambda_out) {
+  if (blockIdx.x == 0) {
+    if (j > 0) lz_finish(norm_part, nblk, j - 1, n_max, tol, st, lambda_out);
+    return;
+  }
+  if (st->conv) return;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.x - 1;
+  if constexpr (!SYM) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int64_t row = int64_t(b) * kLzFullRows + wv * 2 + q;
+      if (row < d) {
+        const float z = row_dot<VEC4>(H + row * d, w, d, lane);
+        if (lane == 0) ypart[row] = z;
+      }
+    }
+  } else {
+    __shared__ float vs[kLzWaves][kLzTile];
+    int I = int((sqrtf(8.f * float(b) + 1.f) - 1.f) * 0.5f);
+    while ((I + 1) * (I + 2) / 2 <= b) ++I;
+    while (I * (I + 1) / 2 > b) --I;
+    const int J = b - I * (I + 1) / 2;
+    const int64_t r0 = int64_t(I) * kLzTile + wv * 32, c0 = int64_t(J) * kLzTile;
+    // Column e of this lane: 4 lane + e, or lane + 64 e.
+    auto col = [&](int e) { return c0 + (VEC4 ? 4 * lane + e : lane + 64 * e); };
+    float wj[4], v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) wj[e] = col(e) < d ? w[col(e)] : 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float t[16][4], u[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int64_t row = r0 + 16 * h + i;
+        const float* p = H + (row < d ? row : d - 1) * d;  // past the end: added to nothing
+        if (VEC4) {
+          float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (col(0) < d) x = *reinterpret_cast<const float4*>(p + col(0));
+          t[i][0] = x.x, t[i][1] = x.y, t[i][2] = x.z, t[i][3] = x.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t[i][e] = col(e) < d ? p[col(e)] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int64_t row = r0 + 16 * h + i;
+        const float wi = row < d ? w[row] : 0.f;
+        u[i] = t[i][0] * wj[0] + t[i][1] * wj[1] + t[i][2] * wj[2] + t[i][3] * wj[3];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += t[i][e] * wi;
+      }
+      const float z = wave_sum16(u, lane);
+      const int64_t row = r0 + 16 * h + (lane >> 2);
+      if ((lane & 3) == 0 && row < d) ypart[int64_t(J) * dp + row] = z;
+    }
+    if (I == J) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) vs[wv][int(col(e) - c0)] = v[e];
+    __syncthreads();
+    if (threadIdx.x < kLzTile && c0 + threadIdx.x < d) {
+      float z = 0.f;
+      for (int k = 0; k < kLzWaves; ++k) z += vs[k][threadIdx.x];
+      ypart[int64_t(I) * dp + c0 + threadIdx.x] = z;
+    }
+  }
+}
+
+// Per workgroup of kLzRows rows: part[block][i] = sum over the rows of
+// q_i . y for i <= j (pitch ld; q_j from LDS), four vectors a wave at a time.
+__device__ inline void lz_dots(const float* Q, int64_t d, int64_t dp, int64_t r0, int j,
+                               const float* ys, const float* qs, double* part, int ld) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const bool in0 = r0 + lane < d, in1 = r0 + lane + 64 < d;
+  const double y0 = in0 ? ys[lane] : 0.f, y1 = in1 ? ys[lane + 64] : 0.f;
+  for (int i0 = wv; i0 <= j; i0 += 4 * kLzWaves) {
+    double s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = i0 + k * kLzWaves;
+      float a = 0.f, b = 0.f;
+      if (i <= j) {
+        const float* q = qs && i == j ? qs : Q + int64_t(i) * dp + r0;
+        if (in0) a = q[lane];
+        if (in1) b = q[lane + 64];
+      }
+      s[k] = double(a) * y0 + double(b) * y1;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[k] += __shfl_xor(s[k], o, 64);
+    if (lane == 0)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k * kLzWaves <= j) part[size_t(blockIdx.x) * ld + i0 + k * kLzWaves] = s[k];
+  }
+}
+
+// q_j = w inv and y = z inv with inv = 1 / ||w||, z the sum of the slots of
+// k_lz_product, and the partial sums of q_i . y.
+__global__ void __launch_bounds__(kLzThreads) k_lz_gather(const float* ypart, int slots,
+                                                          const float* w, int64_t d, int64_t dp,
+                                                          int j, float* Q, float* y, double* part,
+                                                          int ld, const double* norm_part,
+                                                          const LzState* st) {
+  if (st->conv) return;
+  constexpr int kGroups = kLzThreads / kLzRows;
+  __shared__ double sum[kGroups][kLzRows];
+  __shared__ float ys[kLzRows], qs[kLzRows];
+  __shared__ double inv_s;
+  const int t = threadIdx.x, r = t % kLzRows, grp = t / kLzRows;
+  const int64_t r0 = int64_t(blockIdx.x) * kLzRows, row = r0 + r;
+  double z = 0.0;
+  if (row < d) {
+#pragma unroll 8
+    for (int s = grp; s < slots; s += kGroups) z += double(ypart[int64_t(s) * dp + row]);
+  }
+  sum[grp][r] = z;
+  if (t < 64) {
+    double n2 = 0.0;
+    if (j > 0) {
+      for (int k = t; k < int(gridDim.x); k += 64) n2 += norm_part[k];
+      for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o, 64);
+    }
+    if (t == 0) inv_s = j > 0 ? 1.0 / sqrt(n2) : st->inv0;
+  }
+  __syncthreads();
+  if (t < kLzRows) {
+    float yr = 0.f, qr = 0.f;
+    if (row < d) {
+      double a = sum[0][r];
+#pragma unroll
+      for (int k = 1; k < kGroups; ++k) a += sum[k][r];
+      yr = float(a * inv_s);
+      qr = float(double(w[row]) * inv_s);
+      y[row] = yr;
+      Q[int64_t(j) * dp + row] = qr;
+    }
+    ys[r] = yr;
+    qs[r] = qr;
+  }
+  __syncthreads();
+  lz_dots(Q, d, dp, r0, j, ys, qs, part, ld);
+}
+
+// One Gram-Schmidt pass over kLzRows rows: c_i = the sum of part_in[*][i] in a
+// fixed order, w = src - sum_{i<=j} c_i q_i. Pass 0 then leaves the partial sums
+// of q_i . w in part_out, pass 1 the partial ||w||^2 in norm_part[block].
+__global__ void __launch_bounds__(kLzThreads) k_lz_orth(const float* Q, int64_t d, int64_t dp,
+                                                        int j, int pass, const float* src,
+                                                        float* w, const double* part_in,
+                                                        double* part_out, int ld,
+                                                        double* norm_part, LzState* st) {
+  if (st->conv) return;
+  constexpr int kGroups = kLzThreads / kLzRows;
+  __shared__ double c[kLzMax];
+  __shared__ double sum[kGroups][kLzRows];
+  __shared__ float ws[kLzRows];
+  const int t = threadIdx.x, r = t % kLzRows, grp = t / kLzRows;
+  for (int i0 = 0; i0 <= j; i0 += kLzRows) {
+    const int i = i0 + r;
+    double a = 0.0;
+    if (i <= j) {
+#pragma unroll 8
+      for (int k = grp; k < int(gridDim.x); k += kGroups) a += part_in[size_t(k) * ld + i];
+    }
+    sum[grp][r] = a;
+    __syncthreads();
+    if (t < kLzRows && i <= j) {
+      a = sum[0][r];
+#pragma unroll
+      for (int k = 1; k < kGroups; ++k) a += sum[k][r];
+      c[i] = a;
+      if (blockIdx.x == 0 && i == j) st->cj[pass] = a;
+    }
+    __syncthreads();
+  }
+  const int64_t r0 = int64_t(blockIdx.x) * kLzRows, row = r0 + r;
+  double acc = 0.0;
+  if (row < d) {
+#pragma unroll 8
+    for (int i = grp; i <= j; i += kGroups) acc += c[i] * double(Q[int64_t(i) * dp + row]);
+  }
+  sum[grp][r] = acc;
+  __syncthreads();
+  if (t < kLzRows) {
+    float wr = 0.f;
+    if (row < d) {
+      double a = sum[0][r];
+#pragma unroll
+      for (int k = 1; k < kGroups; ++k) a += sum[k][r];
+      wr = float(double(src[row]) - a);
+      w[row] = wr;
+    }
+    ws[r] = wr;
+  }
+  __syncthreads();
+  if (pass == 0) {
+    lz_dots(Q, d, dp, r0, j, ws, nullptr, part_out, ld);
+  } else if (t < 64) {
+    double s = double(ws[t]) * double(ws[t]) + double(ws[t + 64]) * double(ws[t + 64]);
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (t == 0) norm_part[blockIdx.x] = s;
+  }
+}
+
+// The finish of the last step, after which no product follows.
+__global__ void __launch_bounds__(kLzThreads) k_lz_close(const double* norm_part, int nblk, int j,
+                                                         int n_max, float tol, LzState* st,
+                                                         float* lambda_out) {
+  lz_finish(norm_part, nblk, j, n_max, tol, st, lambda_out);
 }
 
 __global__ void k_copy_lz_steps(const LzState* st, int32_t* steps) { *steps = st->steps; }
@@ -961,28 +1136,35 @@ optima_status subspace_iteration(const float* H, int64_t d, const float* V0, int
   return OPTIMA_OK;
 }
 
+// Widths from which k_lz_product reads one triangle of H (SYM) after the first
+// step. us a step, full rows and SYM: d = 2048 27.4 and 27.8, 3000 29.5 and 29.6,
+// 4096 33.1 and 30.1, 8192 67 and 47, 14336 179 and 110.
+constexpr int64_t kLzSymMinDim = 4096;
+
 // Workspace of the Lanczos process for at most m steps: the basis (m rows of
-// pitch dp), y, w, the partial sums of both passes and of the norm, state.
+// pitch dp), y, w, the product's slots, the partial sums of both passes and of
+// the norm, state.
 struct LzLayout {
-  float *Q, *y, *w;
+  float *Q, *y, *w, *ypart;
   double *part1, *part2, *norm_part;
   LzState* st;
   int64_t dp;
-  int nblk1, nblk2;
+  int slots, nblk;
 };
 
 LzLayout lz_layout(void* ws, int64_t d, int m, size_t* bytes) {
   Carver c(ws);
   LzLayout l{};
   l.dp = round_up(d, 64);
-  l.nblk1 = int(ceil_div(d, kRowsPerBlock));
-  l.nblk2 = int(ceil_div(d, kLzRows));
+  l.slots = d >= kLzSymMinDim ? int(ceil_div(d, kLzTile)) : 1;
+  l.nblk = int(ceil_div(d, kLzRows));
   l.Q = c.take<float>(size_t(m) * size_t(l.dp));
   l.y = c.take<float>(size_t(l.dp));
   l.w = c.take<float>(size_t(l.dp));
-  l.part1 = c.take<double>(size_t(m) * size_t(l.nblk1));
-  l.part2 = c.take<double>(size_t(m) * size_t(l.nblk2));
-  l.norm_part = c.take<double>(size_t(l.nblk2));
+  l.ypart = c.take<float>(size_t(l.slots) * size_t(l.dp));
+  l.part1 = c.take<double>(size_t(m) * size_t(l.nblk));
+  l.part2 = c.take<double>(size_t(m) * size_t(l.nblk));
+  l.norm_part = c.take<double>(size_t(l.nblk));
   l.st = c.take<LzState>(1);
   if (bytes) *bytes = c.bytes();
   return l;
@@ -1073,28 +1255,26 @@ optima_status spectral_lanczos(const float* H, int64_t d, const float* v0, int m
   hipLaunchKernelGGL(k_lz_init, dim3(1), dim3(1024), 0, s, v0, d, l.w, l.st, lambda_max);
   OPTIMA_LAUNCH_CHECK();
   const bool vec4 = (d % 4) == 0 && aligned16(H);
+  const int64_t tiles = ceil_div(d, kLzTile);
+  const dim3 rows(unsigned(l.nblk)), threads(kLzThreads);
   constexpr int kPoll = 8;
-  for (int j = 0; j < m; ++j) {
-    if (vec4)
-      hipLaunchKernelGGL(k_lz_matvec<true>, dim3(unsigned(l.nblk1)), dim3(kThreads), 0, s, H, d,
-                         l.dp, l.w, l.Q, j, l.y, l.part1, l.nblk1, l.st);
-    else
-      hipLaunchKernelGGL(k_lz_matvec<false>, dim3(unsigned(l.nblk1)), dim3(kThreads), 0, s, H, d,
-                         l.dp, l.w, l.Q, j, l.y, l.part1, l.nblk1, l.st);
+  int j = 0;
+  for (; j < m; ++j) {
+    const bool sym = j > 0 && l.slots > 1;
+    const dim3 grid(unsigned(1 + (sym ? tiles * (tiles + 1) / 2 : ceil_div(d, kLzFullRows))));
+    auto product = vec4 ? (sym ? k_lz_product<true, true> : k_lz_product<true, false>)
+                        : (sym ? k_lz_product<false, true> : k_lz_product<false, false>);
+    hipLaunchKernelGGL(product, grid, threads, 0, s, H, d, l.dp, l.w, l.ypart, j, l.norm_part,
+                       l.nblk, m, tol, l.st, lambda_max);
     OPTIMA_LAUNCH_CHECK();
-    const dim3 cg(unsigned(ceil_div(j + 1, kThreads / 64)));
-    hipLaunchKernelGGL(k_lz_coef, cg, dim3(kThreads), 0, s, l.part1, l.nblk1, j, 0, l.st);
+    hipLaunchKernelGGL(k_lz_gather, rows, threads, 0, s, l.ypart, sym ? l.slots : 1, l.w, d, l.dp,
+                       j, l.Q, l.y, l.part1, m, l.norm_part, l.st);
     OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_orth, dim3(unsigned(l.nblk2)), dim3(kThreads), 0, s, l.Q, d, l.dp, j,
-                       0, l.y, l.w, l.part2, l.nblk2, l.norm_part, l.st);
+    hipLaunchKernelGGL(k_lz_orth, rows, threads, 0, s, l.Q, d, l.dp, j, 0, l.y, l.w, l.part1,
+                       l.part2, m, l.norm_part, l.st);
     OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_coef, cg, dim3(kThreads), 0, s, l.part2, l.nblk2, j, 1, l.st);
-    OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_orth, dim3(unsigned(l.nblk2)), dim3(kThreads), 0, s, l.Q, d, l.dp, j,
-                       1, l.w, l.w, l.part2, l.nblk2, l.norm_part, l.st);
-    OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_finish, dim3(1), dim3(kLzFinThreads), 0, s, l.norm_part, l.nblk2, j,
-                       m, tol, l.st, lambda_max);
+    hipLaunchKernelGGL(k_lz_orth, rows, threads, 0, s, l.Q, d, l.dp, j, 1, l.w, l.w, l.part2,
+                       l.part1, m, l.norm_part, l.st);
     OPTIMA_LAUNCH_CHECK();
     if ((j + 1) % kPoll == 0 && j + 1 < m) {
       int conv = 0;
@@ -1102,6 +1282,9 @@ optima_status spectral_lanczos(const float* H, int64_t d, const float* v0, int m
       if (conv) break;
     }
   }
+  hipLaunchKernelGGL(k_lz_close, dim3(1), threads, 0, s, l.norm_part, l.nblk, std::min(j, m - 1), m,
+                     tol, l.st, lambda_max);
+  OPTIMA_LAUNCH_CHECK();
   if (steps) {
     hipLaunchKernelGGL(k_copy_lz_steps, dim3(1), dim3(1), 0, s, l.st, steps);
     OPTIMA_LAUNCH_CHECK();

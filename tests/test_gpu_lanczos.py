@@ -181,3 +181,24 @@ def test_lanczos_maximum_steps_and_more_steps_than_rows(L):
     log(f"  d=40: gpu {lam_g:.9e} ({st_g} steps)")
     assert st_g <= d
     assert lam_g == pytest.approx(np.linalg.eigvalsh(Hs)[-1], rel=2e-6)
+
+
+@pytest.mark.parametrize("d", [4096, 4100, 4353])
+def test_lanczos_one_triangle_of_h(L, d):
+    # From 4096 on the steps after the first read only the tiles on and below
+    # the diagonal: whole tiles, a ragged last tile with 16-byte loads and one
+    # without. The trajectory must be the oracle's, as on smaller sizes.
+    rng = np.random.default_rng(d)
+    B = rng.standard_normal((d, 24)).astype(np.float32)
+    Hin = f32_exact(B @ B.T / 24 + np.diag(np.linspace(0.5, 1.5, d)))
+    v0 = rng.standard_normal(d).astype(np.float32)
+    Hd = to_dev(Hin)
+    for m in (2, 3, 9):
+        lam_g, st_g = gpu_lanczos(L, Hd, v0, max_steps=m, tol=0.0)
+        lam_o, _ = oracle.lanczos(Hin, v0, m, 0.0)
+        log(f"  d={d} m={m}: gpu {lam_g:.9e} oracle {lam_o:.9e}")
+        assert st_g == m
+        assert lam_g == pytest.approx(lam_o, rel=2e-6)
+    # A NaN above the diagonal, which only the first step reads.
+    Hd[1, d - 1] = float("nan")
+    assert np.isnan(gpu_lanczos(L, Hd, v0)[0])
