@@ -428,8 +428,8 @@ __device__ inline void grouped_tri_tile(int idx, int nt, int* ti, int* tj) {
     }
 }
 
-// X: [n_rows][d] bf16 with n_rows >= stages * 64. The work units are the
-// (split, tile) pairs of the triangle of d / 256 blocks; split sp covers
+// X: [full * 64][d] bf16, followed, if stages = full + 1, by the 64 rows of
+// `tail`. The work units are the (split, tile) pairs of the triangle of d / 256 blocks; split sp covers
 // stages [stages sp / splits, stages (sp + 1) / splits). The dispatcher
 // sends workgroup b to XCD b % 8, so XCD x runs workgroups x, x + 8, ... in
 // that order. XCD x owns the x-th eighth of the tiles in grouped_tri_tile
@@ -438,12 +438,16 @@ __device__ inline void grouped_tri_tile(int idx, int nt, int* ti, int* tj) {
 // few blocks, which its L2 fetches once for all of them; and all eight XCDs
 // move through the tokens together, so the device-wide cache serves one
 // XCD's misses to the others. The grid is 8 times the largest XCD share;
-// workgroups beyond their XCD's share exit at once.
-// Writes (first) or adds the tile's partial sum into part[sp] ([d][d] fp32).
-template <int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X, int64_t d,
-                                                            int stages, int splits, float* part,
-                                                            int first) {
+// workgroups beyond their XCD's share exit at once. With `spread` (few tiles,
+// whose eighths would leave XCDs idle) workgroup b takes unit b instead.
+// FUSED (splits == 1): H (+)= the tile's sum, both triangles; else the tile's
+// partial sum goes to part[sp] ([d][d] fp32).
+template <int WAVES, bool FUSED>
+__global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
+                                                            const uint16_t* tail, int64_t d,
+                                                            int full, int stages, int splits,
+                                                            int spread, float* part, float* H,
+                                                            int accumulate) {
   using namespace dt;
   using C = Cfg<WAVES>;
   __shared__ __attribute__((aligned(1024))) char lds0[kBufBytes];
@@ -453,8 +457,13 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X, i
   static_assert(kRing == 4 && kRows == 2 * kBufRows, "the loop below is written for this ring");
   const int nt = int(d / kBlock);
   const int n_tiles = nt * (nt + 1) / 2;
-  const int x = blockIdx.x & 7, l = blockIdx.x >> 3;
-  const int t0 = int(int64_t(n_tiles) * x / 8), tx = int(int64_t(n_tiles) * (x + 1) / 8) - t0;
+  int t0 = 0, tx = n_tiles, l = blockIdx.x;
+  if (!spread) {
+    const int x = blockIdx.x & 7;
+    t0 = int(int64_t(n_tiles) * x / 8);
+    tx = int(int64_t(n_tiles) * (x + 1) / 8) - t0;
+    l = blockIdx.x >> 3;
+  }
   if (int64_t(l) >= int64_t(tx) * splits) return;
   const int sp = l / tx;
   int ti, tj;
@@ -466,11 +475,15 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X, i
   const int row = 2 * wave + (lane >> 5);
   const int seg[2] = {((lane & 31) ^ swz(row)) * 16, ((lane & 31) ^ swz(row + 2 * WAVES)) * 16};
   const int64_t row_bytes = d * 2;
-  const char* xb = reinterpret_cast<const char*>(X) + (int64_t(s0) * kRows + row) * row_bytes;
-  const char* a = xb + int64_t(ti) * kBlock * 2;
-  const char* b = xb + int64_t(tj) * kBlock * 2;
   const int64_t round_bytes = 2 * WAVES * row_bytes;
   const int64_t buf_bytes = kBufRows * row_bytes;
+  // This thread's first row of block 0 in buffer q (32 tokens) of the range:
+  // from X, or from the tail's two buffers. (Blocks ti and tj are 512 bytes an
+  // index further on.)
+  const char* xrow = reinterpret_cast<const char*>(X) + (int64_t(s0) * kRows + row) * row_bytes;
+  const char* trow = reinterpret_cast<const char*>(tail) + int64_t(row) * row_bytes;
+  const int q_tail = 2 * (full - s0);
+  const int64_t oa = int64_t(ti) * kBlock * 2, ob = int64_t(tj) * kBlock * 2;
 
   f4 acc[C::kMB][C::kNB];
 #pragma unroll
@@ -482,38 +495,68 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X, i
     // (into buffers nobody reads again) so that every step waits for the
     // same count; they are drained before the epilogue.
     const int nb = 2 * n;
-    auto at = [nb, buf_bytes](const char* p, int q) { return p + (q < nb ? q : nb - 1) * buf_bytes; };
-    issue<C>(a, b, round_bytes, seg, lds0);
-    issue<C>(at(a, 1), at(b, 1), round_bytes, seg, lds1);
-    issue<C>(at(a, 2), at(b, 2), round_bytes, seg, lds2);
+    auto at = [&](int q) {
+      q = q < nb ? q : nb - 1;
+      return q < q_tail ? xrow + q * buf_bytes : trow + (q - q_tail) * buf_bytes;
+    };
+    auto step = [&](int q, char* cur, char* nxt) {
+      const char* p = at(q);
+      ring_step<C>(acc, p + oa, p + ob, round_bytes, seg, cur, nxt);
+    };
+    issue<C>(at(0) + oa, at(0) + ob, round_bytes, seg, lds0);
+    issue<C>(at(1) + oa, at(1) + ob, round_bytes, seg, lds1);
+    issue<C>(at(2) + oa, at(2) + ob, round_bytes, seg, lds2);
     int q = 0;
     for (; q + 4 <= nb; q += 4) {
-      ring_step<C>(acc, at(a, q + 3), at(b, q + 3), round_bytes, seg, lds0, lds3);
-      ring_step<C>(acc, at(a, q + 4), at(b, q + 4), round_bytes, seg, lds1, lds0);
-      ring_step<C>(acc, at(a, q + 5), at(b, q + 5), round_bytes, seg, lds2, lds1);
-      ring_step<C>(acc, at(a, q + 6), at(b, q + 6), round_bytes, seg, lds3, lds2);
+      step(q + 3, lds0, lds3);
+      step(q + 4, lds1, lds0);
+      step(q + 5, lds2, lds1);
+      step(q + 6, lds3, lds2);
     }
     if (q < nb) {
-      ring_step<C>(acc, at(a, q + 3), at(b, q + 3), round_bytes, seg, lds0, lds3);
-      ring_step<C>(acc, at(a, q + 4), at(b, q + 4), round_bytes, seg, lds1, lds0);
+      step(q + 3, lds0, lds3);
+      step(q + 4, lds1, lds0);
     }
     wait_vmcnt<0>();
     __syncthreads();
   }
-  float* P = part + size_t(sp) * size_t(d) * size_t(d);
+  float* P = FUSED ? H : part + size_t(sp) * size_t(d) * size_t(d);
   const int wm = wave / C::WGN, wn = wave % C::WGN;
 #pragma unroll
-  for (int mi = 0; mi < C::kMB; ++mi)
+  for (int mi = 0; mi < C::kMB; ++mi) {
+    const int64_t i0 = int64_t(ti) * kBlock + (wm * C::kMB + mi) * 16 + 4 * (lane >> 4);
+    const int64_t j0 = int64_t(tj) * kBlock + wn * C::kNB * 16 + (lane & 15);
+    if (FUSED && accumulate) {  // 32 loads in flight before the first store
+      float h[C::kNB][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t i = int64_t(ti) * kBlock + (wm * C::kMB + mi) * 16 + 4 * (lane >> 4) + e;
+      for (int ni = 0; ni < C::kNB; ++ni)
 #pragma unroll
-      for (int ni = 0; ni < C::kNB; ++ni) {
-        const int64_t jj = int64_t(tj) * kBlock + (wn * C::kNB + ni) * 16 + (lane & 15);
-        float* q = P + i * d + jj;
-        *q = first ? acc[mi][ni][e] : *q + acc[mi][ni][e];
+        for (int e = 0; e < 4; ++e)
+          h[ni][e] = i0 + e >= j0 + 16 * ni ? P[(i0 + e) * d + j0 + 16 * ni] : 0.f;
+#pragma unroll
+      for (int ni = 0; ni < C::kNB; ++ni)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[mi][ni][e] = h[ni][e] + acc[mi][ni][e];
+    }
+#pragma unroll
+    for (int ni = 0; ni < C::kNB; ++ni) {
+      const int64_t jj = j0 + 16 * ni;
+      const f4 v = acc[mi][ni];
+      if (!FUSED || ti != tj) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) P[(i0 + e) * d + jj] = v[e];
+        // The mirror entries of a lane's four rows are consecutive.
+        if (FUSED) *reinterpret_cast<float4*>(P + jj * d + i0) = make_float4(v[0], v[1], v[2], v[3]);
+      } else {  // the diagonal tile's lower triangle and its mirror
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i0 + e >= jj) {
+            P[(i0 + e) * d + jj] = v[e];
+            P[jj * d + i0 + e] = v[e];
+          }
       }
     }
+  }
 }
 
 // Copies `rows` (< 64) token rows starting at t0 into a zero-padded 64-row
@@ -532,14 +575,17 @@ constexpr int kDirectWaves = 8;  // the layout of k_syrk_direct that the library
 
 struct DirectPlan {
   int64_t tiles;
-  int full_stages, tail_rows, splits;
+  int full_stages, tail_rows;
+  int stages;  // with the tail's
+  int splits;
+  bool spread, fused;
   size_t part_elems;
 };
 
-// Grid of k_syrk_direct over `tiles` tiles and `splits` splits: 8 times the
-// largest XCD share (ceil(tiles / 8) tiles, every split).
-unsigned direct_grid(int64_t tiles, int splits) {
-  return unsigned(8 * ceil_div(tiles, int64_t(8)) * splits);
+// Grid of k_syrk_direct over `tiles` tiles and `splits` splits: every unit, or
+// 8 times the largest XCD share (ceil(tiles / 8) tiles, every split).
+unsigned direct_grid(int64_t tiles, int splits, bool spread) {
+  return unsigned((spread ? tiles : 8 * ceil_div(tiles, int64_t(8))) * splits);
 }
 
 bool direct_ok(int64_t d, int dtype) {
@@ -552,24 +598,37 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   p.tiles = nt * (nt + 1) / 2;
   p.full_stages = int(n_tok / dt::kRows);
   p.tail_rows = int(n_tok % dt::kRows);
-  // Splits along the tokens: the fewest rounds of workgroups per CU relative
-  // to the work, with 1% per split for the partial sums; at most 4 GiB of
-  // partials. Each XCD (an eighth of the CUs) runs the largest eighth of the
-  // tiles for every split.
+  p.stages = p.full_stages + (p.tail_rows > 0);
+  // Eighths of the tiles per XCD, unless they would leave more than a seventh
+  // of the chip idle (1, 3, 6 or 10 tiles: d up to 1024).
+  p.spread = 7 * 8 * ceil_div(p.tiles, int64_t(8)) > 8 * p.tiles;
+  // Splits along the tokens: the rounds of workgroups per CU relative to the
+  // work (1.6 us a 64-token stage), 1% per split for starts and ends, and, from
+  // two splits on, the partial sums' bytes, written and read at 5.2 TB/s, and
+  // the kernel that adds them; at most 4 GiB of partials. A 2048-token sequence
+  // at d = 4096 takes one split (68 us a call, fused); 11 splits, which
+  // 262144 tokens take there, made it 215 us, half of it in the sums.
   int best = 1;
   double best_cost = 1e30;
-  const int max_s = std::max(1, std::min(dt::kMaxSplits, p.full_stages));
+  const int max_s = std::max(1, std::min(dt::kMaxSplits, p.stages));
+  const double tri_bytes = double(p.tiles) * dt::kBlock * dt::kBlock * 4.0;
   for (int S = 1; S <= max_s; ++S) {
     if (S > 1 && double(S) * double(d) * double(d) * 4.0 > double(int64_t(1) << 32)) break;
-    const double rounds = double(ceil_div(ceil_div(p.tiles, int64_t(8)) * S, dt::kCus / 8));
-    const double c = rounds / S * (1.0 + 0.01 * S);
+    const int64_t units = p.spread ? p.tiles * S : 8 * ceil_div(p.tiles, int64_t(8)) * S;
+    const double rounds = double(ceil_div(units, int64_t(dt::kCus)));
+    double c = rounds / S * (1.0 + 0.01 * S) * double(p.stages) * 1.6;
+    if (S > 1) c += S * tri_bytes * 2.0 / 5.2e6 + 5.0;
     if (c < best_cost - 1e-12) {
       best = S;
       best_cost = c;
     }
   }
   p.splits = best;
-  p.part_elems = size_t(p.splits) * size_t(d) * size_t(d);  // one [d][d] partial per split
+  // One [d][d] partial per split. A single split adds to H itself where enough
+  // CUs share the stores of both triangles: d = 512 (3 tiles) with 100 tokens
+  // takes longer that way.
+  p.fused = best == 1 && p.tiles >= 32;
+  p.part_elems = p.fused ? 0 : size_t(best) * size_t(d) * size_t(d);
   return p;
 }
 
@@ -616,24 +675,20 @@ optima_status hessian_accumulate(const void* X, int dtype, int64_t n_tok, int64_
     float* part = c.take<float>(p.part_elems);
     uint16_t* tail = c.take<uint16_t>(size_t(dt::kRows) * size_t(d));
     const uint16_t* Xb = static_cast<const uint16_t*>(X);
-    int splits = p.splits;
-    if (p.full_stages > 0) {
-      hipLaunchKernelGGL(k_syrk_direct<kDirectWaves>, dim3(direct_grid(p.tiles, splits)),
-                         dim3(64 * kDirectWaves), 0, s, Xb, d, p.full_stages, splits, part, 1);
-      OPTIMA_LAUNCH_CHECK();
-    } else {
-      splits = 1;
-    }
     if (p.tail_rows > 0) {
       hipLaunchKernelGGL(k_tail_rows, dim3(256), dim3(kThreads), 0, s, Xb, d,
                          int64_t(p.full_stages) * dt::kRows, p.tail_rows, tail);
       OPTIMA_LAUNCH_CHECK();
-      hipLaunchKernelGGL(k_syrk_direct<kDirectWaves>, dim3(direct_grid(p.tiles, 1)),
-                         dim3(64 * kDirectWaves), 0, s, tail, d, 1, 1, part,
-                         p.full_stages > 0 ? 0 : 1);
-      OPTIMA_LAUNCH_CHECK();
     }
-    return reduce_partials(part, splits, d, d, H, accumulate, s);
+    const dim3 grid(direct_grid(p.tiles, p.splits, p.spread)), threads(64 * kDirectWaves);
+    if (p.fused)
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, true>), grid, threads, 0, s, Xb, tail, d,
+                         p.full_stages, p.stages, 1, int(p.spread), part, H, accumulate);
+    else
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false>), grid, threads, 0, s, Xb, tail, d,
+                         p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
+    OPTIMA_LAUNCH_CHECK();
+    return p.fused ? OPTIMA_OK : reduce_partials(part, p.splits, d, d, H, accumulate, s);
   }
   const HessPlan p = plan(n_tok, d, dtype);
   Carver c(ws);
