@@ -1613,17 +1613,21 @@ __global__ void __launch_bounds__(kThreads) k_prep_sparse(const float* W0, const
   if (bad) atomicOr(flags, 1);
 }
 
-// Split planes of H (row pitch 4 dp bytes), built once per solve.
-// With `flags`, it also sets flags[0] = 1 if H holds a NaN or Inf (the scan
-// of k_scan_pad_h, for an H that needs no padding).
+// Split planes of H (row pitch 4 dp bytes), built once per solve, 4 columns a
+// thread (dp % 128 == 0). With `flags`, it also sets flags[0] = 1 if H holds a
+// NaN or Inf (the scan of k_scan_pad_h, for an H that needs no padding). Bound
+// by HBM: 8 bytes an entry; d = 4096 31 us, d = 14336 324 us (one column a
+// thread, in 2-byte stores: 41 and 408 us).
 __global__ void __launch_bounds__(kThreads) k_split_h(const float* Hm, int dp, uint16_t* HP,
                                                       int* flags) {
   const int i = blockIdx.x;
   bool bad = false;
-  for (int n = blockIdx.y * kThreads + threadIdx.x; n < dp; n += gridDim.y * kThreads) {
-    const float v = Hm[size_t(i) * dp + n];
-    bad |= !isfinite(v);
-    store_split(HP + size_t(i) * dp * 2, n, v);
+  for (int n = 4 * (blockIdx.y * kThreads + threadIdx.x); n < dp; n += 4 * gridDim.y * kThreads) {
+    const float4 h = ld4(Hm + size_t(i) * dp + n);
+    const float v[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bad |= !isfinite(v[e]);
+    store_split4(HP + size_t(i) * dp * 2, n, v);
   }
   if (flags && bad) atomicOr(flags, 1);
 }
@@ -1973,8 +1977,95 @@ __global__ void __launch_bounds__(kThreads) k_cg_init(CgArgs a) {
   if (threadIdx.x == 0) a.rr[j] = s;
 }
 
-// One CG iteration of one active column (one workgroup per column).
-__global__ void __launch_bounds__(kThreads) k_cg_step(CgArgs a) {
+// One CG iteration of one active column (one workgroup of T threads per
+// column), the column's p, q, r and x in registers: thread t holds groups of 4
+// entries t, t + T, ... (dp <= 4 T NV). Bound by HBM: 33 bytes an entry, each
+// vector read and written once. 4096 columns of 4096: 98 us (5.6
+// TB/s), against 171 us of three passes that each read their vectors again.
+template <int T, int NV>
+__global__ void __launch_bounds__(T) k_cg_step(CgArgs a) {
+  constexpr int kWaves = T / 64;
+  __shared__ double red[2][kWaves];
+  const int r = blockIdx.x;
+  if (r >= a.n_rows) return;
+  const int j = a.rows ? a.rows[r] : r;
+  const size_t base = size_t(j) * a.dp;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto sum = [&](double v, double* slots) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) slots[wave] = v;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) t += slots[w];
+    return t;
+  };
+  float4 p[NV], q[NV], rv[NV], x[NV];
+  unsigned keep = 0;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int n = 4 * (threadIdx.x + v * T);
+    bool k4[4] = {false, false, false, false};
+    p[v] = q[v] = rv[v] = x[v] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (n < a.dp) {
+      p[v] = ld4(a.P + base + n);
+      q[v] = ld4(a.Q + base + n);
+      rv[v] = ld4(a.R + base + n);
+      x[v] = ld4(a.X + base + n);
+      mask4(a.mask, a.d, j, n, k4);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) keep |= unsigned(k4[e]) << (4 * v + e);
+  }
+  auto kept = [&](int v, int e) { return (keep >> (4 * v + e)) & 1u; };
+  double pq = 0.0;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const float pe[4] = {p[v].x, p[v].y, p[v].z, p[v].w}, qe[4] = {q[v].x, q[v].y, q[v].z, q[v].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (kept(v, e)) pq += double(pe[e]) * double(qe[e]);
+  }
+  pq = sum(pq, red[0]);
+  const double rr = a.rr[j];
+  const float alpha = float(rr > 0.0 && pq > 0.0 ? rr / pq : 0.0);
+  double rr2 = 0.0;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    float* const pe = &p[v].x;
+    float* const qe = &q[v].x;
+    float* const re = &rv[v].x;
+    float* const xe = &x[v].x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (kept(v, e)) {
+        xe[e] = xe[e] + alpha * pe[e];
+        re[e] = re[e] - alpha * qe[e];
+        rr2 += double(re[e]) * double(re[e]);
+      }
+  }
+  rr2 = sum(rr2, red[1]);
+  const float beta = float(rr > 0.0 ? rr2 / rr : 0.0);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int n = 4 * (threadIdx.x + v * T);
+    if (n >= a.dp) continue;
+    const float re[4] = {rv[v].x, rv[v].y, rv[v].z, rv[v].w};
+    const float po[4] = {p[v].x, p[v].y, p[v].z, p[v].w};
+    float pn[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pn[e] = kept(v, e) ? re[e] + beta * po[e] : 0.f;
+    st4(a.X + base + n, x[v]);
+    st4(a.R + base + n, rv[v]);
+    st4(a.P + base + n, make_float4(pn[0], pn[1], pn[2], pn[3]));
+    if (a.PP) store_split4(a.PP + base * 2, n, pn);
+  }
+  if (threadIdx.x == 0) a.rr[j] = rr2;
+}
+
+// The same in three passes over memory, for columns longer than the registers
+// of 1024 threads hold.
+__global__ void __launch_bounds__(kThreads) k_cg_step_long(CgArgs a) {
   __shared__ double red[kThreads / 64];
   const int r = blockIdx.x;
   if (r >= a.n_rows) return;
@@ -2008,6 +2099,24 @@ __global__ void __launch_bounds__(kThreads) k_cg_step(CgArgs a) {
   if (threadIdx.x == 0) a.rr[j] = rr2;
 }
 
+// One k_cg_step for the active columns: the smallest workgroup whose registers
+// hold a column at 16 entries a thread.
+optima_status launch_cg_step(const CgArgs& a, hipStream_t s) {
+  const dim3 grid(unsigned(a.n_rows));
+  if (a.dp <= 1024)
+    hipLaunchKernelGGL((k_cg_step<256, 1>), grid, dim3(256), 0, s, a);
+  else if (a.dp <= 4096)
+    hipLaunchKernelGGL((k_cg_step<256, 4>), grid, dim3(256), 0, s, a);
+  else if (a.dp <= 8192)
+    hipLaunchKernelGGL((k_cg_step<512, 4>), grid, dim3(512), 0, s, a);
+  else if (a.dp <= 16384)
+    hipLaunchKernelGGL((k_cg_step<1024, 4>), grid, dim3(1024), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_cg_step_long, grid, dim3(kThreads), 0, s, a);
+  OPTIMA_LAUNCH_CHECK();
+  return OPTIMA_OK;
+}
+
 // Termination test of the CG iterate with the rAPDHG rule. With x = 0 off K:
 // g_K = -2 r_K, so r_d = 2 ||r_K||, gap = 2 |x.r|, x^T H x = x.Hw0 - x.r and
 // f(x) = w0^T H w0 - x.Hw0 - x.r (sums over K).
@@ -2035,15 +2144,22 @@ __global__ void __launch_bounds__(kThreads) k_cg_check(CgCheckArgs a) {
   if (r >= a.n_rows) return;
   const int j = a.rows ? a.rows[r] : r;
   const size_t base = size_t(j) * a.dp;
-  const uint8_t* m = a.mask + size_t(j) * a.d;
   double rr = 0.0, xr = 0.0, xh = 0.0;
-  for (int n = threadIdx.x; n < a.d; n += kThreads) {
-    if (!m[n]) continue;
-    const double x = a.X[base + n], rv = a.R[base + n];
-    const double ro = a.scale ? rv / double(a.scale[n]) : rv;  // original coordinates
-    rr += ro * ro;
-    xr += x * rv;
-    xh += x * double(a.HW0[base + n]);
+  for (int n = 4 * threadIdx.x; n < a.dp; n += 4 * kThreads) {
+    const float4 x4 = ld4(a.X + base + n), r4 = ld4(a.R + base + n), h4 = ld4(a.HW0 + base + n);
+    const float xe[4] = {x4.x, x4.y, x4.z, x4.w}, re[4] = {r4.x, r4.y, r4.z, r4.w};
+    const float he[4] = {h4.x, h4.y, h4.z, h4.w};
+    bool keep[4];
+    mask4(a.mask, a.d, j, n, keep);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (!keep[e]) continue;
+      const double x = xe[e], rv = re[e];
+      const double ro = a.scale ? rv / double(a.scale[n + e]) : rv;  // original coordinates
+      rr += ro * ro;
+      xr += x * rv;
+      xh += x * double(he[e]);
+    }
   }
   rr = block_sum(rr, red);
   xr = block_sum(xr, red);
@@ -2534,8 +2650,7 @@ optima_status cg_loop(const Layout& l, ProductArgs p, int dp, int di, const uint
     if (timed) OPTIMA_HIP_TRY(hipEventRecord(ev[0], s));
     for (int i = 0; i < n; ++i) {
       if (auto e = launch_product<kPlain>(p, l, o.precision, s)) return e;
-      hipLaunchKernelGGL(k_cg_step, dim3(unsigned(n_act)), dim3(kThreads), 0, s, cg);
-      OPTIMA_LAUNCH_CHECK();
+      if (auto e = launch_cg_step(cg, s)) return e;
     }
     if (timed) OPTIMA_HIP_TRY(hipEventRecord(ev[1], s));
     inf.gemm_calls += n;
