@@ -71,4 +71,27 @@ __device__ inline double block_sum(double v, double* smem) {
   return t;
 }
 
+// block_sum of N values at once: the shuffles of one hide behind the others',
+// and two barriers serve them all. `smem` needs N * kThreads / 64 doubles. The
+// sums are block_sum's, bit for bit.
+template <int N>
+__device__ inline void block_sums(double (&v)[N], double* smem) {
+  constexpr int kW = kThreads / 64;
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], o, 64);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 0)
+#pragma unroll
+    for (int i = 0; i < N; ++i) smem[i * kW + wave] = v[i];
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    double t = 0.0;
+    for (int w = 0; w < kW; ++w) t += smem[i * kW + w];
+    v[i] = t;
+  }
+}
+
 }  // namespace optima

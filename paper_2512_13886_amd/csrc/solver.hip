@@ -27,6 +27,7 @@
 // (x - x0 vanishes off the kept set), with g0 = H x0 - H w0 packed into the
 // second half of Hx_ag's row.
 #include <atomic>
+#include <vector>
 
 #include "common.h"
 #include "readback.h"
@@ -1739,7 +1740,7 @@ struct CheckArgs {
 // One workgroup per active column: scores x and x_ag, picks the candidate,
 // then terminates the column or applies an accepted restart.
 __global__ void __launch_bounds__(kThreads) k_check(CheckArgs a) {
-  __shared__ double red[kThreads / 64];
+  __shared__ double red[8 * kThreads / 64];
   __shared__ int decision;  // bit 0: terminate, bit 1: restart, bit 2: candidate is x
   const int r = blockIdx.x;
   if (r >= a.n_rows) return;
@@ -1809,18 +1810,14 @@ __global__ void __launch_bounds__(kThreads) k_check(CheckArgs a) {
       qa += xa * ha;
     }
   }
-  rdx = block_sum(rdx, red);
-  gpx = block_sum(gpx, red);
-  fx = block_sum(fx, red);
-  qx = block_sum(qx, red);
   if (a.initial) {
-    cn = block_sum(cn, red);
-    wq = block_sum(wq, red);
+    double v[6] = {rdx, gpx, fx, qx, cn, wq};
+    block_sums<6>(v, red);
+    rdx = v[0], gpx = v[1], fx = v[2], qx = v[3], cn = v[4], wq = v[5];
   } else {
-    rda = block_sum(rda, red);
-    gpa = block_sum(gpa, red);
-    fa = block_sum(fa, red);
-    qa = block_sum(qa, red);
+    double v[8] = {rdx, gpx, fx, qx, rda, gpa, fa, qa};
+    block_sums<8>(v, red);
+    rdx = v[0], gpx = v[1], fx = v[2], qx = v[3], rda = v[4], gpa = v[5], fa = v[6], qa = v[7];
   }
 
   if (threadIdx.x == 0) {
@@ -2138,7 +2135,7 @@ struct CgCheckArgs {
 };
 
 __global__ void __launch_bounds__(kThreads) k_cg_check(CgCheckArgs a) {
-  __shared__ double red[kThreads / 64];
+  __shared__ double red[3 * kThreads / 64];
   __shared__ int stop;
   const int r = blockIdx.x;
   if (r >= a.n_rows) return;
@@ -2161,9 +2158,9 @@ __global__ void __launch_bounds__(kThreads) k_cg_check(CgCheckArgs a) {
       xh += x * double(he[e]);
     }
   }
-  rr = block_sum(rr, red);
-  xr = block_sum(xr, red);
-  xh = block_sum(xh, red);
+  double v[3] = {rr, xr, xh};
+  block_sums<3>(v, red);
+  rr = v[0], xr = v[1], xh = v[2];
   if (threadIdx.x == 0) {
     const optima_solver_opts& o = a.o;
     const double rd = 2.0 * sqrt(rr), gap = 2.0 * fabs(xr);
@@ -2233,6 +2230,10 @@ __global__ void __launch_bounds__(kThreads) k_idx_stage_major(const uint16_t* id
   *reinterpret_cast<uint2*>(out + (size_t(st) * pitch + r) * 4) =
       *reinterpret_cast<const uint2*>(idx + (size_t(j) * stages + st) * 4);
 }
+
+// Checks of a solve of a fixed number of iterations between two host waits: what
+// bounds the launches in the queue and the events in use.
+constexpr int kUnwaitedChecks = 32;
 
 // Split-K limits: at most kMaxSplits ranges, and at most kMaxSplitTiles
 // (tile, range) pairs, which bounds the partial-sum buffer to 128 MiB.
@@ -2858,25 +2859,32 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
     ca.packed = 1;
   }
 
-  // Optional timing of the iteration loop's product launches.
-  hipEvent_t ev[2] = {nullptr, nullptr};
-  if (info) {
-    OPTIMA_HIP_TRY(hipEventCreate(&ev[0]));
-    if (hipEventCreate(&ev[1]) != hipSuccess) {
-      (void)hipEventDestroy(ev[0]);
-      return OPTIMA_E_HIP;
+  // Optional timing of the iteration loop's product launches: a pair of events
+  // around each block of iterations whose time has not been read yet.
+  struct BlockTimes {
+    std::vector<hipEvent_t> ev;  // pairs, kept from one wait to the next
+    struct Block {
+      int n, n_act;
+      bool few;
+    };
+    std::vector<Block> blocks;
+    ~BlockTimes() {
+      for (hipEvent_t e : ev) (void)hipEventDestroy(e);
     }
-  }
-  struct EventGuard {
-    hipEvent_t* e;
-    ~EventGuard() {
-      if (e[0]) (void)hipEventDestroy(e[0]);
-      if (e[1]) (void)hipEventDestroy(e[1]);
+    hipError_t pair(size_t i) {  // the i-th pair exists
+      while (ev.size() < 2 * (i + 1)) {
+        hipEvent_t e = nullptr;
+        const hipError_t r = hipEventCreate(&e);
+        if (r != hipSuccess) return r;
+        ev.push_back(e);
+      }
+      return hipSuccess;
     }
-  } guard{ev};
+  } times;
+  if (info) OPTIMA_HIP_TRY(times.pair(0));
 
   if (use_cg) {
-    const optima_status e = cg_loop(l, p, dp, di, mask, o, W_out, stats, inf, ev, info != nullptr,
+    const optima_status e = cg_loop(l, p, dp, di, mask, o, W_out, stats, inf, times.ev.data(), info != nullptr,
                                     n_act, s);
     if (e) return e;
     if (info) *info = inf;
@@ -2892,6 +2900,7 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
   const int64_t ce = o.check_every;
   // k_block_small keeps x in one buffer and needs no planes of it.
   const bool small = small_path(iprec, dp);
+  int unwaited = 0;  // checks since the last wait
   while (t < o.max_iters && n_act > 0) {
     const int64_t t_next = std::min<int64_t>((t / ce + 1) * ce, o.max_iters);
     const int n = int(t_next - t);
@@ -2910,7 +2919,11 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
     p.XA = l.XA;
     if (iprec == kPrecSparse && !few_column_path(iprec, n_act, dp))
       if (auto e = stage_major_idx(l.XIDX, rows, n_act, l, p, s)) return e;
-    if (info) OPTIMA_HIP_TRY(hipEventRecord(ev[0], s));
+    const size_t tb = times.blocks.size();
+    if (info) {
+      OPTIMA_HIP_TRY(times.pair(tb));
+      OPTIMA_HIP_TRY(hipEventRecord(times.ev[2 * tb], s));
+    }
     bool persisted = false;
     if (small) {
       SmallArgs sa{rows, n_act, di, Hm, l.HP, xbuf[cur], l.XA, l.HX, l.HA, l.HW0, mask,
@@ -2956,13 +2969,14 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
       p.s = n - 1;
       if (auto e = launch_product<kStore>(p, l, iprec, s)) return e;
     }
-    if (info) OPTIMA_HIP_TRY(hipEventRecord(ev[1], s));
+    if (info) {
+      OPTIMA_HIP_TRY(hipEventRecord(times.ev[2 * tb + 1], s));
+      times.blocks.push_back({n, n_act, few_column_path(iprec, n_act, dp)});
+    }
     inf.gemm_calls += n;
     inf.row_products += int64_t(n) * n_act;
     inf.timed_launches += n;
     inf.timed_row_products += int64_t(n) * n_act;
-    const bool few = few_column_path(iprec, n_act, dp);  // this block's launches
-    const int act_block = n_act;
     t = t_next;
 
     ca.rows = rows;
@@ -2976,24 +2990,33 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
     hipLaunchKernelGGL(k_check, dim3(n_act), dim3(kThreads), 0, s, ca);
     OPTIMA_LAUNCH_CHECK();
     inf.checks += 1;
-    hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, rows, n_act, l.st.done, rows_next,
-                       l.n_active);
-    OPTIMA_LAUNCH_CHECK();
-    std::swap(rows, rows_next);
+    // A solve of a fixed number of iterations keeps every column to the end:
+    // nothing to compact, and no reason to wait for each check (20 us of an
+    // idle GPU, a fifth of the 128-wide layer's block of 64 iterations).
+    if (o.fixed_iters && t < o.max_iters && ++unwaited < kUnwaitedChecks) continue;
+    unwaited = 0;
+    if (!o.fixed_iters) {
+      hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, rows, n_act, l.st.done, rows_next,
+                         l.n_active);
+      OPTIMA_LAUNCH_CHECK();
+      std::swap(rows, rows_next);
+    }
     int act_timeout[2] = {0, 0};
     OPTIMA_HIP_TRY(read_back(act_timeout, l.n_active, 2 * sizeof(int), s));
-    n_act = act_timeout[0];
+    if (!o.fixed_iters) n_act = act_timeout[0];
     if (act_timeout[1]) return OPTIMA_E_HIP;  // a grid barrier wait gave up
-    if (info) {
+    for (size_t i = 0; i < times.blocks.size(); ++i) {
+      const BlockTimes::Block& bl = times.blocks[i];
       float ms = 0.f;
-      OPTIMA_HIP_TRY(hipEventElapsedTime(&ms, ev[0], ev[1]));
+      OPTIMA_HIP_TRY(hipEventElapsedTime(&ms, times.ev[2 * i], times.ev[2 * i + 1]));
       inf.timed_product_ms += ms;
-      if (few) {
-        inf.few_launches += n;
-        inf.few_row_products += int64_t(n) * act_block;
+      if (bl.few) {
+        inf.few_launches += bl.n;
+        inf.few_row_products += int64_t(bl.n) * bl.n_act;
         inf.few_product_ms += ms;
       }
     }
+    times.blocks.clear();
   }
   inf.iterations = t;
   if (info) *info = inf;
