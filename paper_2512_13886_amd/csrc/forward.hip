@@ -196,7 +196,8 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_forward256(const char* X,
                     t256_seg_bytes(i);
     }
   Acc256 acc;
-  gemm256_mainloop<Bf16Tag>(acc, src, int(pitch / Tile256::kSRB), l0, l1, l2, l3, l4, l5, l6, l7);
+  gemm256_mainloop<Bf16Tag>(acc, src, int(pitch / Tile256::kSRB), l0, l1, l2, l3, l4, l5, l6, l7,
+                            [] {});
 
   double e = 0.0;
 #pragma unroll

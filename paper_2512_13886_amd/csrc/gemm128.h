@@ -43,50 +43,95 @@ struct AccR128 {
 __device__ inline int r128_row(int mi, int e) { return t256_row(0, mi, e); }
 __device__ inline int r128_col(int ni) { return t256_col(0, ni); }
 
-template <typename T>
-__device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, int64_t off, char* cur,
+// LEFT: stages left, this one included (4: or more); the last three fetch
+// nothing, and wait for what is in flight.
+template <typename T, int LEFT>
+__device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, int s, char* cur,
                                   char* nxt) {
+  constexpr int kStage = 2 * Ring128::kLoads;
   const int wm = threadIdx.x >> 8, wn = (threadIdx.x >> 6) & 3;
   bf16x8 fa[4][2], fb[2][2];
   t256::read<4>(fa, cur, wm * 64);
   t256::read<2>(fb, cur + 128 * Ring128::kSRB, wn * 32);
-  t256::fetch(src.a, off, nxt);
-  t256::fetch(src.b, off, nxt + 128 * Ring128::kSRB);
-  t256::end_memory<4 * Ring128::kLoads>();
+  if constexpr (LEFT >= 4) {
+    const int64_t off = int64_t(s + 3) * Ring128::kSRB;
+    t256::fetch(src.a, off, nxt);
+    t256::fetch(src.b, off, nxt + 128 * Ring128::kSRB);
+  }
+  t256::end_memory<LEFT >= 4 ? 2 * kStage : LEFT == 3 ? kStage : LEFT == 2 ? 0 : -1>();
   t256::quadrant<T>(acc.q, fa, fb);
   t256::barrier();
 }
 
-// n stages (n >= 0). b0..b3 are distinct __shared__ arrays of
-// Ring128::kBufBytes; fetches past the last stage repeat it, into buffers that
-// nobody reads again.
+// The last three stages, from buffers c0, c1, c2.
 template <typename T>
+__device__ inline void r128_last3(AccR128& acc, const OperandsR128& src, char* c0, char* c1,
+                                  char* c2) {
+  r128_stage<T, 3>(acc, src, 0, c0, nullptr);
+  r128_stage<T, 2>(acc, src, 0, c1, nullptr);
+  r128_stage<T, 1>(acc, src, 0, c2, nullptr);
+}
+
+// n stages (n >= 0). b0..b3 are distinct __shared__ arrays of
+// Ring128::kBufBytes. `aside` runs once the first fetches are out.
+template <typename T, typename Aside>
 __device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, int n, char* b0,
-                                     char* b1, char* b2, char* b3) {
+                                     char* b1, char* b2, char* b3, Aside aside) {
+  constexpr int kStage = 2 * Ring128::kLoads;
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc.q[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
   if (n <= 0) return;
-  auto at = [n](int s) { return int64_t(s < n ? s : n - 1) * Ring128::kSRB; };
   auto fetch = [&](int s, char* buf) {
-    t256::fetch(src.a, at(s), buf);
-    t256::fetch(src.b, at(s), buf + 128 * Ring128::kSRB);
+    t256::fetch(src.a, int64_t(s) * Ring128::kSRB, buf);
+    t256::fetch(src.b, int64_t(s) * Ring128::kSRB, buf + 128 * Ring128::kSRB);
   };
-  fetch(0, b0);
-  fetch(1, b1);
-  fetch(2, b2);
-  t256::end_memory<4 * Ring128::kLoads>();
   const bool behind = threadIdx.x >= 256;  // waves 4-7
-  if (behind) t256::barrier();
-  int s = 0;
-  for (; s + 3 < n; s += 4) {
-    r128_stage<T>(acc, src, at(s + 3), b0, b3);
-    r128_stage<T>(acc, src, at(s + 4), b1, b0);
-    r128_stage<T>(acc, src, at(s + 5), b2, b1);
-    r128_stage<T>(acc, src, at(s + 6), b3, b2);
+  fetch(0, b0);
+  if (n < 3) {
+    aside();
+    if (n == 2) {
+      fetch(1, b1);
+      t256::end_memory<kStage>();
+    } else {
+      t256::end_memory<0>();
+    }
+    if (behind) t256::barrier();
+    if (n == 2) {
+      r128_stage<T, 2>(acc, src, 0, b0, nullptr);
+      r128_stage<T, 1>(acc, src, 0, b1, nullptr);
+    } else {
+      r128_stage<T, 1>(acc, src, 0, b0, nullptr);
+    }
+  } else {
+    fetch(1, b1);
+    fetch(2, b2);
+    aside();
+    t256::end_memory<2 * kStage>();
+    if (behind) t256::barrier();
+    int s = 0;
+    for (; s + 7 <= n; s += 4) {
+      r128_stage<T, 4>(acc, src, s, b0, b3);
+      r128_stage<T, 4>(acc, src, s + 1, b1, b0);
+      r128_stage<T, 4>(acc, src, s + 2, b2, b1);
+      r128_stage<T, 4>(acc, src, s + 3, b3, b2);
+    }
+    // 3 to 6 stages are left.
+    if (n - s == 3) {
+      r128_last3<T>(acc, src, b0, b1, b2);
+    } else if (n - s == 4) {
+      r128_stage<T, 4>(acc, src, s, b0, b3);
+      r128_last3<T>(acc, src, b1, b2, b3);
+    } else if (n - s == 5) {
+      r128_stage<T, 4>(acc, src, s, b0, b3);
+      r128_stage<T, 4>(acc, src, s + 1, b1, b0);
+      r128_last3<T>(acc, src, b2, b3, b0);
+    } else {
+      r128_stage<T, 4>(acc, src, s, b0, b3);
+      r128_stage<T, 4>(acc, src, s + 1, b1, b0);
+      r128_stage<T, 4>(acc, src, s + 2, b2, b1);
+      r128_last3<T>(acc, src, b3, b0, b1);
+    }
   }
-  if (s < n) r128_stage<T>(acc, src, at(s + 3), b0, b3);
-  if (s + 1 < n) r128_stage<T>(acc, src, at(s + 4), b1, b0);
-  if (s + 2 < n) r128_stage<T>(acc, src, at(s + 5), b2, b1);
   if (!behind) t256::barrier();
   // No load may still be writing LDS when the workgroup moves on.
   wait_vmcnt<0>();

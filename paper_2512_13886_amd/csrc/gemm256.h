@@ -168,11 +168,12 @@ __device__ inline void stage(Acc256& acc, const Operands256& src, int64_t off1, 
 
 // n stages (n >= 0) of tile products. The LDS arguments are distinct
 // __shared__ arrays of Tile256::kHalfBytes; fetches past the last stage repeat
-// it, into buffers that nobody reads again.
-template <typename T>
+// it, into buffers that nobody reads again. `aside` runs once the first fetches
+// are out.
+template <typename T, typename Aside>
 __device__ inline void gemm256_mainloop(Acc256& acc, const Operands256& src, int n, char* a00,
                                         char* a01, char* b00, char* b01, char* a10, char* a11,
-                                        char* b10, char* b11) {
+                                        char* b10, char* b11, Aside aside) {
 #pragma unroll
   for (int i = 0; i < 32; ++i) acc.q[i >> 4][(i >> 3) & 1][(i >> 1) & 3][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
   if (n <= 0) return;
@@ -184,6 +185,7 @@ __device__ inline void gemm256_mainloop(Acc256& acc, const Operands256& src, int
   t256::fetch(src.a[0], at(1), a10);
   t256::fetch(src.b[0], at(1), b10);
   t256::fetch(src.b[1], at(1), b11);
+  aside();
   t256::end_memory<3 * Tile256::kHalfLoads>();
   const bool behind = threadIdx.x >= 256;  // waves 4-7
   if (behind) t256::barrier();

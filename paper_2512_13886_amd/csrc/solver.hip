@@ -34,6 +34,7 @@
 #include "gemm128.h"
 #include "gemm256.h"
 #include "gemm_core.h"
+#include "gemm_sparse.h"
 
 namespace optima {
 namespace {
@@ -90,21 +91,22 @@ __device__ inline RowCoef row_coef(const ProductArgs& p, int j, float L) {
   return c;
 }
 
-// Column and step coefficients of a tile's rows, put into LDS before the main
-// loop: read in the epilogue, the active list and then the column's iteration
-// count would be two dependent loads and three divisions ahead of every update.
+// Column and step coefficients of a tile's rows, put into LDS while the main
+// loop's first loads are in flight: read in the epilogue, the active list and
+// then the column's iteration count would be two dependent loads and three
+// divisions ahead of every update.
 struct TileRow {
   int j;
   RowCoef c;
 };
 template <int MODE, int BM>
 __device__ inline void load_tile_rows(const ProductArgs& p, int m0, TileRow (&info)[BM]) {
+  static_assert((BM & (BM - 1)) == 0, "a power of two");
   const float L = (MODE == kFused || MODE == kStore) ? *p.Lp : 0.f;
-  for (int t = threadIdx.x; t < BM; t += blockDim.x) {
-    const int r = min(m0 + t, p.n_rows - 1);
-    const int j = p.rows ? p.rows[r] : r;
-    info[t] = TileRow{j, row_coef<MODE>(p, j, L)};
-  }
+  const int t = threadIdx.x & (BM - 1);  // some rows by several threads: no branch
+  const int r = min(m0 + t, p.n_rows - 1);
+  const int j = p.rows ? p.rows[r] : r;
+  info[t] = TileRow{j, row_coef<MODE>(p, j, L)};
 }
 
 __device__ inline float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -124,6 +126,20 @@ __device__ inline void mask4(const uint8_t* mask, int d, int j, int n, bool (&ke
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e) keep[e] = n + e < d && m[e] != 0;
+  }
+}
+
+// The same without a branch, for batches of loads (VEC: d % 4 == 0).
+template <bool VEC>
+__device__ inline void mask4_flat(const uint8_t* mask, int d, int j, int n, bool (&keep)[4]) {
+  const uint8_t* m = mask + size_t(j) * d;
+  if (VEC) {
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(m + (n < d ? n : 0));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) keep[e] = n < d && ((v >> (8 * e)) & 255u) != 0;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) keep[e] = m[n + e < d ? n + e : 0] != 0 && n + e < d;
   }
 }
 
@@ -310,6 +326,19 @@ struct Dense4In {
   float4 ha, hw, xi, xa;
   bool keep[4];
 };
+template <int MODE, bool VEC>
+__device__ inline Dense4In load_dense4_flat(const ProductArgs& p, int j, int n) {
+  Dense4In in{};
+  const size_t o = size_t(j) * p.dp + n;
+  in.ha = ld4(p.HA + o);
+  if (MODE == kFused) {
+    in.hw = ld4(p.HW0 + o);
+    in.xi = ld4(p.Xin + o);
+    in.xa = ld4(p.XA + o);
+    mask4_flat<VEC>(p.mask, p.d, j, n, in.keep);
+  }
+  return in;
+}
 template <int MODE>
 __device__ inline Dense4In load_dense4(const ProductArgs& p, int j, int n) {
   Dense4In in{};
@@ -380,6 +409,74 @@ __device__ inline void epilogue4(const ProductArgs& p, int j, int n, float4 y4, 
     st4(p.out1 + o, make_float4(a.x + y4.x, a.y + y4.y, a.z + y4.z, a.w + y4.w));
   } else {
     finish_dense4<MODE, PREC>(p, j, n, y4, c, load_dense4<MODE>(p, j, n));
+  }
+}
+
+// The epilogue of a tile of ROWS x 128 staged products (staged(r, ch): chunk ch
+// of row r, tile column 4 ch on) at (m0, n0) by THREADS threads, kBatch chunks a
+// thread at a time: a batch's loads go out together (rows past the launch's last
+// read that row's again, as `info` has it), then each chunk is finished. With a
+// branch around each chunk the loads of one wait for those before it, which costs
+// the 128 x 128 ring 2 to 3 % of a launch (d = 1024 with 4096 columns 41.7
+// against 40.3 us); the large tiles' epilogues are bound by bandwidth.
+template <int MODE, int PREC, int ROWS, int THREADS, int kBatch, bool VEC, typename Staged>
+__device__ inline void tile_epilogue_batches(const ProductArgs& p, int m0, int n0,
+                                             const TileRow* info, Staged staged) {
+  constexpr bool kPacked = PREC == kPrecSparse && (MODE == kFused || MODE == kStore);
+  static_assert(ROWS * 32 % (THREADS * kBatch) == 0, "whole batches");
+  const int ch = threadIdx.x & 31, n = n0 + 4 * ch;
+#pragma unroll 1
+  for (int q = 0; q < ROWS * 32 / THREADS; q += kBatch) {
+    float4 y[kBatch], add[kBatch];
+    TileRow ri[kBatch];
+    PackedIn pin[kBatch];
+    Dense4In din[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int r = int(threadIdx.x + THREADS * (q + u)) >> 5;
+      ri[u] = info[r];
+      y[u] = staged(r, ch);
+      if constexpr (kPacked)
+        pin[u] = load_packed<MODE>(p, ri[u].j, n);
+      else if constexpr (MODE == kFused || MODE == kStore)
+        din[u] = load_dense4_flat<MODE, VEC>(p, ri[u].j, n);
+      else if constexpr (MODE == kPlainAdd)
+        add[u] = ld4(p.out2 + size_t(ri[u].j) * p.dp + n);
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int r = int(threadIdx.x + THREADS * (q + u)) >> 5;
+      if (m0 + r >= p.n_rows) continue;
+      const size_t o = size_t(ri[u].j) * p.dp + n;
+      if constexpr (kPacked) {
+        finish_packed<MODE>(p, ri[u].j, n, y[u], ri[u].c, pin[u]);
+      } else if constexpr (MODE == kFused || MODE == kStore) {
+        finish_dense4<MODE, PREC>(p, ri[u].j, n, y[u], ri[u].c, din[u]);
+      } else if constexpr (MODE == kPlainAdd) {
+        st4(p.out1 + o, make_float4(add[u].x + y[u].x, add[u].y + y[u].y, add[u].z + y[u].z,
+                                    add[u].w + y[u].w));
+      } else {
+        st4(p.out1 + o, y[u]);
+        if constexpr (MODE == kPlain2) st4(p.out2 + o, y[u]);
+      }
+    }
+  }
+}
+// `part` (splits > 1): the range's partial sums, row r at part + r dp, instead.
+template <int MODE, int PREC, int ROWS, int THREADS, int BATCH, typename Staged>
+__device__ inline void tile_epilogue(const ProductArgs& p, int m0, int n0, const TileRow* info,
+                                     float* part, Staged staged) {
+  if (part) {
+    const int ch = threadIdx.x & 31;
+#pragma unroll 4
+    for (int q = 0; q < ROWS * 32 / THREADS; ++q) {
+      const int r = int(threadIdx.x + THREADS * q) >> 5;
+      if (m0 + r < p.n_rows) st4(part + size_t(m0 + r) * p.dp + n0 + 4 * ch, staged(r, ch));
+    }
+  } else if (MODE == kFused && PREC != kPrecSparse && (p.d & 3)) {
+    tile_epilogue_batches<MODE, PREC, ROWS, THREADS, BATCH, false>(p, m0, n0, info, staged);
+  } else {
+    tile_epilogue_batches<MODE, PREC, ROWS, THREADS, BATCH, true>(p, m0, n0, info, staged);
   }
 }
 
@@ -480,7 +577,6 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
   int tm, tn;
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
-  load_tile_rows<MODE>(p, m0, info);
   const int stages = p.dp * 4 / Cfg::kSRB;
   const int s0 = int(int64_t(stages) * sp / splits);
   const int s1 = int(int64_t(stages) * (sp + 1) / splits);
@@ -500,9 +596,12 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
                     k_off + t256_seg_bytes(i);
     }
   Acc256 acc;
-  gemm256_mainloop<Bf16x3Tag>(acc, src, s1 - s0, l0, l1, l2, l3, l4, l5, l6, l7);
+  gemm256_mainloop<Bf16x3Tag>(acc, src, s1 - s0, l0, l1, l2, l3, l4, l5, l6, l7,
+                               [&] {
+    if (splits == 1) load_tile_rows<MODE>(p, m0, info);
+  });
 
-  float* P = part + size_t(sp) * size_t(tiles_m) * Cfg::BM * size_t(p.dp);
+  float* P = splits > 1 ? part + size_t(sp) * size_t(tiles_m) * Cfg::BM * size_t(p.dp) : nullptr;
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb) {
     if (qb) __syncthreads();
@@ -523,22 +622,11 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
         }
     __syncthreads();
     if (n0 + 128 * qb >= p.dp) break;  // dp % 128 == 0: a half is all in or all out
-#pragma unroll 4
-    for (int q = 0; q < Cfg::BM * 32 / Cfg::kThreads; ++q) {
-      const int c = threadIdx.x + Cfg::kThreads * q;  // 16-byte chunk of the half
-      const int r = c >> 5, ch = c & 31;
-      const int rg = m0 + r;
-      if (rg >= p.n_rows) continue;
-      const float4 y = *reinterpret_cast<const float4*>(
-          t256_stage_row(l0, l1, l2, l3, l4, l5, l6, l7, r) + ((ch ^ (r & 31)) * 16));
-      const int n = n0 + 128 * qb + 4 * ch;
-      if (splits > 1) {
-        st4(P + size_t(rg) * p.dp + n, y);
-        continue;
-      }
-      const TileRow ri = info[r];
-      epilogue4<MODE, kPrecBf16x3>(p, ri.j, n, y, ri.c);
-    }
+    tile_epilogue<MODE, kPrecBf16x3, Cfg::BM, Cfg::kThreads, 2>(
+        p, m0, n0 + 128 * qb, info, P, [&](int r, int ch) {
+          return *reinterpret_cast<const float4*>(
+              t256_stage_row(l0, l1, l2, l3, l4, l5, l6, l7, r) + ((ch ^ (r & 31)) * 16));
+        });
   }
 }
 
@@ -561,7 +649,6 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
   int tm, tn;
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
-  load_tile_rows<MODE>(p, m0, info);
   const int stages = p.dp * 4 / Cfg::kSRB;
   const int s0 = int(int64_t(stages) * sp / splits);
   const int s1 = int(int64_t(stages) * (sp + 1) / splits);
@@ -578,7 +665,10 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
                t256_seg_bytes(i);
   }
   AccR128 acc;
-  r128_mainloop<Bf16x3Tag>(acc, src, s1 - s0, b0, b1, b2, b3);
+  r128_mainloop<Bf16x3Tag>(acc, src, s1 - s0, b0, b1, b2, b3,
+                           [&] {
+    if (splits == 1) load_tile_rows<MODE>(p, m0, info);
+  });
 
 #pragma unroll
   for (int mi = 0; mi < 4; ++mi)
@@ -593,23 +683,11 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
       }
     }
   __syncthreads();
-  float* P = part + size_t(sp) * size_t(tiles_m) * Cfg::BM * size_t(p.dp);
-#pragma unroll 4
-  for (int q = 0; q < Cfg::BM * 32 / Cfg::kThreads; ++q) {
-    const int c = threadIdx.x + Cfg::kThreads * q;  // 16-byte chunk of the tile
-    const int r = c >> 5, ch = c & 31;
-    const int rg = m0 + r;
-    if (rg >= p.n_rows) continue;
-    const float4 y = *reinterpret_cast<const float4*>(r128_stage_row(b0, b1, r) +
-                                                       ((ch ^ (r & 31)) * 16));
-    const int n = n0 + 4 * ch;
-    if (splits > 1) {
-      st4(P + size_t(rg) * p.dp + n, y);
-      continue;
-    }
-    const TileRow ri = info[r];
-    epilogue4<MODE, kPrecBf16x3>(p, ri.j, n, y, ri.c);
-  }
+  float* P = splits > 1 ? part + size_t(sp) * size_t(tiles_m) * Cfg::BM * size_t(p.dp) : nullptr;
+  tile_epilogue<MODE, kPrecBf16x3, Cfg::BM, Cfg::kThreads, 4>(
+      p, m0, n0, info, P, [&](int r, int ch) {
+        return *reinterpret_cast<const float4*>(r128_stage_row(b0, b1, r) + ((ch ^ (r & 31)) * 16));
+      });
 }
 
 #ifdef OPTIMA_PHASE_STAMPS
@@ -647,14 +725,21 @@ __device__ inline int coop_stamp_block() {
 #endif
 
 // The iteration products with x 2:4-compressed (kPrecSparse): 256 x 128
-// tiles of 8 waves on the sparse MFMA, one workgroup per CU (132 KiB of
-// LDS). Split ranges, partial sums and the epilogue work as in k_product,
-// with partial rows padded to the 256-row tile.
+// tiles of 8 waves on the sparse MFMA, one workgroup per CU (the loop of
+// gemm_sparse.h). Split ranges, partial sums and the epilogue work as in
+// k_product, with partial rows padded to the 256-row tile.
 template <int MODE>
 __global__ void __launch_bounds__(SpTile::kThreads) k_product_sparse(ProductArgs p, int splits,
                                                                      float* part) {
-  __shared__ __attribute__((aligned(1024))) char lds0[SpTile::kBufBytes];
-  __shared__ __attribute__((aligned(1024))) char lds1[SpTile::kBufBytes];
+  __shared__ __attribute__((aligned(1024))) char a00[SpTile::kABytes];
+  __shared__ __attribute__((aligned(1024))) char a01[SpTile::kABytes];
+  __shared__ __attribute__((aligned(1024))) char a10[SpTile::kABytes];
+  __shared__ __attribute__((aligned(1024))) char a11[SpTile::kABytes];
+  __shared__ __attribute__((aligned(1024))) char b0[SpTile::kBBytes];
+  __shared__ __attribute__((aligned(1024))) char b1[SpTile::kBBytes];
+  __shared__ __attribute__((aligned(1024))) char ix0[SpTile::kIdxBytes];
+  __shared__ __attribute__((aligned(1024))) char ix1[SpTile::kIdxBytes];
+  __shared__ TileRow info[SpTile::BM];
   const int tiles_m = (p.n_rows + SpTile::BM - 1) / SpTile::BM;
   const int tiles_n = p.dp / SpTile::BN;
   const int n_tiles = tiles_m * tiles_n;
@@ -667,17 +752,16 @@ __global__ void __launch_bounds__(SpTile::kThreads) k_product_sparse(ProductArgs
   const int s0 = int(int64_t(stages) * sp / splits);
   const int s1 = int(int64_t(stages) * (sp + 1) / splits);
 
-  auto col_of = [&](int r) {
-    r = m0 + r;
-    r = r < p.n_rows ? r : p.n_rows - 1;
-    return p.rows ? p.rows[r] : r;
-  };
   SpOperands src;
-  const char* ap = reinterpret_cast<const char*>(p.Ap);
 #pragma unroll
-  for (int i = 0; i < SpTile::kLoadsA; ++i)
-    src.a[i] = ap + size_t(col_of(sp_a_row(i))) * p.dp * 2 + size_t(s0) * SpTile::kARowBytes +
-               sp_a_seg_bytes(i);
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < Tile256::kHalfLoads; ++i) {
+      const int r = min(m0 + 128 * h + t256_load_row(i), p.n_rows - 1);
+      const int j = p.rows ? p.rows[r] : r;
+      src.a[h][i] = reinterpret_cast<const char*>(p.Ap) + size_t(j) * p.dp * 2 +
+                    size_t(s0) * SpTile::kARowBytes + t256_seg_bytes(i);
+    }
 #pragma unroll
   for (int i = 0; i < SpTile::kLoadsB; ++i)
     src.b[i] = reinterpret_cast<const char*>(p.Bp) + size_t(n0 + sp_b_row(i)) * p.dp * 4 +
@@ -685,35 +769,40 @@ __global__ void __launch_bounds__(SpTile::kThreads) k_product_sparse(ProductArgs
   src.ai = reinterpret_cast<const char*>(p.AidxS) +
            (size_t(s0) * size_t(p.idx_pitch) + size_t(m0 + sp_idx_row())) * 8 + sp_idx_bytes();
   src.ai_stage = int64_t(p.idx_pitch) * 8;
-  f4 acc[SpTile::MB][SpTile::NB];
+  SpAcc acc;
 #ifdef OPTIMA_PHASE_STAMPS
   const uint64_t stamp0 = wall_clock64();
 #endif
-  gemm_sparse_mainloop(acc, src, s1 - s0, lds0, lds1);
+  gemm_sparse_mainloop(acc, src, s1 - s0, a00, a01, b0, ix0, a10, a11, b1, ix1,
+                       [&] {
+    if (splits == 1) load_tile_rows<MODE>(p, m0, info);
+  });
 #ifdef OPTIMA_PHASE_STAMPS
   const uint64_t stamp1 = wall_clock64();
 #endif
 
-  sp_stage_tile(acc, lds0, lds1);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = t256_row(h, mi, e);
+        char* row = sp_stage_row(a00, a01, a10, a11, b0, b1, r);
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) {
+          const int c = t256_col(0, ni);
+          *reinterpret_cast<float*>(row + ((c >> 2) ^ (r & 31)) * 16 + (c & 3) * 4) =
+              acc.q[h][mi][ni][e];
+        }
+      }
   __syncthreads();
-  const float L = (MODE == kFused || MODE == kStore) ? *p.Lp : 0.f;
-  float* P = part + size_t(sp) * size_t(tiles_m) * SpTile::BM * size_t(p.dp);
-  constexpr int kChunks = SpTile::BM * SpTile::BN / 4;
-#pragma unroll 4
-  for (int q = 0; q < kChunks / SpTile::kThreads; ++q) {
-    const int c = threadIdx.x + SpTile::kThreads * q;  // 16-byte chunk of the tile
-    const int r = c >> 5, ch = c & 31;
-    const int rg = m0 + r;
-    if (rg >= p.n_rows) continue;
-    const float4 y = sp_staged_chunk(lds0, lds1, r, ch);
-    const int n = n0 + 4 * ch;
-    if (splits > 1) {
-      st4(P + size_t(rg) * p.dp + n, y);
-      continue;
-    }
-    const int j = p.rows ? p.rows[rg] : rg;
-    epilogue4<MODE, kPrecSparse>(p, j, n, y, row_coef<MODE>(p, j, L));
-  }
+  float* P = splits > 1 ? part + size_t(sp) * size_t(tiles_m) * SpTile::BM * size_t(p.dp) : nullptr;
+  tile_epilogue<MODE, kPrecSparse, SpTile::BM, SpTile::kThreads, 2>(
+      p, m0, n0, info, P, [&](int r, int ch) {
+        return *reinterpret_cast<const float4*>(sp_stage_row(a00, a01, a10, a11, b0, b1, r) +
+                                                ((ch ^ (r & 31)) * 16));
+      });
 #ifdef OPTIMA_PHASE_STAMPS
   tile_stamp(stamp0, stamp1, MODE, p.n_rows);
 #endif
@@ -2342,28 +2431,6 @@ int choose_splits(int tiles, int stages, int tiles_m, int dp, size_t part_cap) {
   return best;
 }
 
-// Number of K ranges for a tile that fills a CU with one workgroup: the
-// fewest CU rounds per unit of work, charging 5% per extra range for the
-// partial sums and their epilogue.
-int choose_splits_one_per_cu(int tiles, int stages, int rows_pad, int dp, size_t part_cap) {
-  const int n_cu = device_cu_count();
-  auto cost = [&](int S) {
-    return double(ceil_div(int64_t(tiles) * S, n_cu)) / S * (1.0 + 0.05 * (S - 1));
-  };
-  int best = 1;
-  double best_cost = cost(1);
-  for (int S = 2; S <= kMaxSplits && S <= stages; ++S) {
-    if (int64_t(tiles) * S > kMaxSplitTiles) break;
-    if (size_t(S) * size_t(rows_pad) * size_t(dp) > part_cap) break;
-    const double c = cost(S);
-    if (c < best_cost - 1e-9) {
-      best = S;
-      best_cost = c;
-    }
-  }
-  return best;
-}
-
 // Tile and number of K ranges of a dense bf16x3 product.
 enum class DenseTile { kSmall, kRing128, k256 };  // k_product, k_product_ring, k_product256
 struct DensePlan {
@@ -2424,6 +2491,46 @@ DensePlan plan_dense(int64_t n_rows, int64_t dp, int out_bytes, size_t part_cap)
         best_us = us;
         best = DensePlan{t.id, S};
       }
+    }
+  }
+  return best;
+}
+
+// Number of K ranges of a 2:4-sparse product, by a model as above: a stage takes
+// 1.17 us on a full chip and 0.95 while part of it is idle, and an epilogue in
+// the tiles' own launch reaches the chip's rate from 0.6 workgroups a CU. us an
+// iteration with 1, 2 and 3 ranges:
+//   d = 768,  3072 columns (72 tiles)    28.3  26.1  27.1
+//   d = 1024, 4096 columns (128 tiles)   36.5  40.0  50.5
+//   d = 2048, 2048 columns (128 tiles)   54.8  49.8  62.3
+//   d = 4096, 800 columns (128 tiles)    80.6  66.8  82.7
+//   d = 4096, 3000 columns (384 tiles)    199   211   210
+// Whole rounds at 5 % a range, without the outputs' bytes, took three ranges for
+// d = 1536 with 4096 columns (82 us, now 47) and d = 2048 with 3072 (91, now 61).
+int plan_sparse(int64_t n_rows, int64_t dp, int out_bytes, size_t part_cap) {
+  constexpr double kStageUs = 1.17, kLeastUs = 0.95, kFixedUs = 4.0, kLaunchUs = 5.0;
+  constexpr double kBytesPerUs = 8.5e6, kFullRate = 0.6;
+  const int n_cu = device_cu_count();
+  const int64_t stages = dp / SpTile::kKPerStage;
+  const int64_t rows = ceil_div(n_rows, SpTile::BM) * SpTile::BM;
+  const int64_t tiles = rows / SpTile::BM * (dp / SpTile::BN);
+  const double outputs = double(n_rows) * double(dp);
+  int best = 1;
+  double best_us = 1e30;
+  for (int S = 1; S <= kMaxSplits && S <= stages; ++S) {
+    if (S > 1 && (tiles * S > kMaxSplitTiles || size_t(S) * size_t(rows) * size_t(dp) > part_cap))
+      break;
+    const int64_t full = tiles * S / n_cu;
+    const double part = double(tiles * S % n_cu) / n_cu;
+    const double per_stage =
+        full * kStageUs + (part > 0.0 ? std::max(kLeastUs, part * kStageUs) : 0.0);
+    const double rate = S > 1 ? 1.0 : std::min(1.0, double(tiles) / (kFullRate * n_cu));
+    double us = double(ceil_div(stages, S)) * per_stage + double(full + (part > 0.0)) * kFixedUs +
+                outputs * out_bytes / (kBytesPerUs * rate);
+    if (S > 1) us += outputs * 8.0 * S / kBytesPerUs + kLaunchUs;
+    if (us < best_us) {
+      best_us = us;
+      best = S;
     }
   }
   return best;
@@ -2553,16 +2660,15 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
     }
     return OPTIMA_OK;
   }
-  const bool sparse = PREC == kPrecSparse;
-  const int bm = sparse ? SpTile::BM : kTile;
+  constexpr bool kSparse = PREC == kPrecSparse;
+  constexpr int bm = kSparse ? SpTile::BM : kTile;
   const int tiles_m = int(ceil_div(p.n_rows, bm));
   const int tiles_n = p.dp / kTile;
-  const int stages = sparse ? p.dp / SpTile::kKPerStage : p.dp * 4 / ProductTile::SRB;
   const int rows_pad = tiles_m * bm;
-  const int S = sparse ? choose_splits_one_per_cu(tiles_m * tiles_n, stages, rows_pad, p.dp,
-                                                  l.part_elems)
-                       : choose_splits(tiles_m * tiles_n, stages, tiles_m, p.dp, l.part_elems);
-  if constexpr (PREC == kPrecSparse)
+  const int S = kSparse ? plan_sparse(p.n_rows, p.dp, epilogue_bytes(MODE), l.part_elems)
+                        : choose_splits(tiles_m * tiles_n, p.dp * 4 / ProductTile::SRB, tiles_m,
+                                        p.dp, l.part_elems);
+  if constexpr (kSparse)
     hipLaunchKernelGGL((k_product_sparse<MODE>), dim3(tiles_m * tiles_n * S),
                        dim3(SpTile::kThreads), 0, s, p, S, l.part);
   else

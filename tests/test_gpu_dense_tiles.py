@@ -1,4 +1,4 @@
-"""The dense bf16x3 products on every tile that their plan takes, at the tiles'
+"""The iteration products on every tile that their plans take, at the tiles'
 and loops' remainders: ragged batches, half a 256-wide tile at the end of H,
 split contractions down to one stage a range. Columns are independent, so the
 oracle runs on a sample of them, the batch's last rows among it."""
@@ -44,6 +44,36 @@ def test_products_match_the_oracle(L, d, n):
     # Before the first check both follow the same continuous map; bf16x3 products
     # are off by up to 3 * 2^-16 each.
     err = np.linalg.norm(W[cols] - ref.W, axis=1) / np.linalg.norm(ref.W, axis=1)
+    assert err.max() <= 1e-4
+    np.testing.assert_allclose(st["f_initial"][cols], ref.f_initial, rtol=1e-5, atol=1e-12)
+
+
+# (d, columns): the 256 x 128 tile of the 2:4 products in one range of 24 stages
+# and in 2 to 11 ranges of 1 to 8 stages, odd counts among them, with one row and
+# one full tile in the last row tile, and a padded d.
+@pytest.mark.parametrize("d, n", [(640, 2100), (1536, 4096), (768, 3073), (512, 257), (768, 300),
+                                  (2048, 130), (1100, 512), (4096, 9)])
+def test_sparse_products_match_the_oracle(L, d, n):
+    rng = np.random.default_rng(d + n)
+    A = rng.standard_normal((d + 64, d)) * np.exp(rng.normal(0.0, 0.5, d))
+    H = A.T @ A
+    H = ((H + H.T) / 2 + 0.01 * np.trace(H) / d * np.eye(d)).astype(np.float32)
+    W0 = (0.02 * rng.standard_normal((n, d))).astype(np.float32)
+    order = rng.random((n, d // 4, 4)).argsort(axis=2)
+    M = (order < rng.integers(0, 3, (n, d // 4, 1))).astype(np.uint8).reshape(n, d)
+    lam = np.float32(1.05 * np.linalg.norm(H.astype(np.float64) @ rng.standard_normal(d)))
+    W, st, info = gpu_solve(L, to_dev(H), to_dev(np.array([lam])), W0, M,
+                            L.SolverOpts.default(max_iters=6, fixed_iters=1))
+    assert info["sparse_products"] == 1
+    W = W.cpu().numpy()
+    assert np.all(W[M == 0].view(np.uint32) == 0)
+    cols = np.unique(np.concatenate([rng.choice(n, min(n, 24), replace=False),
+                                     np.arange(max(0, n - 8), n)]))
+    ref = oracle.rapdhg(H.astype(np.float64), W0[cols], M[cols], float(lam),
+                        oracle.SolverOptions(max_iters=6, fixed_iters=True))
+    # The bound of the dense products.
+    norm = np.linalg.norm(ref.W, axis=1)
+    err = np.linalg.norm(W[cols] - ref.W, axis=1) / np.maximum(norm, 1e-30)
     assert err.max() <= 1e-4
     np.testing.assert_allclose(st["f_initial"][cols], ref.f_initial, rtol=1e-5, atol=1e-12)
 
