@@ -554,7 +554,8 @@ __global__ void k_copy_sub_iters(const SubState* st, int32_t* iters) { *iters = 
 //   k_lz_orth     c_i = q_i . y, w = y - sum_i c_i q_i, and partial sums of
 //                 q_i . w;
 //   k_lz_orth     c'_i = q_i . w, w <- w - sum_i c'_i q_i, and partial sums of
-//                 ||w||^2;
+//                 ||w||^2
+// (small bases: k_lz_one in the place of these three);
 // then alpha_j = c_j + c'_j and beta_j = ||w||. In exact arithmetic c_i
 // vanishes for i < j - 1, c_(j-1) = beta_(j-1) and c_j = alpha_j: the two
 // passes are the three-term recurrence followed by one more Gram-Schmidt pass
@@ -565,10 +566,10 @@ __global__ void k_copy_sub_iters(const SubState* st, int32_t* iters) { *iters = 
 //
 // The small kernels are bound by latency: each workgroup sums the coefficients'
 // partials itself, which saves two launches a step, and the finish runs beside
-// the product. A step takes 26 us at d = 1000 and 110 us at d = 14336; with a
-// launch for each of the two coefficient sums and for the finish (24 us, of which
-// 512 LDS atomics on one word a round and a reciprocal in every pivot's chain
-// were most), and all of H read, it took 37 and 194 us.
+// the product. A step takes 22 us at d = 1000 (k_lz_one) and 110 us at d =
+// 14336; with a launch for each of the two coefficient sums and for the finish
+// (24 us, of which 512 LDS atomics on one word a round and a reciprocal in every
+// pivot's chain were most), and all of H read, it took 37 and 194 us.
 
 constexpr int kLzMax = OPTIMA_LANCZOS_MAX_STEPS;
 constexpr int kLzThreads = 512;
@@ -1011,6 +1012,102 @@ __global__ void __launch_bounds__(kLzThreads) k_lz_orth(const float* Q, int64_t 
   }
 }
 
+// k_lz_gather and both k_lz_orth passes of a step in one workgroup, for matrices
+// (d <= kLzOneMaxDim, one slot) and steps ((j + 1) dp <= kLzOneMaxBasis) whose
+// basis one CU reads and converts in less time than two launches take. Thread t
+// keeps row t of y and then of w, a wave takes the coefficients of two vectors at
+// a time with the vector's entries in registers. norm_part keeps its form:
+// ||w||^2, then zeros.
+//
+// Bound by latency, and by the fp64 conversions as the basis grows. us a step over
+// 64 steps, three launches and this one: d = 128 12.4 and 9.2, 512 21.3 and 15.5,
+// 1000 26.1 and 22.2. Bases of at most 24576, 49152 and any number of entries take
+// 24.0, 23.1 and 23.5 at d = 1024, 22.2, 21.4 and 21.5 at d = 640.
+constexpr int kLzOneMaxDim = 1024;  // a row a thread
+constexpr int64_t kLzOneMaxBasis = 49152;
+
+__global__ void __launch_bounds__(kLzOneMaxDim) k_lz_one(const float* z, float* w, int64_t d,
+                                                         int64_t dp, int j, float* Q,
+                                                         double* norm_part, int nblk, LzState* st) {
+  constexpr int kWaves = kLzOneMaxDim / 64, kSegs = kLzOneMaxDim / 256;
+  __shared__ double c[kLzMax];
+  __shared__ __attribute__((aligned(16))) float v[kLzOneMaxDim];
+  __shared__ double red[kWaves];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, n = int(d);
+  const bool in = t < n;
+  const float zt = in ? z[t] : 0.f, wt = in ? w[t] : 0.f;
+  double n2 = 0.0;
+  for (int k = 0; k < nblk && j > 0; ++k) n2 += norm_part[k];
+  if (st->conv) return;
+  const double inv = j > 0 ? 1.0 / sqrt(n2) : st->inv0;
+  float x = float(double(zt) * inv);
+  v[t] = x;
+  if (in) Q[int64_t(j) * dp + t] = float(double(wt) * inv);
+  __syncthreads();
+#pragma unroll 1
+  for (int pass = 0; pass < 2; ++pass) {
+    double y[kSegs][4];  // entries 4 lane + 256 k + e
+#pragma unroll
+    for (int k = 0; k < kSegs; ++k) {
+      const float4 f = *reinterpret_cast<const float4*>(v + 4 * lane + 256 * k);
+      y[k][0] = f.x, y[k][1] = f.y, y[k][2] = f.z, y[k][3] = f.w;
+    }
+    for (int i0 = wv; i0 <= j; i0 += 2 * kWaves) {
+      float4 q[2][kSegs];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int k = 0; k < kSegs; ++k) {
+          const int i = min(i0 + u * kWaves, j), r = 4 * lane + 256 * k;
+          q[u][k] = make_float4(0.f, 0.f, 0.f, 0.f);
+          // The pitch is a multiple of 64: the load is inside the row.
+          if (r < n) q[u][k] = *reinterpret_cast<const float4*>(Q + int64_t(i) * dp + r);
+        }
+      double s[2] = {0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int k = 0; k < kSegs; ++k) {
+          const int r = 4 * lane + 256 * k;  // the row's padding holds anything
+          s[u] += double(q[u][k].x) * y[k][0];
+          s[u] += double(r + 1 < n ? q[u][k].y : 0.f) * y[k][1];
+          s[u] += double(r + 2 < n ? q[u][k].z : 0.f) * y[k][2];
+          s[u] += double(r + 3 < n ? q[u][k].w : 0.f) * y[k][3];
+        }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) s[u] += __shfl_xor(s[u], o, 64);
+      if (lane == 0)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int i = i0 + u * kWaves;
+          if (i <= j) c[i] = s[u];
+          if (i == j) st->cj[pass] = s[u];
+        }
+    }
+    __syncthreads();
+    if (in) {
+      double a = 0.0;
+#pragma unroll 16
+      for (int i = 0; i <= j; ++i) a += c[i] * double(Q[int64_t(i) * dp + t]);
+      x = float(double(x) - a);
+      v[t] = x;
+    }
+    __syncthreads();
+  }
+  if (in) w[t] = x;
+  double s2 = double(x) * double(x);
+  for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, 64);
+  if (lane == 0) red[wv] = s2;
+  __syncthreads();
+  if (t < nblk) {
+    double sum = 0.0;
+    for (int k = 0; k < kWaves && t == 0; ++k) sum += red[k];
+    norm_part[t] = sum;
+  }
+}
+
 // The finish of the last step, after which no product follows.
 __global__ void __launch_bounds__(kLzThreads) k_lz_close(const double* norm_part, int nblk, int j,
                                                          int n_max, float tol, LzState* st,
@@ -1267,15 +1364,21 @@ optima_status spectral_lanczos(const float* H, int64_t d, const float* v0, int m
     hipLaunchKernelGGL(product, grid, threads, 0, s, H, d, l.dp, l.w, l.ypart, j, l.norm_part,
                        l.nblk, m, tol, l.st, lambda_max);
     OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_gather, rows, threads, 0, s, l.ypart, sym ? l.slots : 1, l.w, d, l.dp,
-                       j, l.Q, l.y, l.part1, m, l.norm_part, l.st);
-    OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_orth, rows, threads, 0, s, l.Q, d, l.dp, j, 0, l.y, l.w, l.part1,
-                       l.part2, m, l.norm_part, l.st);
-    OPTIMA_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_lz_orth, rows, threads, 0, s, l.Q, d, l.dp, j, 1, l.w, l.w, l.part2,
-                       l.part1, m, l.norm_part, l.st);
-    OPTIMA_LAUNCH_CHECK();
+    if (d <= kLzOneMaxDim && int64_t(j + 1) * l.dp <= kLzOneMaxBasis) {
+      hipLaunchKernelGGL(k_lz_one, dim3(1), dim3(kLzOneMaxDim), 0, s, l.ypart, l.w, d, l.dp, j,
+                         l.Q, l.norm_part, l.nblk, l.st);
+      OPTIMA_LAUNCH_CHECK();
+    } else {
+      hipLaunchKernelGGL(k_lz_gather, rows, threads, 0, s, l.ypart, sym ? l.slots : 1, l.w, d,
+                         l.dp, j, l.Q, l.y, l.part1, m, l.norm_part, l.st);
+      OPTIMA_LAUNCH_CHECK();
+      hipLaunchKernelGGL(k_lz_orth, rows, threads, 0, s, l.Q, d, l.dp, j, 0, l.y, l.w, l.part1,
+                         l.part2, m, l.norm_part, l.st);
+      OPTIMA_LAUNCH_CHECK();
+      hipLaunchKernelGGL(k_lz_orth, rows, threads, 0, s, l.Q, d, l.dp, j, 1, l.w, l.w, l.part2,
+                         l.part1, m, l.norm_part, l.st);
+      OPTIMA_LAUNCH_CHECK();
+    }
     if ((j + 1) % kPoll == 0 && j + 1 < m) {
       int conv = 0;
       OPTIMA_HIP_TRY(read_back(&conv, &l.st->conv, sizeof(int), s));

@@ -202,3 +202,28 @@ def test_lanczos_one_triangle_of_h(L, d):
     # A NaN above the diagonal, which only the first step reads.
     Hd[1, d - 1] = float("nan")
     assert np.isnan(gpu_lanczos(L, Hd, v0)[0])
+
+
+@pytest.mark.parametrize("d, steps", [(3, (2,)), (65, (12, 30)), (640, (76, 77, 90)),
+                                      (1000, (48, 49, 60)), (1023, (12,)), (1024, (48, 55)),
+                                      (1025, (12,))])
+def test_lanczos_one_workgroup_steps(L, d, steps):
+    # Up to d = 1024 a step's vector work runs in one workgroup until the basis
+    # holds 49152 entries (76 steps at d = 640, 48 at 1000), then in several:
+    # before, at and beyond the change, and on ragged rows.
+    rng = np.random.default_rng(d)
+    B = rng.standard_normal((d, 24)).astype(np.float32)
+    Hin = f32_exact(B @ B.T / 24 + np.diag(np.linspace(0.5, 1.5, d)))
+    v0 = rng.standard_normal(d).astype(np.float32)
+    Hd = to_dev(Hin)
+    for m in steps:
+        lam_g, st_g = gpu_lanczos(L, Hd, v0, max_steps=m, tol=0.0)
+        lam_o, st_o = oracle.lanczos(Hin, v0, m, 0.0)
+        log(f"  d={d} m={m}: gpu {lam_g:.9e} oracle {lam_o:.9e}")
+        assert lam_g == pytest.approx(lam_o, rel=2e-6)
+        # Up to 12 steps the Ritz value still rises by more than fp32 rounding;
+        # once it has converged, rounding says which step does not raise it.
+        if m <= 12:
+            assert st_g == st_o == m
+    Hd[d - 1, 0] = float("nan")
+    assert np.isnan(gpu_lanczos(L, Hd, v0)[0])
