@@ -77,7 +77,10 @@ def log(msg: str):
     print(msg, file=sys.stderr, flush=True)
 
 
-def kernel_sources_sha1(files=("gemm_core.h", "solver.hip")) -> str:
+SOLVER_SOURCES = ("gemm_core.h", "gemm128.h", "gemm256.h", "gemm_sparse.h", "solver.hip")
+
+
+def kernel_sources_sha1(files=SOLVER_SOURCES) -> str:
     h = hashlib.sha1()
     for f in files:
         with open(os.path.join(ROOT, "paper_2512_13886_amd", "csrc", f), "rb") as fh:
@@ -188,11 +191,8 @@ def product_kernel_name(d: int, rows: int, prec_name: str, sparse: bool) -> str:
     if sparse:
         return ("k_product_sparse<fused> (256 x 128 tiles, x 2:4-compressed, "
                 "v_smfmac_f32_16x16x64_bf16, three bf16 products per fp32 product)")
-    if d >= 8192 and rows >= 256:
-        return ("k_product_wide<fused, bf16x3> (256 x 128 tiles, v_mfma_f32_16x16x32_bf16, "
-                "three bf16 products per fp32 product)")
-    return ("k_product<fused, bf16x3> (128 x 128 tiles, v_mfma_f32_16x16x32_bf16, three "
-            "bf16 products per fp32 product)")
+    return ("k_product256, k_product_ring or k_product<fused, bf16x3> as the plan chooses (256 x 256 "
+            "or 128 x 128 tiles, v_mfma_f32_16x16x32_bf16, three bf16 products per fp32 product)")
 
 
 def product_roofline(d: int, infos: list, prec_name: str, traffic=None,
