@@ -603,11 +603,12 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   // of the chip idle (1, 3, 6 or 10 tiles: d up to 1024).
   p.spread = 7 * 8 * ceil_div(p.tiles, int64_t(8)) > 8 * p.tiles;
   // Splits along the tokens: the rounds of workgroups per CU relative to the
-  // work (1.6 us a 64-token stage), 1% per split for starts and ends, and, from
-  // two splits on, the partial sums' bytes, written and read at 5.2 TB/s, and
+  // work (1.6 us a 64-token stage), and for each split the larger of 1% (starts
+  // and ends) and the partial sums' bytes, written and read at 5.2 TB/s, with
   // the kernel that adds them; at most 4 GiB of partials. A 2048-token sequence
   // at d = 4096 takes one split (68 us a call, fused); 11 splits, which
-  // 262144 tokens take there, made it 215 us, half of it in the sums.
+  // 262144 tokens take there, made it 215 us, half of it in the sums. 262144
+  // tokens in 9 splits, which the sum of both charges chose: 3.71 against 3.65 ms.
   int best = 1;
   double best_cost = 1e30;
   const int max_s = std::max(1, std::min(dt::kMaxSplits, p.stages));
@@ -616,8 +617,9 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
     if (S > 1 && double(S) * double(d) * double(d) * 4.0 > double(int64_t(1) << 32)) break;
     const int64_t units = p.spread ? p.tiles * S : 8 * ceil_div(p.tiles, int64_t(8)) * S;
     const double rounds = double(ceil_div(units, int64_t(dt::kCus)));
-    double c = rounds / S * (1.0 + 0.01 * S) * double(p.stages) * 1.6;
-    if (S > 1) c += S * tri_bytes * 2.0 / 5.2e6 + 5.0;
+    const double work = rounds / S * double(p.stages) * 1.6;
+    const double sums = S > 1 ? S * tri_bytes * 2.0 / 5.2e6 + 5.0 : 0.0;
+    const double c = work + std::max(0.01 * S * work, sums);
     if (c < best_cost - 1e-12) {
       best = S;
       best_cost = c;
