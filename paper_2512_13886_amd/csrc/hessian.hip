@@ -440,8 +440,12 @@ __device__ inline void grouped_tri_tile(int idx, int nt, int* ti, int* tj) {
 // XCD's misses to the others. The grid is 8 times the largest XCD share;
 // workgroups beyond their XCD's share exit at once. With `spread` (few tiles,
 // whose eighths would leave XCDs idle) workgroup b takes unit b instead.
-// FUSED (splits == 1): H (+)= the tile's sum, both triangles; else the tile's
-// partial sum goes to part[sp] ([d][d] fp32).
+// !FUSED: the tile's partial sum over split sp goes to part[sp] ([d][d] fp32).
+// FUSED: one workgroup runs the tile's `splits` ranges one after the other and
+// does H (+)= their sum, both triangles. Registers hold one 256 x 256 fp32 tile,
+// so the running sum waits in part[tile] (256 KiB, thread by thread, 16 bytes a
+// lane) while a range is summed; only its own thread reads an entry back. The
+// sums are added in the order of k_hess_reduce: H is the same bit for bit.
 template <int WAVES, bool FUSED>
 __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
                                                             const uint16_t* tail, int64_t d,
@@ -464,61 +468,104 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
     tx = int(int64_t(n_tiles) * (x + 1) / 8) - t0;
     l = blockIdx.x >> 3;
   }
-  if (int64_t(l) >= int64_t(tx) * splits) return;
-  const int sp = l / tx;
+  if (int64_t(l) >= int64_t(tx) * (FUSED ? 1 : splits)) return;
+  const int tile = t0 + l % tx;
+  int sp = l / tx;
   int ti, tj;
-  grouped_tri_tile(t0 + l % tx, nt, &ti, &tj);
-  const int s0 = int(int64_t(stages) * sp / splits);
-  const int s1 = int(int64_t(stages) * (sp + 1) / splits);
-  const int n = s1 - s0;
+  grouped_tri_tile(tile, nt, &ti, &tj);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = 2 * wave + (lane >> 5);
   const int seg[2] = {((lane & 31) ^ swz(row)) * 16, ((lane & 31) ^ swz(row + 2 * WAVES)) * 16};
   const int64_t row_bytes = d * 2;
   const int64_t round_bytes = 2 * WAVES * row_bytes;
   const int64_t buf_bytes = kBufRows * row_bytes;
-  // This thread's first row of block 0 in buffer q (32 tokens) of the range:
-  // from X, or from the tail's two buffers. (Blocks ti and tj are 512 bytes an
-  // index further on.)
-  const char* xrow = reinterpret_cast<const char*>(X) + (int64_t(s0) * kRows + row) * row_bytes;
-  const char* trow = reinterpret_cast<const char*>(tail) + int64_t(row) * row_bytes;
+  // The workgroup's stages, nb = 2 n buffers of 32 tokens (at least one stage).
+  const int s0 = FUSED ? 0 : int(int64_t(stages) * sp / splits);
+  const int s1 = FUSED ? stages : int(int64_t(stages) * (sp + 1) / splits);
+  const int nb = 2 * (s1 - s0);
+  // This thread's first rows of blocks ti and tj in buffer 0, and the offset of
+  // buffer q: in X, or in the tail's two buffers (a scalar, so that a step adds
+  // it with the rest of the addresses). Loads past the last buffer repeat it
+  // (into buffers nobody reads again) so that every step waits for the same
+  // count; they are drained after the loop.
+  const char* x0 = reinterpret_cast<const char*>(X) + int64_t(s0) * kRows * row_bytes;
+  const char* xa = x0 + row * row_bytes + int64_t(ti) * kBlock * 2;
+  const char* xb = x0 + row * row_bytes + int64_t(tj) * kBlock * 2;
   const int q_tail = 2 * (full - s0);
-  const int64_t oa = int64_t(ti) * kBlock * 2, ob = int64_t(tj) * kBlock * 2;
-
+  const int64_t to_tail = int64_t(reinterpret_cast<uintptr_t>(tail)) -
+                          int64_t(reinterpret_cast<uintptr_t>(x0)) - q_tail * buf_bytes;
+  auto at = [&](int q) {
+    q = q < nb ? q : nb - 1;
+    return q * buf_bytes + (q < q_tail ? int64_t(0) : to_tail);
+  };
   f4 acc[C::kMB][C::kNB];
 #pragma unroll
   for (int mi = 0; mi < C::kMB; ++mi)
 #pragma unroll
     for (int ni = 0; ni < C::kNB; ++ni) acc[mi][ni] = f4{0.f, 0.f, 0.f, 0.f};
-  if (n > 0) {
-    // nb = 2 n buffers of 32 tokens. Loads past the last buffer repeat it
-    // (into buffers nobody reads again) so that every step waits for the
-    // same count; they are drained before the epilogue.
-    const int nb = 2 * n;
-    auto at = [&](int q) {
-      q = q < nb ? q : nb - 1;
-      return q < q_tail ? xrow + q * buf_bytes : trow + (q - q_tail) * buf_bytes;
-    };
-    auto step = [&](int q, char* cur, char* nxt) {
-      const char* p = at(q);
-      ring_step<C>(acc, p + oa, p + ob, round_bytes, seg, cur, nxt);
-    };
-    issue<C>(at(0) + oa, at(0) + ob, round_bytes, seg, lds0);
-    issue<C>(at(1) + oa, at(1) + ob, round_bytes, seg, lds1);
-    issue<C>(at(2) + oa, at(2) + ob, round_bytes, seg, lds2);
-    int q = 0;
-    for (; q + 4 <= nb; q += 4) {
-      step(q + 3, lds0, lds3);
-      step(q + 4, lds1, lds0);
-      step(q + 5, lds2, lds1);
-      step(q + 6, lds3, lds2);
-    }
-    if (q < nb) {
-      step(q + 3, lds0, lds3);
-      step(q + 4, lds1, lds0);
+  auto step = [&](int q, char* cur, char* nxt) {
+    const int64_t off = at(q);
+    ring_step<C>(acc, xa + off, xb + off, round_bytes, seg, cur, nxt);
+  };
+  // FUSED: after buffer q - 1, if a range but the last ends there, its sum joins
+  // the running sum. The ring goes on across ranges; the stores are drained, so
+  // the counts that its steps wait for stay those of its loads. (The opaque base
+  // and the barriers keep the compiler from holding 32 addresses, or all loads,
+  // in registers that it would have to spill for them.)
+  f4* const sums = reinterpret_cast<f4*>(part) + size_t(tile) * (kBlock * kBlock / 4);
+  int cut = FUSED ? 2 * int(int64_t(stages) / splits) : 0;
+  auto range_end = [&](int q) {
+    if (!FUSED || q != cut || q == nb) return;
+    f4* Q = sums;
+    asm volatile("" : "+s"(Q));
+#pragma unroll
+    for (int mi = 0; mi < C::kMB; ++mi) {
+      f4* const q4 = Q + mi * C::kNB * 64 * WAVES;
+      if (sp > 0) {
+        f4 sum[C::kNB];
+#pragma unroll
+        for (int ni = 0; ni < C::kNB; ++ni) sum[ni] = q4[ni * 64 * WAVES + threadIdx.x];
+#pragma unroll
+        for (int ni = 0; ni < C::kNB; ++ni) acc[mi][ni] = sum[ni] + acc[mi][ni];
+      }
+#pragma unroll
+      for (int ni = 0; ni < C::kNB; ++ni) {
+        q4[ni * 64 * WAVES + threadIdx.x] = acc[mi][ni];
+        acc[mi][ni] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
     wait_vmcnt<0>();
-    __syncthreads();
+    ++sp;
+    cut = 2 * int(int64_t(stages) * (sp + 1) / splits);
+  };
+
+  issue<C>(xa + at(0), xb + at(0), round_bytes, seg, lds0);
+  issue<C>(xa + at(1), xb + at(1), round_bytes, seg, lds1);
+  issue<C>(xa + at(2), xb + at(2), round_bytes, seg, lds2);
+  int q = 0;
+  for (; q + 4 <= nb; q += 4) {
+    step(q + 3, lds0, lds3);
+    step(q + 4, lds1, lds0);
+    range_end(q + 2);
+    step(q + 5, lds2, lds1);
+    step(q + 6, lds3, lds2);
+    range_end(q + 4);
+  }
+  if (q < nb) {
+    step(q + 3, lds0, lds3);
+    step(q + 4, lds1, lds0);
+  }
+  wait_vmcnt<0>();
+  __syncthreads();
+  if (FUSED && sp > 0) {
+#pragma unroll
+    for (int mi = 0; mi < C::kMB; ++mi) {
+      const f4* q4 = sums + mi * C::kNB * 64 * WAVES;
+#pragma unroll
+      for (int ni = 0; ni < C::kNB; ++ni) acc[mi][ni] = q4[ni * 64 * WAVES + threadIdx.x] + acc[mi][ni];
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
   float* P = FUSED ? H : part + size_t(sp) * size_t(d) * size_t(d);
   const int wm = wave / C::WGN, wn = wave % C::WGN;
@@ -603,34 +650,60 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   // of the chip idle (1, 3, 6 or 10 tiles: d up to 1024).
   p.spread = 7 * 8 * ceil_div(p.tiles, int64_t(8)) > 8 * p.tiles;
   // Splits along the tokens: the rounds of workgroups per CU relative to the
-  // work (1.6 us a 64-token stage), and for each split the larger of 1% (starts
-  // and ends) and the partial sums' bytes, written and read at 5.2 TB/s, with
-  // the kernel that adds them; at most 4 GiB of partials. A 2048-token sequence
-  // at d = 4096 takes one split (68 us a call, fused); 11 splits, which
-  // 262144 tokens take there, made it 215 us, half of it in the sums. 262144
-  // tokens in 9 splits, which the sum of both charges chose: 3.71 against 3.65 ms.
-  int best = 1;
+  // work, 1% a split for starts and ends, at most 4 GiB of partials. This is a
+  // lower bound for precision too: each split is a chain of fp32 sums of its
+  // own, and a 2048-token sequence at d = 4096 in one chain instead of 11 had a
+  // relative error of 1.5e-7 against 64 bits instead of 3.8e-8. (The last rows that
+  // are no stage do not lengthen a single chain.)
+  const int64_t share = ceil_div(p.tiles, int64_t(8));
+  const auto affordable = [d](int S) {
+    return S == 1 || double(S) * double(d) * double(d) * 4.0 <= double(int64_t(1) << 32);
+  };
+  const int max_s = std::min(dt::kMaxSplits, p.stages);
+  int least = p.full_stages > 0 && p.tail_rows > 0 && affordable(2) ? 2 : 1;
   double best_cost = 1e30;
-  const int max_s = std::max(1, std::min(dt::kMaxSplits, p.stages));
-  const double tri_bytes = double(p.tiles) * dt::kBlock * dt::kBlock * 4.0;
-  for (int S = 1; S <= max_s; ++S) {
-    if (S > 1 && double(S) * double(d) * double(d) * 4.0 > double(int64_t(1) << 32)) break;
-    const int64_t units = p.spread ? p.tiles * S : 8 * ceil_div(p.tiles, int64_t(8)) * S;
-    const double rounds = double(ceil_div(units, int64_t(dt::kCus)));
-    const double work = rounds / S * double(p.stages) * 1.6;
-    const double sums = S > 1 ? S * tri_bytes * 2.0 / 5.2e6 + 5.0 : 0.0;
-    const double c = work + std::max(0.01 * S * work, sums);
+  for (int S = least; S <= max_s && affordable(S); ++S) {
+    const double c = double(ceil_div(share * S, int64_t(dt::kCus / 8))) / S * (1.0 + 0.01 * S);
     if (c < best_cost - 1e-12) {
-      best = S;
+      least = S;
       best_cost = c;
     }
   }
-  p.splits = best;
-  // One [d][d] partial per split. A single split adds to H itself where enough
-  // CUs share the stores of both triangles: d = 512 (3 tiles) with 100 tokens
-  // takes longer that way.
-  p.fused = best == 1 && p.tiles >= 32;
-  p.part_elems = p.fused ? 0 : size_t(best) * size_t(d) * size_t(d);
+  // More than that only where tiles spread over all CUs gain from it, and from
+  // 32 stages a split on: d = 256 with 32768 tokens in 64 splits instead of 32
+  // gained nothing and was off by 1.17e-7 instead of 1.06e-7; d = 1024 in 25
+  // instead of 16 took 64 us instead of 72, 1.08e-7 instead of 1.15e-7. The
+  // rounds relative to the work (1.6 us a 64-token stage), and for each split
+  // the larger of 1% and the partial sums' bytes, written and read at 5.2 TB/s,
+  // with the kernel that adds them.
+  const double tri_bytes = double(p.tiles) * dt::kBlock * dt::kBlock * 4.0;
+  p.splits = least;
+  best_cost = 1e30;
+  const int most = p.stages >= 32 * least ? max_s : least;
+  for (int S = least; S <= most && affordable(S); ++S) {
+    const int64_t units = p.spread ? p.tiles * S : 8 * share * S;
+    const double rounds = double(ceil_div(units, int64_t(dt::kCus)));
+    const double work = rounds / S * double(p.stages) * 1.6;
+    const double c = work + std::max(0.01 * S * work, S * tri_bytes * 2.0 / 5.2e6 + 5.0);
+    if (c < best_cost - 1e-12) {
+      p.splits = S;
+      best_cost = c;
+    }
+  }
+  // FUSED: every tile's ranges in one workgroup, kRangeUs between two of them
+  // and kEndUs for the stores to H. Short ranges of many tiles, where the
+  // partial sums outweigh the idle CUs: d = 4096 with 512 tokens 83 us instead
+  // of 105, 2048 tokens 145 instead of 206.
+  constexpr double kRangeUs = 8.0, kEndUs = 13.0;
+  const double rounds = double(ceil_div(8 * share, int64_t(dt::kCus)));
+  const double fused_cost =
+      rounds * (double(p.stages) * 1.6 + (least - 1) * kRangeUs + kEndUs);
+  p.fused = p.tiles >= 32 && fused_cost < 0.9 * best_cost;
+  // One [d][d] partial per split; the running sums of FUSED (d (d + 256) / 2
+  // entries) fit one of them. The size stays that of the split plan, so that a
+  // workspace for more tokens always holds fewer.
+  p.part_elems = size_t(p.splits) * size_t(d) * size_t(d);
+  if (p.fused) p.splits = least;
   return p;
 }
 
@@ -682,10 +755,10 @@ optima_status hessian_accumulate(const void* X, int dtype, int64_t n_tok, int64_
                          int64_t(p.full_stages) * dt::kRows, p.tail_rows, tail);
       OPTIMA_LAUNCH_CHECK();
     }
-    const dim3 grid(direct_grid(p.tiles, p.splits, p.spread)), threads(64 * kDirectWaves);
+    const dim3 grid(direct_grid(p.tiles, p.fused ? 1 : p.splits, p.spread)), threads(64 * kDirectWaves);
     if (p.fused)
       hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, true>), grid, threads, 0, s, Xb, tail, d,
-                         p.full_stages, p.stages, 1, int(p.spread), part, H, accumulate);
+                         p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
     else
       hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false>), grid, threads, 0, s, Xb, tail, d,
                          p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
