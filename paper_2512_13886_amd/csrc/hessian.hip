@@ -440,13 +440,14 @@ __device__ inline void grouped_tri_tile(int idx, int nt, int* ti, int* tj) {
 // XCD's misses to the others. The grid is 8 times the largest XCD share;
 // workgroups beyond their XCD's share exit at once. With `spread` (few tiles,
 // whose eighths would leave XCDs idle) workgroup b takes unit b instead.
+// !TAIL (stages = full) spares each step the choice between X and the tail.
 // !FUSED: the tile's partial sum over split sp goes to part[sp] ([d][d] fp32).
 // FUSED: one workgroup runs the tile's `splits` ranges one after the other and
 // does H (+)= their sum, both triangles. Registers hold one 256 x 256 fp32 tile,
 // so the running sum waits in part[tile] (256 KiB, thread by thread, 16 bytes a
 // lane) while a range is summed; only its own thread reads an entry back. The
 // sums are added in the order of k_hess_reduce: H is the same bit for bit.
-template <int WAVES, bool FUSED>
+template <int WAVES, bool FUSED, bool TAIL>
 __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
                                                             const uint16_t* tail, int64_t d,
                                                             int full, int stages, int splits,
@@ -496,7 +497,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
                           int64_t(reinterpret_cast<uintptr_t>(x0)) - q_tail * buf_bytes;
   auto at = [&](int q) {
     q = q < nb ? q : nb - 1;
-    return q * buf_bytes + (q < q_tail ? int64_t(0) : to_tail);
+    return q * buf_bytes + (!TAIL || q < q_tail ? int64_t(0) : to_tail);
   };
   f4 acc[C::kMB][C::kNB];
 #pragma unroll
@@ -757,10 +758,13 @@ optima_status hessian_accumulate(const void* X, int dtype, int64_t n_tok, int64_
     }
     const dim3 grid(direct_grid(p.tiles, p.fused ? 1 : p.splits, p.spread)), threads(64 * kDirectWaves);
     if (p.fused)
-      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, true>), grid, threads, 0, s, Xb, tail, d,
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, true, true>), grid, threads, 0, s, Xb, tail, d,
+                         p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
+    else if (p.tail_rows == 0)
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false, false>), grid, threads, 0, s, Xb, tail, d,
                          p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
     else
-      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false>), grid, threads, 0, s, Xb, tail, d,
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false, true>), grid, threads, 0, s, Xb, tail, d,
                          p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
     OPTIMA_LAUNCH_CHECK();
     return p.fused ? OPTIMA_OK : reduce_partials(part, p.splits, d, d, H, accumulate, s);
