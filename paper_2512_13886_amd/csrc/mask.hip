@@ -280,6 +280,9 @@ __global__ void __launch_bounds__(T, WAVES) k_mask_select(const float* W0, int64
     // The last key kept is (top, r.lo) or above; below it none is.
     uint32_t top = r.lo;
     if (r.need != r.count) {
+      // Rows of one high word end the first call before any barrier that follows
+      // its reads of the waves' ranges, which the second call writes again.
+      __syncthreads();
       narrow<T, NK>(r, kl, [&](int q) { return in_row(q) && kh[q] == top; }, sh);
     } else {
       r.lo = 0u;

@@ -67,6 +67,24 @@ def test_unstructured_row_shapes(L, n, d):
             np.testing.assert_array_equal(gpu_mask(L, Wo, c, L.MASK_UNSTRUCTURED, sparsity), ref)
 
 
+# Rows whose keys share their high word (and whose range is found on the low
+# words, or by index alone) among ordinary ones, more rows than workgroups in the
+# smallest case, in every workgroup shape.
+@pytest.mark.parametrize("n, d", [(6000, 16), (40, 1000), (40, 4096), (20, 8192), (20, 16384)])
+def test_unstructured_rows_of_one_high_word(L, n, d):
+    rng = np.random.default_rng(n + d)
+    W = rng.standard_normal((n, d)).astype(np.float32)
+    c = 1.0 + rng.permutation(d) * 2.0 ** -52  # differ in the low word alone
+    W[0::5] = 0.0
+    W[1::5] = np.nan
+    W[2::5] = 1.0
+    W[3::10] = rng.choice([-1.0, 1.0], (len(W[3::10]), d))
+    for cs in (c, np.ones(d), np.zeros(d)):
+        for sparsity in (1.0 / d, 0.5, 0.9):
+            ref = oracle.wanda_mask(W, cs, "unstructured", sparsity)
+            np.testing.assert_array_equal(gpu_mask(L, W, cs, L.MASK_UNSTRUCTURED, sparsity), ref)
+
+
 @pytest.mark.parametrize("n, d", [(1, 4), (5000, 8), (3, 4 * 257)])
 def test_2to4_row_blocks(L, n, d):
     rng = np.random.default_rng(d)
