@@ -100,7 +100,8 @@ int optima_abi_version(void);
  * otherwise); H may alias nothing else. ws must hold
  * optima_hessian_workspace_bytes(n_tok, d, dtype) bytes: split-K partial sums,
  * plus a token-slab transpose buffer unless X is bf16 with d % 256 == 0 (then
- * token rows are read in place and only a 64-row tail buffer is needed).
+ * token rows are read in place and only a 64-row tail buffer is needed). The size
+ * for more tokens is never smaller.
  * ------------------------------------------------------------------------- */
 size_t optima_hessian_workspace_bytes(int64_t n_tok, int64_t d, int dtype);
 optima_status optima_hessian_accumulate(const void* X, int dtype, int64_t n_tok,

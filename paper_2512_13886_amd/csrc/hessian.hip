@@ -428,9 +428,10 @@ __device__ inline void grouped_tri_tile(int idx, int nt, int* ti, int* tj) {
     }
 }
 
-// X: [full * 64][d] bf16, followed, if stages = full + 1, by the 64 rows of
-// `tail`. The work units are the (split, tile) pairs of the triangle of d / 256 blocks; split sp covers
-// stages [stages sp / splits, stages (sp + 1) / splits). The dispatcher
+// X: [full * 64][d] bf16 (full >= 1), followed, if not NULL, by the 64 rows of
+// `tail`. The work units are the (split, tile) pairs of the triangle of d / 256
+// blocks; split sp covers stages [full sp / splits, full (sp + 1) / splits), and
+// the tail is one split more. The dispatcher
 // sends workgroup b to XCD b % 8, so XCD x runs workgroups x, x + 8, ... in
 // that order. XCD x owns the x-th eighth of the tiles in grouped_tri_tile
 // order (a few feature blocks) for every split, and runs them split by
@@ -440,18 +441,18 @@ __device__ inline void grouped_tri_tile(int idx, int nt, int* ti, int* tj) {
 // XCD's misses to the others. The grid is 8 times the largest XCD share;
 // workgroups beyond their XCD's share exit at once. With `spread` (few tiles,
 // whose eighths would leave XCDs idle) workgroup b takes unit b instead.
-// !TAIL (stages = full) spares each step the choice between X and the tail.
-// !FUSED: the tile's partial sum over split sp goes to part[sp] ([d][d] fp32).
-// FUSED: one workgroup runs the tile's `splits` ranges one after the other and
-// does H (+)= their sum, both triangles. Registers hold one 256 x 256 fp32 tile,
-// so the running sum waits in part[tile] (256 KiB, thread by thread, 16 bytes a
+// The partial sums are part[0] for split 0, part[1] for the tail, then the other
+// splits ([d][d] fp32 each): sums in that order, few rows to few rows first.
+// FUSED: one workgroup runs all ranges of a tile, the tail's first, and does
+// H (+)= their sum, both triangles. Registers hold one 256 x 256 fp32 tile, so
+// the running sum waits in part[tile] (256 KiB, thread by thread, 16 bytes a
 // lane) while a range is summed; only its own thread reads an entry back. The
 // sums are added in the order of k_hess_reduce: H is the same bit for bit.
-template <int WAVES, bool FUSED, bool TAIL>
+template <int WAVES, bool FUSED>
 __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
                                                             const uint16_t* tail, int64_t d,
-                                                            int full, int stages, int splits,
-                                                            int spread, float* part, float* H,
+                                                            int full, int splits, int spread,
+                                                            float* part, float* H,
                                                             int accumulate) {
   using namespace dt;
   using C = Cfg<WAVES>;
@@ -469,7 +470,8 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
     tx = int(int64_t(n_tiles) * (x + 1) / 8) - t0;
     l = blockIdx.x >> 3;
   }
-  if (int64_t(l) >= int64_t(tx) * (FUSED ? 1 : splits)) return;
+  const int tails = tail != nullptr;
+  if (int64_t(l) >= int64_t(tx) * (FUSED ? 1 : splits + tails)) return;
   const int tile = t0 + l % tx;
   int sp = l / tx;
   int ti, tj;
@@ -480,24 +482,25 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
   const int64_t row_bytes = d * 2;
   const int64_t round_bytes = 2 * WAVES * row_bytes;
   const int64_t buf_bytes = kBufRows * row_bytes;
-  // The workgroup's stages, nb = 2 n buffers of 32 tokens (at least one stage).
-  const int s0 = FUSED ? 0 : int(int64_t(stages) * sp / splits);
-  const int s1 = FUSED ? stages : int(int64_t(stages) * (sp + 1) / splits);
+  // The workgroup's nb buffers of 32 tokens (at least one stage of two).
+  const bool rest = !FUSED && sp == splits;  // the tail's unit
+  const int s0 = FUSED || rest ? 0 : int(int64_t(full) * sp / splits);
+  const int s1 = FUSED ? full + tails : rest ? 1 : int(int64_t(full) * (sp + 1) / splits);
   const int nb = 2 * (s1 - s0);
   // This thread's first rows of blocks ti and tj in buffer 0, and the offset of
-  // buffer q: in X, or in the tail's two buffers (a scalar, so that a step adds
-  // it with the rest of the addresses). Loads past the last buffer repeat it
-  // (into buffers nobody reads again) so that every step waits for the same
-  // count; they are drained after the loop.
-  const char* x0 = reinterpret_cast<const char*>(X) + int64_t(s0) * kRows * row_bytes;
+  // buffer q: in X, or (FUSED) first in the tail's two buffers (a scalar, so that
+  // a step adds it with the rest of the addresses). Loads past the last buffer
+  // repeat it (into buffers nobody reads again) so that every step waits for the
+  // same count; they are drained after the loop.
+  const char* x0 = reinterpret_cast<const char*>(rest ? tail : X) + int64_t(s0) * kRows * row_bytes;
   const char* xa = x0 + row * row_bytes + int64_t(ti) * kBlock * 2;
   const char* xb = x0 + row * row_bytes + int64_t(tj) * kBlock * 2;
-  const int q_tail = 2 * (full - s0);
+  const int q_x = FUSED ? 2 * tails : 0;
   const int64_t to_tail = int64_t(reinterpret_cast<uintptr_t>(tail)) -
-                          int64_t(reinterpret_cast<uintptr_t>(x0)) - q_tail * buf_bytes;
+                          int64_t(reinterpret_cast<uintptr_t>(x0)) + q_x * buf_bytes;
   auto at = [&](int q) {
-    q = q < nb ? q : nb - 1;
-    return q * buf_bytes + (!TAIL || q < q_tail ? int64_t(0) : to_tail);
+    q = (q < nb ? q : nb - 1) - q_x;
+    return q * buf_bytes + (FUSED && q < 0 ? to_tail : int64_t(0));
   };
   f4 acc[C::kMB][C::kNB];
 #pragma unroll
@@ -514,7 +517,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
   // and the barriers keep the compiler from holding 32 addresses, or all loads,
   // in registers that it would have to spill for them.)
   f4* const sums = reinterpret_cast<f4*>(part) + size_t(tile) * (kBlock * kBlock / 4);
-  int cut = FUSED ? 2 * int(int64_t(stages) / splits) : 0;
+  int cut = FUSED ? (tails ? 2 : 2 * int(int64_t(full) / splits)) : 0;
   auto range_end = [&](int q) {
     if (!FUSED || q != cut || q == nb) return;
     f4* Q = sums;
@@ -538,7 +541,7 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
     }
     wait_vmcnt<0>();
     ++sp;
-    cut = 2 * int(int64_t(stages) * (sp + 1) / splits);
+    cut = q_x + 2 * int(int64_t(full) * (sp + 1 - tails) / splits);
   };
 
   issue<C>(xa + at(0), xb + at(0), round_bytes, seg, lds0);
@@ -568,7 +571,8 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  float* P = FUSED ? H : part + size_t(sp) * size_t(d) * size_t(d);
+  const int slot = rest ? 1 : sp + (sp > 0 ? tails : 0);
+  float* P = FUSED ? H : part + size_t(slot) * size_t(d) * size_t(d);
   const int wm = wave / C::WGN, wn = wave % C::WGN;
 #pragma unroll
   for (int mi = 0; mi < C::kMB; ++mi) {
@@ -624,8 +628,7 @@ constexpr int kDirectWaves = 8;  // the layout of k_syrk_direct that the library
 struct DirectPlan {
   int64_t tiles;
   int full_stages, tail_rows;
-  int stages;  // with the tail's
-  int splits;
+  int splits;  // of the whole stages
   bool spread, fused;
   size_t part_elems;
 };
@@ -646,7 +649,7 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   p.tiles = nt * (nt + 1) / 2;
   p.full_stages = int(n_tok / dt::kRows);
   p.tail_rows = int(n_tok % dt::kRows);
-  p.stages = p.full_stages + (p.tail_rows > 0);
+  const int stages = std::max(1, p.full_stages);
   // Eighths of the tiles per XCD, unless they would leave more than a seventh
   // of the chip idle (1, 3, 6 or 10 tiles: d up to 1024).
   p.spread = 7 * 8 * ceil_div(p.tiles, int64_t(8)) > 8 * p.tiles;
@@ -654,16 +657,15 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   // work, 1% a split for starts and ends, at most 4 GiB of partials. This is a
   // lower bound for precision too: each split is a chain of fp32 sums of its
   // own, and a 2048-token sequence at d = 4096 in one chain instead of 11 had a
-  // relative error of 1.5e-7 against 64 bits instead of 3.8e-8. (The last rows that
-  // are no stage do not lengthen a single chain.)
+  // relative error of 1.5e-7 against 64 bits instead of 3.8e-8.
   const int64_t share = ceil_div(p.tiles, int64_t(8));
   const auto affordable = [d](int S) {
     return S == 1 || double(S) * double(d) * double(d) * 4.0 <= double(int64_t(1) << 32);
   };
-  const int max_s = std::min(dt::kMaxSplits, p.stages);
-  int least = p.full_stages > 0 && p.tail_rows > 0 && affordable(2) ? 2 : 1;
+  const int max_s = std::min(dt::kMaxSplits, stages);
+  int least = 1;
   double best_cost = 1e30;
-  for (int S = least; S <= max_s && affordable(S); ++S) {
+  for (int S = 1; S <= max_s && affordable(S); ++S) {
     const double c = double(ceil_div(share * S, int64_t(dt::kCus / 8))) / S * (1.0 + 0.01 * S);
     if (c < best_cost - 1e-12) {
       least = S;
@@ -675,18 +677,21 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   // gained nothing and was off by 1.17e-7 instead of 1.06e-7; d = 1024 in 25
   // instead of 16 took 64 us instead of 72, 1.08e-7 instead of 1.15e-7. The
   // rounds relative to the work (1.6 us a 64-token stage), and for each split
-  // the larger of 1% and the partial sums' bytes, written and read at 5.2 TB/s,
-  // with the kernel that adds them.
+  // the larger of 1% of a full chip's work and the partial sums' bytes, written
+  // and read at 5.2 TB/s. With rounds(S) / S against a price of a split that grows
+  // no faster than the work, a split that pays off pays off for more tokens too.
   const double tri_bytes = double(p.tiles) * dt::kBlock * dt::kBlock * 4.0;
+  const int64_t units = p.spread ? p.tiles : 8 * share;  // a split
+  const double stage_us = double(stages) * 1.6;
+  const double split_us =
+      std::max(0.01 * double(units) / dt::kCus * stage_us, tri_bytes * 2.0 / 5.2e6);
   p.splits = least;
   best_cost = 1e30;
-  const int most = p.stages >= 32 * least ? max_s : least;
+  const int most = stages >= 32 * least ? max_s : least;
   for (int S = least; S <= most && affordable(S); ++S) {
-    const int64_t units = p.spread ? p.tiles * S : 8 * share * S;
-    const double rounds = double(ceil_div(units, int64_t(dt::kCus)));
-    const double work = rounds / S * double(p.stages) * 1.6;
-    const double c = work + std::max(0.01 * S * work, S * tri_bytes * 2.0 / 5.2e6 + 5.0);
-    if (c < best_cost - 1e-12) {
+    const double rounds = double(ceil_div(units * S, int64_t(dt::kCus)));
+    const double c = rounds / S * stage_us + S * split_us + 5.0;
+    if (c < best_cost * (1.0 - 1e-12)) {
       p.splits = S;
       best_cost = c;
     }
@@ -696,14 +701,20 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   // partial sums outweigh the idle CUs: d = 4096 with 512 tokens 83 us instead
   // of 105, 2048 tokens 145 instead of 206.
   constexpr double kRangeUs = 8.0, kEndUs = 13.0;
+  const int tails = p.full_stages > 0 && p.tail_rows > 0;
   const double rounds = double(ceil_div(8 * share, int64_t(dt::kCus)));
   const double fused_cost =
-      rounds * (double(p.stages) * 1.6 + (least - 1) * kRangeUs + kEndUs);
-  p.fused = p.tiles >= 32 && fused_cost < 0.9 * best_cost;
-  // One [d][d] partial per split; the running sums of FUSED (d (d + 256) / 2
-  // entries) fit one of them. The size stays that of the split plan, so that a
-  // workspace for more tokens always holds fewer.
-  p.part_elems = size_t(p.splits) * size_t(d) * size_t(d);
+      rounds * (double(stages + tails) * 1.6 + (least - 1 + tails) * kRangeUs + kEndUs);
+  const double split_cost = best_cost + tails * (tri_bytes * 2.0 / 5.2e6 + 3.0);
+  p.fused = p.tiles >= 32 && fused_cost < 0.9 * split_cost;
+  // One [d][d] partial per split and one for the last rows, which are no stage:
+  // a chain of sums of their own, as a longer one would be less precise (3000
+  // tokens of d = 3072 off by 1.54e-7 instead of 1.51e-7). The running sums of
+  // FUSED (d (d + 256) / 2 entries) fit one partial. The size stays that of the
+  // split plan, which never takes fewer splits for more stages, and from the first
+  // token beyond a stage on has room for last rows: a workspace for more tokens
+  // always holds fewer.
+  p.part_elems = size_t(p.splits + (n_tok > dt::kRows)) * size_t(d) * size_t(d);
   if (p.fused) p.splits = least;
   return p;
 }
@@ -756,18 +767,20 @@ optima_status hessian_accumulate(const void* X, int dtype, int64_t n_tok, int64_
                          int64_t(p.full_stages) * dt::kRows, p.tail_rows, tail);
       OPTIMA_LAUNCH_CHECK();
     }
-    const dim3 grid(direct_grid(p.tiles, p.fused ? 1 : p.splits, p.spread)), threads(64 * kDirectWaves);
+    const uint16_t* rest = p.full_stages > 0 && p.tail_rows > 0 ? tail : nullptr;
+    if (p.full_stages == 0) Xb = tail;  // the padded copy is the only stage
+    const int full = std::max(1, p.full_stages), splits = p.splits + (rest != nullptr);
+    const dim3 threads(64 * kDirectWaves);
     if (p.fused)
-      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, true, true>), grid, threads, 0, s, Xb, tail, d,
-                         p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
-    else if (p.tail_rows == 0)
-      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false, false>), grid, threads, 0, s, Xb, tail, d,
-                         p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, true>), dim3(direct_grid(p.tiles, 1, p.spread)),
+                         threads, 0, s, Xb, rest, d, full, p.splits, int(p.spread), part, H,
+                         accumulate);
     else
-      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false, true>), grid, threads, 0, s, Xb, tail, d,
-                         p.full_stages, p.stages, p.splits, int(p.spread), part, H, accumulate);
+      hipLaunchKernelGGL((k_syrk_direct<kDirectWaves, false>),
+                         dim3(direct_grid(p.tiles, splits, p.spread)), threads, 0, s, Xb, rest, d,
+                         full, p.splits, int(p.spread), part, H, 0);
     OPTIMA_LAUNCH_CHECK();
-    return p.fused ? OPTIMA_OK : reduce_partials(part, p.splits, d, d, H, accumulate, s);
+    return p.fused ? OPTIMA_OK : reduce_partials(part, splits, d, d, H, accumulate, s);
   }
   const HessPlan p = plan(n_tok, d, dtype);
   Carver c(ws);

@@ -166,3 +166,15 @@ def test_binding_structs_mirror_the_header(c_name, py_name):
             assert pt is ctypes.c_void_p, f
         else:
             assert pt is ctype[t], (f, t)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_hessian_workspace_never_shrinks_with_more_tokens(dtype):
+    # A caller sizes it for its longest sequence and then hands over shorter ones,
+    # of whole 64-token stages or not.
+    import paper_2512_13886_amd as L
+    stages = list(range(130)) + [int(130 * 1.045 ** i) for i in range(1, 130)]
+    for d in list(range(256, 16385, 256)) + [14336 + 128, 23040, 100, 1000]:
+        need = [L.optima_hessian_workspace_bytes(n, d, dtype)
+                for k in stages for n in (64 * k, 64 * k + 1, 64 * k + 63)]
+        assert all(a <= b for a, b in zip(need, need[1:])), d
