@@ -499,8 +499,9 @@ __global__ void __launch_bounds__(64 * WAVES) k_syrk_direct(const uint16_t* X,
   const int64_t to_tail = int64_t(reinterpret_cast<uintptr_t>(tail)) -
                           int64_t(reinterpret_cast<uintptr_t>(x0)) + q_x * buf_bytes;
   auto at = [&](int q) {
-    q = (q < nb ? q : nb - 1) - q_x;
-    return q * buf_bytes + (FUSED && q < 0 ? to_tail : int64_t(0));
+    q = q < nb ? q : nb - 1;
+    if (!FUSED) return int64_t(uint32_t(q)) * buf_bytes;
+    return (q - q_x) * buf_bytes + (q < q_x ? to_tail : int64_t(0));
   };
   f4 acc[C::kMB][C::kNB];
 #pragma unroll
