@@ -18,11 +18,12 @@
 // of 128 stages): 80 us plus 12 us of fused update, against 111 us for the
 // 4-wave tile split in two.
 //
-// The small products of split planes have accumulators of their own: the long
-// ranges that this tile makes worth while would else round their sum three times
-// a stage. d = 512, 606 columns, 8 CG iterations in one range: W is off by 2.4e-7
-// of fp64, 3.2e-7 with one accumulator; 64 iterations of d = 4096 with 1024
-// columns 5.2e-7 instead of 5.7e-7. It costs no time (0.2 %, as two runs differ).
+// A tile that takes a contraction in fewer workgroups than the sum has ranges
+// (SumRanges) ends each range in registers: its sum joins a running one by plain
+// fp32 additions, in the order in which k_split_epilogue adds the ranges of
+// several workgroups, so that W is the same bit for bit. An MFMA chain of the
+// whole contraction is longer and less precise: d = 512, 606 columns, 8 CG
+// iterations, W off by 3.2e-7 of fp64 in one chain, 2.0e-7 in 16.
 #pragma once
 
 #include "gemm256.h"
@@ -44,8 +45,31 @@ struct OperandsR128 {
 };
 
 struct AccR128 {
-  f4 q[4][2];      // [16-row block][16-column block]
-  f4 cross[4][2];  // the hi lo and lo hi products of split planes, until the loop ends
+  f4 q[4][2];    // [16-row block][16-column block]
+  f4 sum[4][2];  // of the ranges that have ended
+};
+// Where the ranges of a sum end, as a workgroup meets them: `count` ranges of
+// `stages` stages, range r ending before stage stages (r + 1) / count.
+struct SumRanges {
+  int until;        // stages to the end of the present range
+  int len, rem, count, part;
+
+  // From stage s0 on. (32 bits: stages count stays below 2^31.)
+  __device__ inline SumRanges(int stages, int count_, int s0)
+      : len(stages / count_), rem(stages % count_), count(count_) {
+    int r = s0 * count / stages;
+    while (stages * r / count <= s0) ++r;
+    until = stages * r / count - s0;
+    part = stages * r % count;
+  }
+  // A stage has been added; whether its range ends.
+  __device__ inline bool step() {
+    if (--until > 0) return false;
+    part += rem;
+    until = len + (part >= count);
+    part -= part >= count ? count : 0;
+    return true;
+  }
 };
 __device__ inline int r128_row(int mi, int e) { return t256_row(0, mi, e); }
 __device__ inline int r128_col(int ni) { return t256_col(0, ni); }
@@ -53,8 +77,8 @@ __device__ inline int r128_col(int ni) { return t256_col(0, ni); }
 // LEFT: stages left, this one included (4: or more); the last three fetch
 // nothing, and wait for what is in flight.
 template <typename T, int LEFT>
-__device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, int s, char* cur,
-                                  char* nxt) {
+__device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, SumRanges& ranges, int s,
+                                  char* cur, char* nxt) {
   constexpr int kStage = 2 * Ring128::kLoads;
   const int wm = threadIdx.x >> 8, wn = (threadIdx.x >> 6) & 3;
   bf16x8 fa[4][2], fb[2][2];
@@ -66,28 +90,35 @@ __device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, int s, 
     t256::fetch(src.b, off, nxt + 128 * Ring128::kSRB);
   }
   t256::end_memory<LEFT >= 4 ? 2 * kStage : LEFT == 3 ? kStage : LEFT == 2 ? 0 : -1>();
-  t256::quadrant<T>(acc.q, acc.cross, fa, fb);
+  t256::quadrant<T>(acc.q, fa, fb);
+  if (LEFT > 1 && ranges.step()) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      acc.sum[i >> 1][i & 1] += acc.q[i >> 1][i & 1];
+      acc.q[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
   t256::barrier();
 }
 
 // The last three stages, from buffers c0, c1, c2.
 template <typename T>
-__device__ inline void r128_last3(AccR128& acc, const OperandsR128& src, char* c0, char* c1,
-                                  char* c2) {
-  r128_stage<T, 3>(acc, src, 0, c0, nullptr);
-  r128_stage<T, 2>(acc, src, 0, c1, nullptr);
-  r128_stage<T, 1>(acc, src, 0, c2, nullptr);
+__device__ inline void r128_last3(AccR128& acc, const OperandsR128& src, SumRanges& ranges, char* c0,
+                                  char* c1, char* c2) {
+  r128_stage<T, 3>(acc, src, ranges, 0, c0, nullptr);
+  r128_stage<T, 2>(acc, src, ranges, 0, c1, nullptr);
+  r128_stage<T, 1>(acc, src, ranges, 0, c2, nullptr);
 }
 
-// n stages (n >= 0). b0..b3 are distinct __shared__ arrays of
+// n stages (n >= 0), whose sum's ranges end as `ranges` has it. b0..b3 are distinct __shared__ arrays of
 // Ring128::kBufBytes. `aside` runs once the first fetches are out.
 template <typename T, typename Aside>
-__device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, int n, char* b0,
-                                     char* b1, char* b2, char* b3, Aside aside) {
+__device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumRanges ranges, int n,
+                                     char* b0, char* b1, char* b2, char* b3, Aside aside) {
   constexpr int kStage = 2 * Ring128::kLoads;
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    acc.q[i >> 1][i & 1] = acc.cross[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+    acc.q[i >> 1][i & 1] = acc.sum[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
   if (n <= 0) return;
   auto fetch = [&](int s, char* buf) {
     t256::fetch(src.a, int64_t(s) * Ring128::kSRB, buf);
@@ -105,10 +136,10 @@ __device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, int 
     }
     if (behind) t256::barrier();
     if (n == 2) {
-      r128_stage<T, 2>(acc, src, 0, b0, nullptr);
-      r128_stage<T, 1>(acc, src, 0, b1, nullptr);
+      r128_stage<T, 2>(acc, src, ranges, 0, b0, nullptr);
+      r128_stage<T, 1>(acc, src, ranges, 0, b1, nullptr);
     } else {
-      r128_stage<T, 1>(acc, src, 0, b0, nullptr);
+      r128_stage<T, 1>(acc, src, ranges, 0, b0, nullptr);
     }
   } else {
     fetch(1, b1);
@@ -118,33 +149,31 @@ __device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, int 
     if (behind) t256::barrier();
     int s = 0;
     for (; s + 7 <= n; s += 4) {
-      r128_stage<T, 4>(acc, src, s, b0, b3);
-      r128_stage<T, 4>(acc, src, s + 1, b1, b0);
-      r128_stage<T, 4>(acc, src, s + 2, b2, b1);
-      r128_stage<T, 4>(acc, src, s + 3, b3, b2);
+      r128_stage<T, 4>(acc, src, ranges, s, b0, b3);
+      r128_stage<T, 4>(acc, src, ranges, s + 1, b1, b0);
+      r128_stage<T, 4>(acc, src, ranges, s + 2, b2, b1);
+      r128_stage<T, 4>(acc, src, ranges, s + 3, b3, b2);
     }
     // 3 to 6 stages are left.
     if (n - s == 3) {
-      r128_last3<T>(acc, src, b0, b1, b2);
+      r128_last3<T>(acc, src, ranges, b0, b1, b2);
     } else if (n - s == 4) {
-      r128_stage<T, 4>(acc, src, s, b0, b3);
-      r128_last3<T>(acc, src, b1, b2, b3);
+      r128_stage<T, 4>(acc, src, ranges, s, b0, b3);
+      r128_last3<T>(acc, src, ranges, b1, b2, b3);
     } else if (n - s == 5) {
-      r128_stage<T, 4>(acc, src, s, b0, b3);
-      r128_stage<T, 4>(acc, src, s + 1, b1, b0);
-      r128_last3<T>(acc, src, b2, b3, b0);
+      r128_stage<T, 4>(acc, src, ranges, s, b0, b3);
+      r128_stage<T, 4>(acc, src, ranges, s + 1, b1, b0);
+      r128_last3<T>(acc, src, ranges, b2, b3, b0);
     } else {
-      r128_stage<T, 4>(acc, src, s, b0, b3);
-      r128_stage<T, 4>(acc, src, s + 1, b1, b0);
-      r128_stage<T, 4>(acc, src, s + 2, b2, b1);
-      r128_last3<T>(acc, src, b3, b0, b1);
+      r128_stage<T, 4>(acc, src, ranges, s, b0, b3);
+      r128_stage<T, 4>(acc, src, ranges, s + 1, b1, b0);
+      r128_stage<T, 4>(acc, src, ranges, s + 2, b2, b1);
+      r128_last3<T>(acc, src, ranges, b3, b0, b1);
     }
   }
   if (!behind) t256::barrier();
-  if constexpr (std::is_same<T, Bf16x3Tag>::value) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc.q[i >> 1][i & 1] += acc.cross[i >> 1][i & 1];
-  }
+  for (int i = 0; i < 8; ++i) acc.q[i >> 1][i & 1] = acc.sum[i >> 1][i & 1] + acc.q[i >> 1][i & 1];
   // No load may still be writing LDS when the workgroup moves on.
   wait_vmcnt<0>();
   __syncthreads();

@@ -631,10 +631,11 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
 }
 
 // The dense products on the 128 x 128 tiles of gemm128.h, one workgroup per CU.
-// Split ranges, partial sums and the epilogue work as in k_product.
+// Split ranges, partial sums and the epilogue work as in k_product; `ranges` (at
+// least `splits`) are those of the sum.
 template <int MODE>
 __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs p, int splits,
-                                                                    float* part) {
+                                                                    int ranges, float* part) {
   using Cfg = Ring128;
   __shared__ __attribute__((aligned(1024))) char b0[Cfg::kBufBytes];
   __shared__ __attribute__((aligned(1024))) char b1[Cfg::kBufBytes];
@@ -665,7 +666,7 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
                t256_seg_bytes(i);
   }
   AccR128 acc;
-  r128_mainloop<Bf16x3Tag>(acc, src, s1 - s0, b0, b1, b2, b3,
+  r128_mainloop<Bf16x3Tag>(acc, src, SumRanges(stages, ranges, s0), s1 - s0, b0, b1, b2, b3,
                            [&] {
     if (splits == 1) load_tile_rows<MODE>(p, m0, info);
   });
@@ -2431,7 +2432,45 @@ int choose_splits(int tiles, int stages, int tiles_m, int dp, size_t part_cap) {
   return best;
 }
 
-// Tile and number of K ranges of a dense bf16x3 product.
+// The same for a tile that fills a CU with one workgroup: the fewest CU rounds
+// per unit of work, charging 5% per extra range.
+int choose_splits_one_per_cu(int tiles, int stages, int rows_pad, int dp, size_t part_cap) {
+  const int n_cu = device_cu_count();
+  auto cost = [&](int S) {
+    return double(ceil_div(int64_t(tiles) * S, n_cu)) / S * (1.0 + 0.05 * (S - 1));
+  };
+  int best = 1;
+  double best_cost = cost(1);
+  for (int S = 2; S <= kMaxSplits && S <= stages; ++S) {
+    if (int64_t(tiles) * S > kMaxSplitTiles) break;
+    if (size_t(S) * size_t(rows_pad) * size_t(dp) > part_cap) break;
+    const double c = cost(S);
+    if (c < best_cost - 1e-9) {
+      best = S;
+      best_cost = c;
+    }
+  }
+  return best;
+}
+
+// Number of ranges of the contraction that the sums of a dense bf16x3 product
+// are made of: each one chain of MFMA sums, the ranges added in their order. It
+// depends on the shape alone, so that the choice of a tile and of the number of
+// its workgroups (plan_dense) does not change results, and is what bounds their
+// error: W of 8 CG iterations over 606 columns of d = 512 is off by 2.0e-7 of
+// fp64 with these 16 ranges, 3.2e-7 with one. The rules are those by which tiles
+// of 128 x 128, two a CU, or of 256 x 128, one a CU, would be split to fill the
+// chip.
+int dense_ranges(int64_t n_rows, int64_t dp, size_t part_cap) {
+  const bool wide = (dp >= 8192 && n_rows >= 256) || (dp >= 4096 && n_rows >= 4096);
+  const int bm = wide ? 2 * kTile : kTile;
+  const int tiles_m = int(ceil_div(n_rows, bm)), tiles = tiles_m * int(dp / kTile);
+  const int stages = int(dp / 32);
+  return wide ? choose_splits_one_per_cu(tiles, stages, tiles_m * bm, int(dp), part_cap)
+              : choose_splits(tiles, stages, tiles_m, int(dp), part_cap);
+}
+
+// Tile and number of workgroups along K of a dense bf16x3 product.
 enum class DenseTile { kSmall, kRing128, k256 };  // k_product, k_product_ring, k_product256
 struct DensePlan {
   DenseTile tile;
@@ -2442,51 +2481,57 @@ struct DensePlan {
 int epilogue_bytes(int mode) { return mode == kFused ? 33 : mode == kStore ? 16 : mode == kPlain ? 4 : 8; }
 
 // The cheapest by a model of the launch in microseconds: rounds of workgroups
-// over the chip, each its stages and a fixed part (start, first fetches,
-// staging), then the outputs' bytes and, for S ranges, the partial sums' and a
-// second launch. A stage takes less while part of the chip is idle (the loads
-// and the clock are shared), down to least_us. The constants are fits to 16
-// iterations of solves with d from 512 to 14336 and 256 to 14336 columns; the
-// model is within 8 % of most of them. us an iteration, and what each tile would take (k_product,
-// k_product_ring, k_product256; splits chosen for each):
-//   d = 14336, 4096 columns   4350  4090  3390
-//   d = 4096,  4096 columns    424   415   332
-//   d = 4096,  1024 columns    111    95   103
-//   d = 4096,   256 columns     39    36    48
-//   d = 2048,  4096 columns    115   119   124
-//   d = 1024,  4096 columns     53    42    62
+// over the chip, each its stages and, after the first, a fixed part; the launch's
+// own; the outputs' bytes; for S workgroups along K the partial sums', the second
+// launch and a little each; and in the ring the ends of ranges that it takes in
+// registers. A stage takes less while part of the chip is idle (the loads and the
+// clock are shared), down to least_us. The constants are a fit to every tile and S
+// for 245 shapes, d from 384 to 14336 and 16 to 14336 columns: 7 % off, the choice
+// 0.4 % slower than the best one in the mean and 5 % at most. us an iteration by
+// k_product, k_product_ring and k_product256, each with its best S:
+//   d = 512,  256 columns     13.6  13.0
+//   d = 1024, 512 columns     24.1  18.6
+//   d = 1024, 4096 columns    55    44    62
+//   d = 2048, 1024 columns    44    41    48
+//   d = 4096, 1024 columns   113    98   105
+//   d = 4096, 3072 columns   316   313   273
 // k_product's two workgroups a CU make its rounds twice as wide and hide part
 // of its epilogue; the ring keeps a CU's loads busy with one workgroup, and the
 // 256 x 256 tile loads half as much for the same outputs.
-DensePlan plan_dense(int64_t n_rows, int64_t dp, int out_bytes, size_t part_cap) {
+DensePlan plan_dense(int64_t n_rows, int64_t dp, int ranges, int out_bytes, size_t part_cap) {
   struct Tile {
     DenseTile id;
     int side, per_cu;
-    double stage_us, least_us, fixed_us;
+    double stage_us, least_us, base_us, round_us;
   };
-  static constexpr Tile kTiles[] = {{DenseTile::kSmall, 128, 2, 1.27, 1.0, 8.0},
-                                    {DenseTile::kRing128, 128, 1, 0.58, 0.45, 8.0},
-                                    {DenseTile::k256, 256, 1, 2.05, 1.45, 6.0}};
-  constexpr double kBytesPerUs = 8.5e6, kLaunchUs = 5.0;
+  static constexpr Tile kTiles[] = {{DenseTile::kSmall, 128, 2, 1.11, 0.81, 5.5, 0.0},
+                                    {DenseTile::kRing128, 128, 1, 0.53, 0.48, 5.6, 1.2},
+                                    {DenseTile::k256, 256, 1, 1.61, 1.37, 6.7, 2.4}};
+  constexpr double kOutBytesPerUs = 6.2e6, kPartBytesPerUs = 7.0e6;
+  constexpr double kLaunchUs = 1.5, kSplitUs = 0.3, kEndUs = 0.37;
   const int n_cu = device_cu_count();
   const int64_t stages = dp / 32;
   const double outputs = double(n_rows) * double(dp);
   DensePlan best{DenseTile::kSmall, 1};
   double best_us = 1e30;
   for (const Tile& t : kTiles) {
+    const bool ring = t.id == DenseTile::kRing128;
     const int64_t tiles_m = ceil_div(n_rows, t.side);
     const int64_t tiles = tiles_m * ceil_div(dp, t.side);
-    for (int S = 1; S <= kMaxSplits && S <= stages; ++S) {
+    // The ring ends ranges in registers; the others' workgroups are one each.
+    for (int S = ring ? 1 : ranges; S <= kMaxSplits && S <= stages; ++S) {
       if (S > 1 && (tiles * S > kMaxSplitTiles ||
                     size_t(S) * size_t(tiles_m * t.side) * size_t(dp) > part_cap))
         break;
       const int64_t slots = int64_t(t.per_cu) * n_cu, full = tiles * S / slots;
       const double part = double(tiles * S % slots) / double(slots);
+      const double rounds = double(full + (part > 0.0));
       const double per_stage =
           full * t.stage_us + (part > 0.0 ? std::max(t.least_us, part * t.stage_us) : 0.0);
-      double us = double(ceil_div(stages, S)) * per_stage +
-                  double(full + (part > 0.0)) * t.fixed_us + outputs * out_bytes / kBytesPerUs;
-      if (S > 1) us += outputs * 8.0 * S / kBytesPerUs + kLaunchUs;
+      double us = t.base_us + double(ceil_div(stages, S)) * per_stage + (rounds - 1.0) * t.round_us +
+                  outputs * out_bytes / kOutBytesPerUs;
+      if (ring && S < ranges) us += rounds * double(ceil_div(ranges, S) - 1) * kEndUs;
+      if (S > 1) us += outputs * 8.0 * S / kPartBytesPerUs + kLaunchUs + kSplitUs * S;
       if (us < best_us) {
         best_us = us;
         best = DensePlan{t.id, S};
@@ -2638,7 +2683,8 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
     }
   }
   if constexpr (PREC == kPrecBf16x3) {
-    const DensePlan plan = plan_dense(p.n_rows, p.dp, epilogue_bytes(MODE), l.part_elems);
+    const int ranges = dense_ranges(p.n_rows, p.dp, l.part_elems);
+    const DensePlan plan = plan_dense(p.n_rows, p.dp, ranges, epilogue_bytes(MODE), l.part_elems);
     const int bm = plan.tile == DenseTile::k256 ? Tile256::BM : kTile;
     const int tiles_m = int(ceil_div(p.n_rows, bm)), tiles_n = int(ceil_div(p.dp, bm));
     const dim3 grid(unsigned(tiles_m * tiles_n * plan.splits));
@@ -2647,7 +2693,7 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
                          l.part);
     else if (plan.tile == DenseTile::kRing128)
       hipLaunchKernelGGL((k_product_ring<MODE>), grid, dim3(Ring128::kThreads), 0, s, p,
-                         plan.splits, l.part);
+                         plan.splits, std::max(plan.splits, ranges), l.part);
     else
       hipLaunchKernelGGL((k_product<MODE, PREC>), grid, dim3(ProductTile::kThreads), 0, s, p,
                          plan.splits, l.part);

@@ -48,6 +48,27 @@ def test_products_match_the_oracle(L, d, n):
     np.testing.assert_allclose(st["f_initial"][cols], ref.f_initial, rtol=1e-5, atol=1e-12)
 
 
+# The sums' ranges are a matter of the shape, not of the tile: the same columns in
+# two batches whose sums have as many ranges, which the 128 x 128 ring ends in
+# registers in one batch and workgroups of the 256 x 256 tile take one each in the
+# other (2 ranges of 32 stages, 3 of 18 or 19).
+@pytest.mark.parametrize("d, n, m", [(2048, 3072, 2048), (1792, 6144, 3072)])
+@pytest.mark.parametrize("method", ["rapdhg", "cg"])
+def test_tiles_give_the_same_bits(L, d, n, m, method):
+    g = torch.Generator(device=dev()).manual_seed(d)
+    A = torch.randn(2 * d, d, generator=g, device=dev())
+    H = A.t() @ A / d + torch.eye(d, device=dev())
+    H = torch.tril(H) + torch.tril(H, -1).t()
+    W0 = 0.02 * torch.randn(n, d, generator=g, device=dev())
+    M = (torch.rand(n, d, generator=g, device=dev()) < 0.5).to(torch.uint8)
+    opts = L.SolverOpts.default(method=L.METHOD_CG if method == "cg" else L.METHOD_RAPDHG,
+                                max_iters=5, fixed_iters=1)
+    lam = torch.full((1,), 8.0, device=dev())
+    every, _, _ = gpu_solve(L, H, lam, W0, M, opts)
+    some, _, _ = gpu_solve(L, H, lam, W0[:m].contiguous(), M[:m].contiguous(), opts)
+    assert torch.equal(every[:m].view(torch.int32), some.view(torch.int32))
+
+
 # (d, columns): the 256 x 128 tile of the 2:4 products in one range of 24 stages
 # and in 2 to 11 ranges of 1 to 8 stages, odd counts among them, with one row and
 # one full tile in the last row tile, and a padded d.
