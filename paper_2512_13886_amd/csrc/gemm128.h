@@ -49,18 +49,26 @@ struct AccR128 {
   f4 sum[4][2];  // of the ranges that have ended
 };
 // Where the ranges of a sum end, as a workgroup meets them: `count` ranges of
-// `stages` stages, range r ending before stage stages (r + 1) / count.
+// `stages` stages, range r ending before stage stages (r + 1) / count; the
+// workgroup starts at stage s0. count 0: it has one range.
+struct SumShape {
+  int stages, count, s0;
+};
 struct SumRanges {
-  int until;        // stages to the end of the present range
+  int until;  // stages to the end of the present range
   int len, rem, count, part;
 
-  // From stage s0 on. (32 bits: stages count stays below 2^31.)
-  __device__ inline SumRanges(int stages, int count_, int s0)
-      : len(stages / count_), rem(stages % count_), count(count_) {
-    int r = s0 * count / stages;
-    while (stages * r / count <= s0) ++r;
-    until = stages * r / count - s0;
-    part = stages * r % count;
+  // Divisions, for after the first loads. (32 bits: stages count stays below 2^31.)
+  __device__ inline explicit SumRanges(const SumShape& s)
+      : until(0x7fffffff), len(0), rem(0), count(s.count), part(0) {
+    if (!count) return;
+    const unsigned n = s.stages, c = count;
+    unsigned r = s.s0 * c / n;
+    while (n * r / c <= unsigned(s.s0)) ++r;
+    len = n / c;
+    rem = n % c;
+    until = n * r / c - s.s0;
+    part = n * r % c;
   }
   // A stage has been added; whether its range ends.
   __device__ inline bool step() {
@@ -110,10 +118,10 @@ __device__ inline void r128_last3(AccR128& acc, const OperandsR128& src, SumRang
   r128_stage<T, 1>(acc, src, ranges, 0, c2, nullptr);
 }
 
-// n stages (n >= 0), whose sum's ranges end as `ranges` has it. b0..b3 are distinct __shared__ arrays of
+// n stages (n >= 0) of a sum with ranges as `shape` has them. b0..b3 are distinct __shared__ arrays of
 // Ring128::kBufBytes. `aside` runs once the first fetches are out.
 template <typename T, typename Aside>
-__device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumRanges ranges, int n,
+__device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumShape shape, int n,
                                      char* b0, char* b1, char* b2, char* b3, Aside aside) {
   constexpr int kStage = 2 * Ring128::kLoads;
 #pragma unroll
@@ -128,6 +136,7 @@ __device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumR
   fetch(0, b0);
   if (n < 3) {
     aside();
+    SumRanges ranges(shape);
     if (n == 2) {
       fetch(1, b1);
       t256::end_memory<kStage>();
@@ -145,6 +154,7 @@ __device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumR
     fetch(1, b1);
     fetch(2, b2);
     aside();
+    SumRanges ranges(shape);
     t256::end_memory<2 * kStage>();
     if (behind) t256::barrier();
     int s = 0;

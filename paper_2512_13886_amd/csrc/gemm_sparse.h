@@ -41,10 +41,11 @@
 // iteration, then this loop): d = 8192, 4096 columns 947, 828; d = 14336, 1024
 // columns 781, 654; d = 4096, 4096 columns 253, 231 (596 TFLOP/s counted dense).
 // Launches with few stages per workgroup gain nothing or lose up to 1 us (d =
-// 2048, 128 columns: 18.6, 19.4). All eight waves in step: 5 to 10 % slower.
+// 2048, 128 columns: 18.6, 19.4; gemm_sparse_short). All eight waves in step: 5 to
+// 10 % slower.
 #pragma once
 
-#include "gemm256.h"
+#include "gemm128.h"
 
 namespace optima {
 
@@ -86,8 +87,10 @@ __device__ inline bf16x16 sp_b_pair(bf16x8 k0, bf16x8 k1) {
   return __builtin_shufflevector(k0, k1, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
 }
 
+template <bool RANGES>
 struct SpAcc {
-  f4 q[2][4][2];  // [A half][16-row block][16-column block]
+  f4 q[2][4][2];                  // [A half][16-row block][16-column block]
+  f4 sum[RANGES ? 2 : 0][4][2];  // of the ranges that have ended
 };
 
 namespace sp {
@@ -140,10 +143,34 @@ __device__ inline void half(f4 (&c)[4][2], const bf16x8 (&a)[4][2], const bf16x1
   }
 }
 
+// After a stage: if its range ends, the range's sum joins those before it.
+template <bool RANGES>
+__device__ inline void end_range(SpAcc<RANGES>& acc, SumRanges& ranges) {
+  if (!ranges.step()) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    f4& q = acc.q[i >> 3][(i >> 1) & 3][i & 1];
+    acc.sum[i >> 3][(i >> 1) & 3][i & 1] += q;
+    q = f4{0.f, 0.f, 0.f, 0.f};
+  }
+}
+
+template <bool RANGES>
+__device__ inline void add_ranges(SpAcc<RANGES>& acc) {
+  if constexpr (RANGES)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      f4& q = acc.q[i >> 3][(i >> 1) & 3][i & 1];
+      q = acc.sum[i >> 3][(i >> 1) & 3][i & 1] + q;
+    }
+}
+
 // One stage from buffers a0, a1, b, ix; na1 is the other A1 buffer, s1 and s2
 // the next two stages.
-__device__ inline void stage(SpAcc& acc, const SpOperands& src, int64_t s1, int64_t s2, char* a0,
-                             char* a1, char* b, char* ix, char* na1) {
+template <bool RANGES>
+__device__ inline void stage(SpAcc<RANGES>& acc, const SpOperands& src, SumRanges& ranges,
+                             int64_t s1, int64_t s2, char* a0, char* a1, char* b, char* ix,
+                             char* na1) {
   constexpr int kLeave = SpTile::kInFlight;
   const int wm = threadIdx.x >> 8;
   bf16x8 fa[4][2];
@@ -162,6 +189,7 @@ __device__ inline void stage(SpAcc& acc, const SpOperands& src, int64_t s1, int6
   fetch_b(src, s2, b, ix);
   t256::end_memory<kLeave>();
   half(acc.q[1], fa, fb, x1);
+  if constexpr (RANGES) end_range(acc, ranges);
   t256::barrier();
 }
 
@@ -172,12 +200,16 @@ __device__ inline void stage(SpAcc& acc, const SpOperands& src, int64_t s1, int6
 // last stage repeat it, into buffers that nobody reads again. (Peeling the last
 // two stages without them cost the loop 2 % and gained nothing on short
 // contractions.) `aside` runs once the first fetches are out.
-template <typename Aside>
-__device__ inline void gemm_sparse_mainloop(SpAcc& acc, const SpOperands& src, int n, char* a00,
+template <bool RANGES, typename Aside>
+__device__ inline void gemm_sparse_mainloop(SpAcc<RANGES>& acc, const SpOperands& src,
+                                            SumShape shape, int n, char* a00,
                                             char* a01, char* b0, char* ix0, char* a10, char* a11,
                                             char* b1, char* ix1, Aside aside) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc.q[i >> 3][(i >> 1) & 3][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 16; ++i) {
+    acc.q[i >> 3][(i >> 1) & 3][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (RANGES) acc.sum[i >> 3][(i >> 1) & 3][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+  }
   if (n <= 0) return;
   auto at = [n](int s) { return int64_t(s < n ? s : n - 1); };
   t256::fetch(src.a[0], 0, a00);
@@ -186,18 +218,81 @@ __device__ inline void gemm_sparse_mainloop(SpAcc& acc, const SpOperands& src, i
   t256::fetch(src.a[0], at(1) * SpTile::kARowBytes, a10);
   sp::fetch_b(src, at(1), b1, ix1);
   aside();
+  SumRanges ranges(shape);
   t256::end_memory<SpTile::kInFlight>();
   const bool behind = threadIdx.x >= 256;  // waves 4-7
   if (behind) t256::barrier();
   int s = 0;
   for (; s + 1 < n; s += 2) {
-    sp::stage(acc, src, at(s + 1), at(s + 2), a00, a01, b0, ix0, a11);
-    sp::stage(acc, src, at(s + 2), at(s + 3), a10, a11, b1, ix1, a01);
+    sp::stage(acc, src, ranges, at(s + 1), at(s + 2), a00, a01, b0, ix0, a11);
+    sp::stage(acc, src, ranges, at(s + 2), at(s + 3), a10, a11, b1, ix1, a01);
   }
-  if (s < n) sp::stage(acc, src, at(s + 1), at(s + 2), a00, a01, b0, ix0, a11);
+  if (s < n) sp::stage(acc, src, ranges, at(s + 1), at(s + 2), a00, a01, b0, ix0, a11);
   if (!behind) t256::barrier();
+  sp::add_ranges(acc);
   // No load may still be writing LDS when the workgroup moves on.
   wait_vmcnt<0>();
+  __syncthreads();
+}
+
+// The same with all eight waves in step, for few stages: whole stages with one
+// barrier each, the first two fetched at once, none fetched twice. Without ranges
+// both halves of A have registers, so that a stage's LDS reads all go out before
+// its first MFMA. d = 512 with 64 columns (a stage a workgroup) 11.0 us an
+// iteration, 11.5 by the loop above.
+template <bool RANGES, typename Aside>
+__device__ inline void gemm_sparse_short(SpAcc<RANGES>& acc, const SpOperands& src, SumShape shape,
+                                         int n, char* a00, char* a01, char* b0, char* ix0,
+                                         char* a10, char* a11, char* b1, char* ix1, Aside aside) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    acc.q[i >> 3][(i >> 1) & 3][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (RANGES) acc.sum[i >> 3][(i >> 1) & 3][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  if (n <= 0) return;
+  constexpr int kStage = SpTile::kInFlight;  // a wave's loads
+  SumRanges ranges(SumShape{0, 0, 0});
+  const int wm = threadIdx.x >> 8;
+  auto fetch = [&](int s, char* a0, char* a1, char* b, char* ix) {
+    t256::fetch(src.a[0], int64_t(s) * SpTile::kARowBytes, a0);
+    sp::fetch_b(src, s, b, ix);
+    t256::fetch(src.a[1], int64_t(s) * SpTile::kARowBytes, a1);
+  };
+  // Waits for stage s; every wave has then read the stage before it.
+  auto landed = [&](int s) {
+    if (s == 0 && n > 1)
+      t256::end_memory<kStage>();
+    else
+      t256::end_memory<0>();
+  };
+  auto compute = [&](const char* a0, const char* a1, const char* b, const char* ix) {
+    bf16x8 fa[4][2], fa1[4][2];
+    bf16x16 fb[2][2];
+    int x0[4], x1[4];
+    t256::read<4>(fa, a0, wm * 64);
+    sp::read_b(fb, b);
+    sp::read_idx(x0, ix, wm * 64);
+    sp::read_idx(x1, ix, 128 + wm * 64);
+    if (!RANGES) t256::read<4>(fa1, a1, wm * 64);  // registers for both halves
+    sp::half(acc.q[0], fa, fb, x0);
+    if (RANGES) t256::read<4>(fa1, a1, wm * 64);
+    sp::half(acc.q[1], fa1, fb, x1);
+    if constexpr (RANGES) sp::end_range(acc, ranges);
+  };
+  fetch(0, a00, a01, b0, ix0);
+  if (n > 1) fetch(1, a10, a11, b1, ix1);
+  aside();
+  if (RANGES) ranges = SumRanges(shape);
+  for (int s = 0; s < n; s += 2) {
+    landed(s);
+    if (s > 0 && s + 1 < n) fetch(s + 1, a10, a11, b1, ix1);
+    compute(a00, a01, b0, ix0);
+    if (s + 1 == n) break;
+    landed(s + 1);
+    if (s + 2 < n) fetch(s + 2, a00, a01, b0, ix0);
+    compute(a10, a11, b1, ix1);
+  }
+  sp::add_ranges(acc);
   __syncthreads();
 }
 

@@ -505,8 +505,8 @@ __global__ void __launch_bounds__(ProductTile::kThreads) k_product(ProductArgs p
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * kTile, n0 = tn * kTile;
   const int stages = p.dp * 4 / Cfg::SRB;
-  const int s0 = int(int64_t(stages) * sp / splits);
-  const int s1 = int(int64_t(stages) * (sp + 1) / splits);
+  const int s0 = int(unsigned(stages * sp) / unsigned(splits));
+  const int s1 = int(unsigned(stages * (sp + 1)) / unsigned(splits));
 
   Operands<Cfg> src;
   const size_t k_off = size_t(s0) * Cfg::SRB;
@@ -578,8 +578,8 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   const int stages = p.dp * 4 / Cfg::kSRB;
-  const int s0 = int(int64_t(stages) * sp / splits);
-  const int s1 = int(int64_t(stages) * (sp + 1) / splits);
+  const int s0 = int(unsigned(stages * sp) / unsigned(splits));
+  const int s1 = int(unsigned(stages * (sp + 1)) / unsigned(splits));
 
   Operands256 src;
   const size_t k_off = size_t(s0) * Cfg::kSRB;
@@ -631,8 +631,8 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
 }
 
 // The dense products on the 128 x 128 tiles of gemm128.h, one workgroup per CU.
-// Split ranges, partial sums and the epilogue work as in k_product; `ranges` (at
-// least `splits`) are those of the sum.
+// Split ranges, partial sums and the epilogue work as in k_product; `ranges` (0:
+// `splits`) are those of the sum.
 template <int MODE>
 __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs p, int splits,
                                                                     int ranges, float* part) {
@@ -651,8 +651,8 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * Cfg::BM, n0 = tn * Cfg::BN;
   const int stages = p.dp * 4 / Cfg::kSRB;
-  const int s0 = int(int64_t(stages) * sp / splits);
-  const int s1 = int(int64_t(stages) * (sp + 1) / splits);
+  const int s0 = int(unsigned(stages * sp) / unsigned(splits));
+  const int s1 = int(unsigned(stages * (sp + 1)) / unsigned(splits));
 
   OperandsR128 src;
   const size_t k_off = size_t(s0) * Cfg::kSRB;
@@ -666,7 +666,7 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
                t256_seg_bytes(i);
   }
   AccR128 acc;
-  r128_mainloop<Bf16x3Tag>(acc, src, SumRanges(stages, ranges, s0), s1 - s0, b0, b1, b2, b3,
+  r128_mainloop<Bf16x3Tag>(acc, src, SumShape{stages, ranges, s0}, s1 - s0, b0, b1, b2, b3,
                            [&] {
     if (splits == 1) load_tile_rows<MODE>(p, m0, info);
   });
@@ -725,13 +725,17 @@ __device__ inline int coop_stamp_block() {
 }
 #endif
 
+// The loops of gemm_sparse.h, for many stages and for few, each also with ranges of
+// the sum that end in registers.
+enum class SparseLoop { kLong, kRanges, kShort, kShortRanges };
+
 // The iteration products with x 2:4-compressed (kPrecSparse): 256 x 128
 // tiles of 8 waves on the sparse MFMA, one workgroup per CU (the loop of
 // gemm_sparse.h). Split ranges, partial sums and the epilogue work as in
 // k_product, with partial rows padded to the 256-row tile.
-template <int MODE>
+template <int MODE, SparseLoop LOOP>
 __global__ void __launch_bounds__(SpTile::kThreads) k_product_sparse(ProductArgs p, int splits,
-                                                                     float* part) {
+                                                                     int ranges, float* part) {
   __shared__ __attribute__((aligned(1024))) char a00[SpTile::kABytes];
   __shared__ __attribute__((aligned(1024))) char a01[SpTile::kABytes];
   __shared__ __attribute__((aligned(1024))) char a10[SpTile::kABytes];
@@ -750,8 +754,8 @@ __global__ void __launch_bounds__(SpTile::kThreads) k_product_sparse(ProductArgs
   tile_of_block(lin, n_tiles, tiles_m, tiles_n, &tm, &tn);
   const int m0 = tm * SpTile::BM, n0 = tn * SpTile::BN;
   const int stages = p.dp / SpTile::kKPerStage;
-  const int s0 = int(int64_t(stages) * sp / splits);
-  const int s1 = int(int64_t(stages) * (sp + 1) / splits);
+  const int s0 = int(unsigned(stages * sp) / unsigned(splits));
+  const int s1 = int(unsigned(stages * (sp + 1)) / unsigned(splits));
 
   SpOperands src;
 #pragma unroll
@@ -770,14 +774,19 @@ __global__ void __launch_bounds__(SpTile::kThreads) k_product_sparse(ProductArgs
   src.ai = reinterpret_cast<const char*>(p.AidxS) +
            (size_t(s0) * size_t(p.idx_pitch) + size_t(m0 + sp_idx_row())) * 8 + sp_idx_bytes();
   src.ai_stage = int64_t(p.idx_pitch) * 8;
-  SpAcc acc;
+  constexpr bool kRanges = LOOP == SparseLoop::kRanges || LOOP == SparseLoop::kShortRanges;
+  SpAcc<kRanges> acc;
 #ifdef OPTIMA_PHASE_STAMPS
   const uint64_t stamp0 = wall_clock64();
 #endif
-  gemm_sparse_mainloop(acc, src, s1 - s0, a00, a01, b0, ix0, a10, a11, b1, ix1,
-                       [&] {
+  const auto rows = [&] {
     if (splits == 1) load_tile_rows<MODE>(p, m0, info);
-  });
+  };
+  const SumShape sum{stages, ranges, s0};
+  if constexpr (LOOP == SparseLoop::kShort || LOOP == SparseLoop::kShortRanges)
+    gemm_sparse_short(acc, src, sum, s1 - s0, a00, a01, b0, ix0, a10, a11, b1, ix1, rows);
+  else
+    gemm_sparse_mainloop(acc, src, sum, s1 - s0, a00, a01, b0, ix0, a10, a11, b1, ix1, rows);
 #ifdef OPTIMA_PHASE_STAMPS
   const uint64_t stamp1 = wall_clock64();
 #endif
@@ -2541,41 +2550,71 @@ DensePlan plan_dense(int64_t n_rows, int64_t dp, int ranges, int out_bytes, size
   return best;
 }
 
-// Number of K ranges of a 2:4-sparse product, by a model as above: a stage takes
-// 1.17 us on a full chip and 0.95 while part of it is idle, and an epilogue in
-// the tiles' own launch reaches the chip's rate from 0.6 workgroups a CU. us an
-// iteration with 1, 2 and 3 ranges:
-//   d = 768,  3072 columns (72 tiles)    28.3  26.1  27.1
-//   d = 1024, 4096 columns (128 tiles)   36.5  40.0  50.5
-//   d = 2048, 2048 columns (128 tiles)   54.8  49.8  62.3
-//   d = 4096, 800 columns (128 tiles)    80.6  66.8  82.7
-//   d = 4096, 3000 columns (384 tiles)    199   211   210
-// Whole rounds at 5 % a range, without the outputs' bytes, took three ranges for
-// d = 1536 with 4096 columns (82 us, now 47) and d = 2048 with 3072 (91, now 61).
-int plan_sparse(int64_t n_rows, int64_t dp, int out_bytes, size_t part_cap) {
-  constexpr double kStageUs = 1.17, kLeastUs = 0.95, kFixedUs = 4.0, kLaunchUs = 5.0;
-  constexpr double kBytesPerUs = 8.5e6, kFullRate = 0.6;
+// The same for a 2:4-sparse product.
+int sparse_ranges(int64_t n_rows, int64_t dp, size_t part_cap) {
+  const int tiles_m = int(ceil_div(n_rows, SpTile::BM));
+  return choose_splits_one_per_cu(tiles_m * int(dp / SpTile::BN), int(dp / SpTile::kKPerStage),
+                                  tiles_m * SpTile::BM, int(dp), part_cap);
+}
+
+struct SparsePlan {
+  int splits;
+  SparseLoop loop;
+};
+
+// Workgroups along K and loop of a 2:4-sparse product, by a model as above. The
+// epilogue in the tiles' own launch reaches the chip's rate from 0.39 workgroups a
+// CU. Fit to every S and loop for 288 shapes, d from 128 to 4096 and 12 to 6144
+// columns: 5 % off, the choice 0.3 % slower than the best one in the mean and 4 %
+// at most. us an iteration by the long loop and by the short one (each with its
+// best S of a range a workgroup), and by the better of them with ranges that end
+// in registers:
+//   d = 256,    64 columns   10.7  10.0  11.2
+//   d = 512,  1024 columns   21.5  20.5  17.7
+//   d = 1536,  128 columns   17.5  17.0  17.4
+//   d = 1536, 4096 columns   81.4  80.7  51.5
+//   d = 2048, 2048 columns   48.6  59.9  58.2
+//   d = 4096, 3072 columns  207.7       202.5
+SparsePlan plan_sparse(int64_t n_rows, int64_t dp, int ranges, int out_bytes, size_t part_cap) {
+  struct Loop {
+    SparseLoop id;
+    double base_us, stage_us, least_us, extra_us;  // extra: a round's
+  };
+  static constexpr Loop kLoops[] = {{SparseLoop::kLong, 7.36, 1.28, 1.01, 0.0},
+                                    {SparseLoop::kRanges, 7.36, 1.28, 1.03, 0.23},
+                                    {SparseLoop::kShort, 6.14, 1.11, 1.16, 0.0},
+                                    {SparseLoop::kShortRanges, 6.78, 1.29, 1.11, 0.0}};
+  constexpr double kRoundUs = 2.47, kLaunchUs = 1.46, kSplitUs = 0.43, kEndUs = 0.48;
+  constexpr double kOutBytesPerUs = 10.65e6, kPartBytesPerUs = 9.3e6, kFullRate = 0.39;
+  constexpr int64_t kShortStages = 12;  // as far as measured
   const int n_cu = device_cu_count();
   const int64_t stages = dp / SpTile::kKPerStage;
   const int64_t rows = ceil_div(n_rows, SpTile::BM) * SpTile::BM;
   const int64_t tiles = rows / SpTile::BM * (dp / SpTile::BN);
   const double outputs = double(n_rows) * double(dp);
-  int best = 1;
+  SparsePlan best{1, SparseLoop::kRanges};
   double best_us = 1e30;
   for (int S = 1; S <= kMaxSplits && S <= stages; ++S) {
     if (S > 1 && (tiles * S > kMaxSplitTiles || size_t(S) * size_t(rows) * size_t(dp) > part_cap))
       break;
-    const int64_t full = tiles * S / n_cu;
+    const int64_t full = tiles * S / n_cu, own = ceil_div(stages, S);
     const double part = double(tiles * S % n_cu) / n_cu;
-    const double per_stage =
-        full * kStageUs + (part > 0.0 ? std::max(kLeastUs, part * kStageUs) : 0.0);
+    const double rounds = double(full + (part > 0.0));
     const double rate = S > 1 ? 1.0 : std::min(1.0, double(tiles) / (kFullRate * n_cu));
-    double us = double(ceil_div(stages, S)) * per_stage + double(full + (part > 0.0)) * kFixedUs +
-                outputs * out_bytes / (kBytesPerUs * rate);
-    if (S > 1) us += outputs * 8.0 * S / kBytesPerUs + kLaunchUs;
-    if (us < best_us) {
-      best_us = us;
-      best = S;
+    double rest = (rounds - 1.0) * kRoundUs + outputs * out_bytes / (kOutBytesPerUs * rate);
+    if (S > 1) rest += outputs * 8.0 * S / kPartBytesPerUs + kLaunchUs + kSplitUs * S;
+    if (S < ranges) rest += rounds * double(ceil_div(ranges, S) - 1) * kEndUs;
+    for (const Loop& l : kLoops) {
+      const bool in_ranges = l.id == SparseLoop::kRanges || l.id == SparseLoop::kShortRanges;
+      const bool few = l.id == SparseLoop::kShort || l.id == SparseLoop::kShortRanges;
+      if (in_ranges != (S < ranges) || (few && own > kShortStages)) continue;
+      const double per_stage =
+          full * l.stage_us + (part > 0.0 ? std::max(l.least_us, part * l.stage_us) : 0.0);
+      const double us = l.base_us + rounds * l.extra_us + double(own) * per_stage + rest;
+      if (us < best_us) {
+        best_us = us;
+        best = SparsePlan{S, l.id};
+      }
     }
   }
   return best;
@@ -2693,7 +2732,7 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
                          l.part);
     else if (plan.tile == DenseTile::kRing128)
       hipLaunchKernelGGL((k_product_ring<MODE>), grid, dim3(Ring128::kThreads), 0, s, p,
-                         plan.splits, std::max(plan.splits, ranges), l.part);
+                         plan.splits, plan.splits < ranges ? ranges : 0, l.part);
     else
       hipLaunchKernelGGL((k_product<MODE, PREC>), grid, dim3(ProductTile::kThreads), 0, s, p,
                          plan.splits, l.part);
@@ -2711,15 +2750,30 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
   const int tiles_m = int(ceil_div(p.n_rows, bm));
   const int tiles_n = p.dp / kTile;
   const int rows_pad = tiles_m * bm;
-  const int S = kSparse ? plan_sparse(p.n_rows, p.dp, epilogue_bytes(MODE), l.part_elems)
-                        : choose_splits(tiles_m * tiles_n, p.dp * 4 / ProductTile::SRB, tiles_m,
-                                        p.dp, l.part_elems);
-  if constexpr (kSparse)
-    hipLaunchKernelGGL((k_product_sparse<MODE>), dim3(tiles_m * tiles_n * S),
-                       dim3(SpTile::kThreads), 0, s, p, S, l.part);
-  else
+  int S;
+  if constexpr (kSparse) {
+    const int ranges = sparse_ranges(p.n_rows, p.dp, l.part_elems);
+    const SparsePlan plan = plan_sparse(p.n_rows, p.dp, ranges, epilogue_bytes(MODE), l.part_elems);
+    S = plan.splits;
+    const dim3 grid(unsigned(tiles_m * tiles_n * S)), block(SpTile::kThreads);
+    const int sum_ranges = S < ranges ? ranges : 0;
+    if (plan.loop == SparseLoop::kShortRanges)
+      hipLaunchKernelGGL((k_product_sparse<MODE, SparseLoop::kShortRanges>), grid, block, 0, s, p, S,
+                         sum_ranges, l.part);
+    else if (plan.loop == SparseLoop::kShort)
+      hipLaunchKernelGGL((k_product_sparse<MODE, SparseLoop::kShort>), grid, block, 0, s, p, S,
+                         sum_ranges, l.part);
+    else if (plan.loop == SparseLoop::kRanges)
+      hipLaunchKernelGGL((k_product_sparse<MODE, SparseLoop::kRanges>), grid, block, 0, s, p, S,
+                         sum_ranges, l.part);
+    else
+      hipLaunchKernelGGL((k_product_sparse<MODE, SparseLoop::kLong>), grid, block, 0, s, p, S,
+                         sum_ranges, l.part);
+  } else {
+    S = choose_splits(tiles_m * tiles_n, p.dp * 4 / ProductTile::SRB, tiles_m, p.dp, l.part_elems);
     hipLaunchKernelGGL((k_product<MODE, PREC>), dim3(tiles_m * tiles_n * S),
                        dim3(ProductTile::kThreads), 0, s, p, S, l.part);
+  }
   OPTIMA_LAUNCH_CHECK();
   if (S > 1) {
     const dim3 g(unsigned(p.n_rows), unsigned(ceil_div(p.dp, 4 * kThreads)));
