@@ -1334,12 +1334,17 @@ __global__ void __launch_bounds__(64 * kSkinnyWaves) k_few_persistent(PersistArg
 // 4 g .. 4 g + 3, whose state stays in its registers for the whole block. Only the next x goes
 // through LDS (two buffers, one barrier an iteration).
 //
-// Bound by latency: the chain of one barrier, the LDS reads, dp / 32 dependent
-// MFMAs (one chain for each of the three bf16 products) and the update: 0.68 us
-// an iteration for 64 columns at dp = 128 (bf16x3), 1.5 us at dp = 256. As a
-// product launch per iteration, split along K and finished by a second kernel,
-// they took 9.7 and 10.9 us, nearly all of it the time of the two launches; 4096
-// columns at dp = 256 took 23 us an iteration and take 1.7 us.
+// A product's sum has the ranges that the tiles' sums have (dense_ranges). EACH: a
+// range a 32-wide step (up to 8192 columns at dp = 128), whose MFMA chains are
+// independent; else bit s of `cuts` is set where a range ends after step s.
+//
+// Bound by latency: the chain of one barrier, the LDS reads, the MFMAs of a step
+// (three for the bf16 products), the ranges' additions and the update: 0.56 us
+// an iteration for 64 columns at dp = 128 (bf16x3), 1.3 us at dp = 256 (0.53 and
+// 1.25 with one chain of all steps for each of the three products). As a product
+// launch per iteration, split along K and finished by a second kernel, they took
+// 9.7 and 10.9 us, nearly all of it the time of the two launches; 4096 columns at
+// dp = 256 took 23 us an iteration and take 1.5 us.
 constexpr int kSmallMaxDp = 256;
 constexpr int kSmallCols = 16;
 constexpr int kSmallChunk = 64;  // iterations whose step coefficients are tabled at once
@@ -1357,10 +1362,11 @@ struct SmallArgs {
   const int* kbase;
   const float* Lp;
   int n_iter;
+  unsigned cuts;
 };
 
-template <int DP, int PREC>
-__global__ void __launch_bounds__(kSmallThreads) k_block_small(SmallArgs a) {
+template <int DP, int PREC, bool EACH>  // dp = 128: two workgroups a CU
+__global__ void __launch_bounds__(kSmallThreads, DP == 128 ? 4 : 2) k_block_small(SmallArgs a) {
   constexpr bool kSplit = PREC == kPrecBf16x3;
   constexpr int kSteps = DP / 32, kThr = kSmallThreads;
   constexpr int NB = DP / 16 / (kThr / 64);  // 16-row blocks of H per wave
@@ -1408,6 +1414,21 @@ __global__ void __launch_bounds__(kSmallThreads) k_block_small(SmallArgs a) {
     }
   }
   const float L = *a.Lp;
+  // This lane's pieces of the 32 entries of step s of its x row, and MFMA p of the
+  // step: hi hi, hi lo, lo hi, or 4 entries each.
+  constexpr int kTerms = kSplit ? 3 : 8;
+  auto read_x = [](uint4 (&v)[2], const char* xr, int s) {
+    v[0] = *reinterpret_cast<const uint4*>(xr + (kSplit ? s * 64 : s * 128));
+    v[1] = *reinterpret_cast<const uint4*>(xr + (kSplit ? 2 * DP + s * 64 : s * 128 + 64));
+  };
+  auto term = [](int p, const uint4 (&v)[2], const uint4 (&hs)[2], f4 c) {
+    if constexpr (kSplit)
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v[p >> 1]),
+                                                     __builtin_bit_cast(bf16x8, hs[p & 1]), c, 0, 0, 0);
+    else
+      return __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f4, v[p >> 2])[p & 3],
+                                                  __builtin_bit_cast(f4, hs[p >> 2])[p & 3], c, 0, 0, 0);
+  };
   // alpha and eta of the 16 columns for kSmallChunk iterations: two divisions
   // an entry, which would lengthen every iteration's chain.
   __shared__ f4 tab_alpha[kSmallChunk][kSmallCols / 4], tab_eta[kSmallChunk][kSmallCols / 4];
@@ -1446,35 +1467,48 @@ __global__ void __launch_bounds__(kSmallThreads) k_block_small(SmallArgs a) {
     // Every wave is past its reads of this buffer: they precede the barrier of
     // the iteration before.
     __syncthreads();
-    f4 acc[NB][3];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int q = 0; q < 3; ++q) acc[b][q] = f4{0.f, 0.f, 0.f, 0.f};
     const char* xr = xb + r * kPitch + 16 * g;
+    f4 y[NB];
 #pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-      if constexpr (kSplit) {
-        const bf16x8 xh = *reinterpret_cast<const bf16x8*>(xr + s * 64);
-        const bf16x8 xl = *reinterpret_cast<const bf16x8*>(xr + 2 * DP + s * 64);
+    for (int b = 0; b < NB; ++b) y[b] = f4{0.f, 0.f, 0.f, 0.f};
+    constexpr int kGroup = EACH ? 2 : kSteps;  // steps whose chains run together
+    f4 acc[EACH ? kGroup : 1][NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-          const bf16x8 bh = __builtin_bit_cast(bf16x8, h[b][s][0]);
-          const bf16x8 bl = __builtin_bit_cast(bf16x8, h[b][s][1]);
-          acc[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bh, acc[b][0], 0, 0, 0);
-          acc[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bl, acc[b][1], 0, 0, 0);
-          acc[b][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, bh, acc[b][2], 0, 0, 0);
-        }
+    for (int s0 = 0; s0 < kSteps; s0 += kGroup) {
+#pragma unroll
+      for (int u = 0; u < (EACH ? kGroup : 1); ++u)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[u][b] = f4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (EACH) {
+        uint4 xv[kGroup][2];
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u) read_x(xv[u], xr, s0 + u);
+#pragma unroll
+        for (int p = 0; p < kTerms; ++p)
+#pragma unroll
+          for (int u = 0; u < kGroup; ++u)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[u][b] = term(p, xv[u], h[b][s0 + u], acc[u][b]);
+#pragma unroll
+        for (int u = 0; u < kGroup; ++u)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) y[b] = s0 + u ? y[b] + acc[u][b] : acc[u][b];
       } else {
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-          const f4 xv = *reinterpret_cast<const f4*>(xr + s * 128 + v * 64);
+        for (int s = 0; s < kSteps; ++s) {
+          uint4 xv[2];
+          read_x(xv, xr, s);
 #pragma unroll
-          for (int t = 0; t < 4; ++t)
+          for (int p = 0; p < kTerms; ++p)
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-              acc[b][t & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                  xv[t], __builtin_bit_cast(f4, h[b][s][v])[t], acc[b][t & 1], 0, 0, 0);
+            for (int b = 0; b < NB; ++b) acc[0][b] = term(p, xv, h[b][s], acc[0][b]);
+          if (s + 1 == kSteps || ((a.cuts >> s) & 1u)) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+              y[b] += acc[0][b];
+              acc[0][b] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+          }
         }
       }
     }
@@ -1482,10 +1516,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_block_small(SmallArgs a) {
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const float y = kSplit ? acc[b][0][e] + (acc[b][1][e] + acc[b][2][e])
-                               : acc[b][0][e] + acc[b][1][e];
-        ha[b][e] = (1.f - alpha[e]) * ha[b][e] + alpha[e] * y;
-        hx[b][e] = y;
+        ha[b][e] = (1.f - alpha[e]) * ha[b][e] + alpha[e] * y[b][e];
+        hx[b][e] = y[b][e];
       }
   }
 #pragma unroll
@@ -2688,17 +2720,17 @@ bool small_path(int prec, int dp) { return prec != kPrecSparse && dp <= kSmallMa
 optima_status launch_small(const SmallArgs& a, int dp, int prec, hipStream_t s) {
   const dim3 grid(unsigned(ceil_div(a.n_rows, kSmallCols))), block(kSmallThreads);
   static_assert(kSmallMaxDp == 2 * kTile, "dp is 128 or 256");
-  if (dp == kTile) {
-    if (prec == kPrecBf16x3)
-      hipLaunchKernelGGL((k_block_small<kTile, kPrecBf16x3>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((k_block_small<kTile, kPrecF32>), grid, block, 0, s, a);
-  } else {
-    if (prec == kPrecBf16x3)
-      hipLaunchKernelGGL((k_block_small<2 * kTile, kPrecBf16x3>), grid, block, 0, s, a);
-    else
-      hipLaunchKernelGGL((k_block_small<2 * kTile, kPrecF32>), grid, block, 0, s, a);
-  }
+  const bool each = a.cuts == (1u << (dp / 32 - 1)) - 1;
+  auto kernel = dp == kTile ? (prec == kPrecBf16x3 ? (each ? k_block_small<kTile, kPrecBf16x3, true>
+                                                           : k_block_small<kTile, kPrecBf16x3, false>)
+                                                   : (each ? k_block_small<kTile, kPrecF32, true>
+                                                           : k_block_small<kTile, kPrecF32, false>))
+                            : (prec == kPrecBf16x3
+                                   ? (each ? k_block_small<2 * kTile, kPrecBf16x3, true>
+                                           : k_block_small<2 * kTile, kPrecBf16x3, false>)
+                                   : (each ? k_block_small<2 * kTile, kPrecF32, true>
+                                           : k_block_small<2 * kTile, kPrecF32, false>));
+  hipLaunchKernelGGL(kernel, grid, block, 0, s, a);
   OPTIMA_LAUNCH_CHECK();
   return OPTIMA_OK;
 }
@@ -3133,7 +3165,9 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
     bool persisted = false;
     if (small) {
       SmallArgs sa{rows, n_act, di, Hm, l.HP, xbuf[cur], l.XA, l.HX, l.HA, l.HW0, mask,
-                   l.st.kbase, l.L, n};
+                   l.st.kbase, l.L, n, 0u};
+      const int ranges = dense_ranges(n_act, dp, l.part_elems);
+      for (int r = 1; r < ranges; ++r) sa.cuts |= 1u << (dp / 32 * r / ranges - 1);
       if (auto e = launch_small(sa, dp, iprec, s)) return e;
       if (o.cooperative && few_column_path(iprec, n_act, dp)) inf.persistent_launches += 1;
       persisted = true;

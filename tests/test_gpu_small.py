@@ -49,6 +49,23 @@ def test_one_block_matches_the_oracle(L, prec, bound, d, n, iters):
     np.testing.assert_array_equal(st["iters"], iters)
 
 
+# Batches whose sums have fewer ranges than 32-wide steps of the contraction (3 of
+# 4, 5 of 8 and 2 of 8); columns are independent, so the oracle runs on a sample.
+@pytest.mark.parametrize("prec, bound", [(0, 1e-5), (1, 1e-4)])
+@pytest.mark.parametrize("d, n", [(128, 16500), (200, 9000), (256, 40000)])
+def test_large_batches_match_the_oracle(L, prec, bound, d, n):
+    H, W0, M, lam = _problem(d, n, d + n)
+    W, _, _ = gpu_solve(L, to_dev(H), to_dev(np.array([lam])), W0, M,
+                        L.SolverOpts.default(max_iters=40, fixed_iters=1, precision=prec))
+    W = W.cpu().numpy()
+    assert np.all(W[M == 0].view(np.uint32) == 0)
+    cols = np.concatenate([np.arange(1, 20), np.arange(n - 20, n - 1)])
+    ref = oracle.rapdhg(H.astype(np.float64), W0[cols], M[cols], float(lam),
+                        oracle.SolverOptions(max_iters=40, fixed_iters=True))
+    err = np.linalg.norm(W[cols] - ref.W, axis=1) / np.linalg.norm(ref.W, axis=1)
+    assert err.max() <= bound
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("d, n", [(128, 33), (250, 33)])
 def test_restarted_blocks_reach_the_optimum(L, prec, d, n):
