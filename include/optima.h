@@ -369,7 +369,10 @@ typedef struct {
                              per iteration. 0: one launch per iteration (for
                              callers whose streams cannot take cooperative
                              launches). Falls back to per-iteration launches
-                             by itself when the device refuses them. */
+                             by itself when the device refuses them. Dense
+                             solves with d <= 256 run those iterations in one
+                             ordinary launch whatever this says and for any
+                             number of columns. */
 } optima_solver_opts;
 
 typedef struct {
@@ -392,13 +395,14 @@ typedef struct {
                                  around each run of back-to-back product launches */
   int64_t sparse_products;    /* 1 if the iteration products ran 2:4-sparse (opts.sparse) */
   int64_t few_launches;       /* the timed launches that ran the few-column kernel (at most 8
-                                 active columns with split planes: H streamed once per launch) */
+                                 active columns with split planes: H streamed once per launch;
+                                 not the one-launch blocks of dense solves with d <= 256) */
   int64_t few_row_products;   /* columns multiplied by those launches */
   double few_product_ms;      /* their device time (included in timed_product_ms) */
   int64_t persistent_launches; /* blocks of few-column iterations (the iterations between two
-                                  checks) that opts.cooperative let run as one launch keeping
-                                  H's planes in registers (d <= 4096); each counts all of its
-                                  iterations in few_launches */
+                                  checks) that ran as one cooperative launch keeping H's planes
+                                  in registers (d <= 4096); each counts all of its iterations in
+                                  few_launches */
 } optima_solve_info;
 
 void optima_solver_opts_default(optima_solver_opts* opts);

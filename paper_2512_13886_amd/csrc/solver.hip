@@ -3169,7 +3169,6 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
       const int ranges = dense_ranges(n_act, dp, l.part_elems);
       for (int r = 1; r < ranges; ++r) sa.cuts |= 1u << (dp / 32 * r / ranges - 1);
       if (auto e = launch_small(sa, dp, iprec, s)) return e;
-      if (o.cooperative && few_column_path(iprec, n_act, dp)) inf.persistent_launches += 1;
       persisted = true;
     } else if (o.cooperative && persistent_path(iprec, n_act, dp) &&
         size_t(nc) * size_t(dp) * 4 < (size_t(1) << 31)) {
@@ -3211,7 +3210,7 @@ optima_status qp_solve(const float* H, int64_t d, const float* lambda_max, const
     }
     if (info) {
       OPTIMA_HIP_TRY(hipEventRecord(times.ev[2 * tb + 1], s));
-      times.blocks.push_back({n, n_act, few_column_path(iprec, n_act, dp)});
+      times.blocks.push_back({n, n_act, !small && few_column_path(iprec, n_act, dp)});
     }
     inf.gemm_calls += n;
     inf.row_products += int64_t(n) * n_act;

@@ -76,7 +76,8 @@ def test_sparse_cooperative_matches_per_iteration_launches(L, d, n):
     assert i0["few_launches"] == i1["few_launches"] == 200
 
 
-@pytest.mark.parametrize("d,n", [(256, 3), (4096, 7)])
+# (Up to d = 256 dense solves run blocks of iterations without this kernel.)
+@pytest.mark.parametrize("d,n", [(512, 3), (4096, 7)])
 def test_dense_cooperative_matches_per_iteration_launches(L, d, n):
     # 50 % unstructured masks: dense bf16x3 products
     rng = np.random.default_rng(2000 + d + n)

@@ -87,3 +87,16 @@ def test_columns_do_not_depend_on_the_batch(L):
     sub, st2, _ = gpu_solve(L, to_dev(H), to_dev(np.array([lam])), W0[20:31], M[20:31], o)
     np.testing.assert_array_equal(W[20:31].cpu().numpy(), sub.cpu().numpy())
     np.testing.assert_array_equal(st["iters"][20:31], st2["iters"])
+
+
+@pytest.mark.parametrize("d, n", [(128, 3), (256, 3), (256, 40)])
+def test_counters_do_not_depend_on_the_cooperative_option(L, d, n):
+    # No cooperative launch and no few-column kernel runs here.
+    H, W0, M, lam = _problem(d, n, d + n)
+    out = [gpu_solve(L, to_dev(H), to_dev(np.array([lam])), W0, M,
+                     L.SolverOpts.default(max_iters=130, fixed_iters=1, cooperative=c))
+           for c in (0, 1)]
+    np.testing.assert_array_equal(out[0][0].cpu().numpy(), out[1][0].cpu().numpy())
+    for _, _, info in out:
+        assert info["persistent_launches"] == info["few_launches"] == 0
+        assert info["timed_launches"] == 130 and info["checks"] == 4
