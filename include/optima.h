@@ -330,9 +330,9 @@ optima_status optima_linear_forward(const void* X, int64_t n_tok, int64_t d_in,
  * iterations also covers their CG update kernels). ws:
  * optima_qp_workspace_bytes(d, n_cols) bytes.
  * Blocking: the call synchronises `stream` once per check to learn how many
- * columns are still active (with fixed_iters, where all are, once every 32
- * checks and at the end). Non-convergence is not an error; it is reported
- * per column. Returns OPTIMA_E_NONFINITE if H or W0 holds NaN/Inf,
+ * columns are still active (RAPDHG with fixed_iters, where all are, once
+ * every 32 checks and at the end). Non-convergence is not an error; it is
+ * reported per column. Returns OPTIMA_E_NONFINITE if H or W0 holds NaN/Inf,
  * lambda_max is not a positive finite number, or opts.col_scale holds an
  * entry that is not positive and finite.
  * ------------------------------------------------------------------------- */
