@@ -303,8 +303,8 @@ optima_status linear_forward(const void* X, int64_t n_tok, int64_t d_in, const f
   OPTIMA_LAUNCH_CHECK();
   // The products are queued behind the flag's copy and check the flag
   // themselves, so that the GPU does not wait for the host in between.
-  HostMailbox* box = nullptr;
-  OPTIMA_HIP_TRY(read_back_begin(l.flags, sizeof(int), s, &box));
+  PendingReadBack finite;
+  OPTIMA_HIP_TRY(finite.begin(l.flags, sizeof(int), s));
   if (n_tok > 0) {
     int64_t tiles = ceil_div(n_tok, Tile256::BM) * ceil_div(d_out, Tile256::BN);
     if (forward_wide(n_tok, d_out)) {
@@ -327,7 +327,7 @@ optima_status linear_forward(const void* X, int64_t n_tok, int64_t d_in, const f
     }
   }
   int flag = 0;
-  OPTIMA_HIP_TRY(read_back_end(&flag, sizeof(int), box));
+  OPTIMA_HIP_TRY(finite.end(&flag));
   if (flag) return OPTIMA_E_NONFINITE;
   if (n_tok == 0 && err_out) OPTIMA_HIP_TRY(hipMemsetAsync(err_out, 0, sizeof(double), s));
   return OPTIMA_OK;

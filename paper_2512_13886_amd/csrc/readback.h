@@ -131,27 +131,53 @@ inline hipError_t wait_stream(hipStream_t s) {
 }
 
 // read_back below in two halves, for work queued between them that does not
-// depend on the outcome: begin queues the copy, end waits for it alone. The
-// host thread makes no other library call in between.
-inline hipError_t read_back_begin(const void* src, size_t bytes, hipStream_t s, HostMailbox** box) {
-  if (bytes > kMailboxBytes) return hipErrorInvalidValue;
-  hipError_t e = mailbox_for(s, box);
-  if (e != hipSuccess) return e;
-  if ((e = hipMemcpyAsync((*box)->host, src, bytes, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-  return hipEventRecord((*box)->ev, s);
-}
-inline hipError_t read_back_end(void* dst, size_t bytes, HostMailbox* box) {
-  const hipError_t e = poll_event(box->ev);
-  if (e == hipSuccess) memcpy(dst, box->host, bytes);
-  return e;
-}
+// depend on the outcome: begin queues the copy, end waits for it alone. A call
+// that ends in between (a launch that fails) waits in the destructor: the
+// mailbox is the host thread's next call's, on any stream.
+class PendingReadBack {
+ public:
+  PendingReadBack() = default;
+  PendingReadBack(const PendingReadBack&) = delete;
+  PendingReadBack& operator=(const PendingReadBack&) = delete;
+  ~PendingReadBack() {
+    if (box_) (void)poll_event(box_->ev);
+  }
+
+  hipError_t begin(const void* src, size_t bytes, hipStream_t s) {
+    if (bytes > kMailboxBytes) return hipErrorInvalidValue;
+    HostMailbox* b = nullptr;
+    hipError_t e = mailbox_for(s, &b);
+    if (e != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(b->host, src, bytes, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+    if ((e = hipEventRecord(b->ev, s)) != hipSuccess) {
+      (void)hipStreamSynchronize(s);  // no event to wait for the copy by
+      return e;
+    }
+    box_ = b;
+    bytes_ = bytes;
+    return hipSuccess;
+  }
+
+  // After begin has succeeded.
+  hipError_t end(void* dst) {
+    HostMailbox* const b = box_;
+    box_ = nullptr;
+    const hipError_t e = poll_event(b->ev);
+    if (e == hipSuccess) memcpy(dst, b->host, bytes_);
+    return e;
+  }
+
+ private:
+  HostMailbox* box_ = nullptr;
+  size_t bytes_ = 0;
+};
 
 // Copies `bytes` (at most kMailboxBytes) of device memory at src into dst
 // once the work queued on s so far has finished.
 inline hipError_t read_back(void* dst, const void* src, size_t bytes, hipStream_t s) {
-  HostMailbox* b = nullptr;
-  const hipError_t e = read_back_begin(src, bytes, s, &b);
-  return e != hipSuccess ? e : read_back_end(dst, bytes, b);
+  PendingReadBack p;
+  const hipError_t e = p.begin(src, bytes, s);
+  return e != hipSuccess ? e : p.end(dst);
 }
 
 // The same two waits without the pinned mailbox, for calls that may not
