@@ -18,12 +18,14 @@
 // of 128 stages): 80 us plus 12 us of fused update, against 111 us for the
 // 4-wave tile split in two.
 //
-// A tile that takes a contraction in fewer workgroups than the sum has ranges
-// (SumRanges) ends each range in registers: its sum joins a running one by plain
-// fp32 additions, in the order in which k_split_epilogue adds the ranges of
-// several workgroups, so that W is the same bit for bit. An MFMA chain of the
-// whole contraction is longer and less precise: d = 512, 606 columns, 8 CG
-// iterations, W off by 3.2e-7 of fp64 in one chain, 2.0e-7 in 16.
+// What bounds the error of a sum is the number of MFMA additions to one chain. It
+// is kept down in one of two ways. Without RANGES the small products of split planes
+// have accumulators of their own, and a stage rounds the sum once instead of three
+// times. With RANGES the workgroup ends the ranges of its sum (SumRanges) in
+// registers, where they join a running sum by plain fp32 additions. d = 768 with
+// 3072 columns, 8 CG iterations: W is off by 9.7e-7 of fp64 in one range, 9.1e-7 in
+// five, which take 2.1 instead of 2.0 ms of 64 rAPDHG iterations. Both at once need
+// more registers than there are: half as long again.
 #pragma once
 
 #include "gemm256.h"
@@ -44,9 +46,10 @@ struct OperandsR128 {
   const char* b[Ring128::kLoads];
 };
 
+template <bool RANGES>
 struct AccR128 {
-  f4 q[4][2];    // [16-row block][16-column block]
-  f4 sum[4][2];  // of the ranges that have ended
+  f4 q[4][2];      // [16-row block][16-column block]
+  f4 other[4][2];  // the ranges that have ended, or the hi lo and lo hi products
 };
 // Where the ranges of a sum end, as a workgroup meets them: `count` ranges of
 // `stages` stages, range r ending before stage stages (r + 1) / count; the
@@ -84,9 +87,9 @@ __device__ inline int r128_col(int ni) { return t256_col(0, ni); }
 
 // LEFT: stages left, this one included (4: or more); the last three fetch
 // nothing, and wait for what is in flight.
-template <typename T, int LEFT>
-__device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, SumRanges& ranges, int s,
-                                  char* cur, char* nxt) {
+template <typename T, int LEFT, bool RANGES>
+__device__ inline void r128_stage(AccR128<RANGES>& acc, const OperandsR128& src, SumRanges& ranges,
+                                  int s, char* cur, char* nxt) {
   constexpr int kStage = 2 * Ring128::kLoads;
   const int wm = threadIdx.x >> 8, wn = (threadIdx.x >> 6) & 3;
   bf16x8 fa[4][2], fb[2][2];
@@ -98,11 +101,11 @@ __device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, SumRang
     t256::fetch(src.b, off, nxt + 128 * Ring128::kSRB);
   }
   t256::end_memory<LEFT >= 4 ? 2 * kStage : LEFT == 3 ? kStage : LEFT == 2 ? 0 : -1>();
-  t256::quadrant<T>(acc.q, fa, fb);
-  if (LEFT > 1 && ranges.step()) {
+  t256::quadrant<T>(acc.q, RANGES ? acc.q : acc.other, fa, fb);
+  if (RANGES && LEFT > 1 && ranges.step()) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      acc.sum[i >> 1][i & 1] += acc.q[i >> 1][i & 1];
+      acc.other[i >> 1][i & 1] += acc.q[i >> 1][i & 1];
       acc.q[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
     }
   }
@@ -110,23 +113,24 @@ __device__ inline void r128_stage(AccR128& acc, const OperandsR128& src, SumRang
 }
 
 // The last three stages, from buffers c0, c1, c2.
-template <typename T>
-__device__ inline void r128_last3(AccR128& acc, const OperandsR128& src, SumRanges& ranges, char* c0,
-                                  char* c1, char* c2) {
+template <typename T, bool RANGES>
+__device__ inline void r128_last3(AccR128<RANGES>& acc, const OperandsR128& src, SumRanges& ranges,
+                                  char* c0, char* c1, char* c2) {
   r128_stage<T, 3>(acc, src, ranges, 0, c0, nullptr);
   r128_stage<T, 2>(acc, src, ranges, 0, c1, nullptr);
   r128_stage<T, 1>(acc, src, ranges, 0, c2, nullptr);
 }
 
-// n stages (n >= 0) of a sum with ranges as `shape` has them. b0..b3 are distinct __shared__ arrays of
-// Ring128::kBufBytes. `aside` runs once the first fetches are out.
-template <typename T, typename Aside>
-__device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumShape shape, int n,
-                                     char* b0, char* b1, char* b2, char* b3, Aside aside) {
+// n stages (n >= 0) of a sum, with RANGES its ranges as `shape` has them. b0..b3 are
+// distinct __shared__ arrays of Ring128::kBufBytes. `aside` runs once the first
+// fetches are out.
+template <typename T, bool RANGES, typename Aside>
+__device__ inline void r128_mainloop(AccR128<RANGES>& acc, const OperandsR128& src, SumShape shape,
+                                     int n, char* b0, char* b1, char* b2, char* b3, Aside aside) {
   constexpr int kStage = 2 * Ring128::kLoads;
 #pragma unroll
   for (int i = 0; i < 8; ++i)
-    acc.q[i >> 1][i & 1] = acc.sum[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
+    acc.q[i >> 1][i & 1] = acc.other[i >> 1][i & 1] = f4{0.f, 0.f, 0.f, 0.f};
   if (n <= 0) return;
   auto fetch = [&](int s, char* buf) {
     t256::fetch(src.a, int64_t(s) * Ring128::kSRB, buf);
@@ -183,7 +187,8 @@ __device__ inline void r128_mainloop(AccR128& acc, const OperandsR128& src, SumS
   }
   if (!behind) t256::barrier();
 #pragma unroll
-  for (int i = 0; i < 8; ++i) acc.q[i >> 1][i & 1] = acc.sum[i >> 1][i & 1] + acc.q[i >> 1][i & 1];
+  for (int i = 0; i < 8; ++i)
+    acc.q[i >> 1][i & 1] = acc.other[i >> 1][i & 1] + acc.q[i >> 1][i & 1];
   // No load may still be writing LDS when the workgroup moves on.
   wait_vmcnt<0>();
   __syncthreads();

@@ -101,18 +101,21 @@ __device__ inline void read(bf16x8 (&f)[NBLK][2], const char* half, int r0) {
   }
 }
 
+// The second and third products of split planes go to `cross`, which may be c.
 template <typename T>
-__device__ inline void quadrant(f4 (&c)[4][2], const bf16x8 (&a)[4][2], const bf16x8 (&b)[2][2]) {
+__device__ inline void quadrant(f4 (&c)[4][2], f4 (&cross)[4][2], const bf16x8 (&a)[4][2],
+                                const bf16x8 (&b)[2][2]) {
   constexpr bool kSplit = std::is_same<T, Bf16x3Tag>::value;
 #pragma unroll
   for (int p = 0; p < (kSplit ? 3 : 2); ++p) {
     // bf16: both K steps; split planes: hi hi, hi lo, lo hi.
     const int pa = kSplit ? p >> 1 : p, pb = kSplit ? p & 1 : p;
+    f4 (&to)[4][2] = kSplit && p > 0 ? cross : c;
 #pragma unroll
     for (int mi = 0; mi < 4; ++mi)
 #pragma unroll
       for (int ni = 0; ni < 2; ++ni)
-        c[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mi][pa], b[ni][pb], c[mi][ni], 0, 0, 0);
+        to[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mi][pa], b[ni][pb], to[mi][ni], 0, 0, 0);
   }
 }
 
@@ -146,21 +149,21 @@ __device__ inline void stage(Acc256& acc, const Operands256& src, int64_t off1, 
   read<2>(fb0, b0, wn * 32);
   fetch(src.a[1], off1, na1);
   end_memory<-1>();
-  quadrant<T>(acc.q[0][0], fa, fb0);
+  quadrant<T>(acc.q[0][0], acc.q[0][0], fa, fb0);
   barrier();
   read<2>(fb1, b1, wn * 32);
   fetch(src.a[0], off2, a0);
   end_memory<-1>();
-  quadrant<T>(acc.q[0][1], fa, fb1);
+  quadrant<T>(acc.q[0][1], acc.q[0][1], fa, fb1);
   barrier();
   read<4>(fa, a1, wm * 64);
   fetch(src.b[0], off2, b0);
   end_memory<-1>();
-  quadrant<T>(acc.q[1][1], fa, fb1);
+  quadrant<T>(acc.q[1][1], acc.q[1][1], fa, fb1);
   barrier();
   fetch(src.b[1], off2, b1);
   end_memory<3 * Tile256::kHalfLoads>();
-  quadrant<T>(acc.q[1][0], fa, fb0);
+  quadrant<T>(acc.q[1][0], acc.q[1][0], fa, fb0);
   barrier();
 }
 

@@ -631,9 +631,9 @@ __global__ void __launch_bounds__(Tile256::kThreads) k_product256(ProductArgs p,
 }
 
 // The dense products on the 128 x 128 tiles of gemm128.h, one workgroup per CU.
-// Split ranges, partial sums and the epilogue work as in k_product; `ranges` (0:
-// `splits`) are those of the sum.
-template <int MODE>
+// Split ranges, partial sums and the epilogue work as in k_product; with RANGES
+// the sum has `ranges` ranges.
+template <int MODE, bool RANGES>
 __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs p, int splits,
                                                                     int ranges, float* part) {
   using Cfg = Ring128;
@@ -665,7 +665,7 @@ __global__ void __launch_bounds__(Ring128::kThreads) k_product_ring(ProductArgs 
     src.b[i] = reinterpret_cast<const char*>(p.Bp) + size_t(n0 + t) * p.dp * 4 + k_off +
                t256_seg_bytes(i);
   }
-  AccR128 acc;
+  AccR128<RANGES> acc;
   r128_mainloop<Bf16x3Tag>(acc, src, SumShape{stages, ranges, s0}, s1 - s0, b0, b1, b2, b3,
                            [&] {
     if (splits == 1) load_tile_rows<MODE>(p, m0, info);
@@ -1334,9 +1334,10 @@ __global__ void __launch_bounds__(64 * kSkinnyWaves) k_few_persistent(PersistArg
 // 4 g .. 4 g + 3, whose state stays in its registers for the whole block. Only the next x goes
 // through LDS (two buffers, one barrier an iteration).
 //
-// A product's sum has the ranges that the tiles' sums have (dense_ranges). EACH: a
-// range a 32-wide step (up to 8192 columns at dp = 128), whose MFMA chains are
-// independent; else bit s of `cuts` is set where a range ends after step s.
+// A product's sum has at least the ranges that the tiles' sums have (dense_ranges).
+// EACH: a range a 32-wide step, whose MFMA chains are independent, for more than
+// half as many; else bit s of `cuts` is set where a range ends after step s, and the
+// small products of split planes have a chain of their own.
 //
 // Bound by latency: the chain of one barrier, the LDS reads, the MFMAs of a step
 // (three for the bf16 products), the ranges' additions and the update: 0.56 us
@@ -1472,7 +1473,9 @@ __global__ void __launch_bounds__(kSmallThreads, DP == 128 ? 4 : 2) k_block_smal
 #pragma unroll
     for (int b = 0; b < NB; ++b) y[b] = f4{0.f, 0.f, 0.f, 0.f};
     constexpr int kGroup = EACH ? 2 : kSteps;  // steps whose chains run together
-    f4 acc[EACH ? kGroup : 1][NB];
+    f4 acc[EACH ? kGroup : 1][NB], cross[NB];  // cross: hi lo and lo hi, unless EACH
+#pragma unroll
+    for (int b = 0; b < NB; ++b) cross[b] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s0 = 0; s0 < kSteps; s0 += kGroup) {
 #pragma unroll
@@ -1501,7 +1504,10 @@ __global__ void __launch_bounds__(kSmallThreads, DP == 128 ? 4 : 2) k_block_smal
 #pragma unroll
           for (int p = 0; p < kTerms; ++p)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) acc[0][b] = term(p, xv, h[b][s], acc[0][b]);
+            for (int b = 0; b < NB; ++b) {
+              f4& to = kSplit && p > 0 ? cross[b] : acc[0][b];
+              to = term(p, xv, h[b][s], to);
+            }
           if (s + 1 == kSteps || ((a.cuts >> s) & 1u)) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
@@ -1510,6 +1516,9 @@ __global__ void __launch_bounds__(kSmallThreads, DP == 128 ? 4 : 2) k_block_smal
             }
           }
         }
+        if constexpr (kSplit)
+#pragma unroll
+          for (int b = 0; b < NB; ++b) y[b] += cross[b];
       }
     }
 #pragma unroll
@@ -2494,14 +2503,13 @@ int choose_splits_one_per_cu(int tiles, int stages, int rows_pad, int dp, size_t
   return best;
 }
 
-// Number of ranges of the contraction that the sums of a dense bf16x3 product
-// are made of: each one chain of MFMA sums, the ranges added in their order. It
-// depends on the shape alone, so that the choice of a tile and of the number of
-// its workgroups (plan_dense) does not change results, and is what bounds their
-// error: W of 8 CG iterations over 606 columns of d = 512 is off by 2.0e-7 of
-// fp64 with these 16 ranges, 3.2e-7 with one. The rules are those by which tiles
-// of 128 x 128, two a CU, or of 256 x 128, one a CU, would be split to fill the
-// chip.
+// Number of ranges of the contraction that the sums of a dense bf16x3 product are
+// made of: each one chain of MFMA sums, the ranges added in their order. They are
+// what bounds the sums' error and a matter of the shape alone: a tile takes at
+// least as many workgroups along K, or, the ring, ring_ranges in registers.
+// W of 8 CG iterations over 606 columns of d = 512 is off by 2.0e-7 of fp64 with
+// these 16 ranges, 3.2e-7 with one. The rules are those by which tiles of 128 x
+// 128, two a CU, or of 256 x 128, one a CU, would be split to fill the chip.
 int dense_ranges(int64_t n_rows, int64_t dp, size_t part_cap) {
   const bool wide = (dp >= 8192 && n_rows >= 256) || (dp >= 4096 && n_rows >= 4096);
   const int bm = wide ? 2 * kTile : kTile;
@@ -2509,6 +2517,17 @@ int dense_ranges(int64_t n_rows, int64_t dp, size_t part_cap) {
   const int stages = int(dp / 32);
   return wide ? choose_splits_one_per_cu(tiles, stages, tiles_m * bm, int(dp), part_cap)
               : choose_splits(tiles, stages, tiles_m, int(dp), part_cap);
+}
+
+// Ranges of the 128 x 128 ring's sums where it takes fewer workgroups along K than
+// `ranges` and ends them in registers: more than two for each workgroup that would
+// fill the chip are more precise than one each with the small products apart (W of
+// 8 CG iterations: 640 x 4000 1.06e-6 off fp64 and 1.08e-6, 4096 x 1024 1.43e-6 and
+// 1.55e-6), and as many as the other tiles have than those.
+int ring_ranges(int64_t n_rows, int64_t dp, int ranges) {
+  const int64_t tiles = ceil_div(n_rows, kTile) * (dp / kTile);
+  const int fill = int(std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, device_cu_count() / tiles)));
+  return std::min(std::max(ranges, 2 * fill + 1), int(dp / 32));
 }
 
 // Tile and number of workgroups along K of a dense bf16x3 product.
@@ -2527,29 +2546,32 @@ int epilogue_bytes(int mode) { return mode == kFused ? 33 : mode == kStore ? 16 
 // launch and a little each; and in the ring the ends of ranges that it takes in
 // registers. A stage takes less while part of the chip is idle (the loads and the
 // clock are shared), down to least_us. The constants are a fit to every tile and S
-// for 245 shapes, d from 384 to 14336 and 16 to 14336 columns: 7 % off, the choice
-// 0.4 % slower than the best one in the mean and 5 % at most. us an iteration by
-// k_product, k_product_ring and k_product256, each with its best S:
-//   d = 512,  256 columns     13.6  13.0
-//   d = 1024, 512 columns     24.1  18.6
-//   d = 1024, 4096 columns    55    44    62
-//   d = 2048, 1024 columns    44    41    48
-//   d = 4096, 1024 columns   113    98   105
-//   d = 4096, 3072 columns   316   313   273
+// for 560 shapes, d from 128 to 7000 and 11 to 9000 columns: 8 % off, the choice
+// 0.4 % slower than the best one in the mean and 8 % at most. Sums of one range are
+// more precise in the ring, so there another tile has to be 3 % faster. us an
+// iteration by k_product, k_product_ring and k_product256, each with its best S:
+//   d = 512,  215 columns     12.3  11.6  17.8
+//   d = 1024, 508 columns     18.6  17.8  26.1
+//   d = 1024, 3377 columns    46    39    52
+//   d = 2944, 893 columns     71    61    64
+//   d = 4096, 1024 columns   109    89   100
+//   d = 768,  6094 columns    53    56    58
+//   d = 3072, 4886 columns   314   297   246
 // k_product's two workgroups a CU make its rounds twice as wide and hide part
 // of its epilogue; the ring keeps a CU's loads busy with one workgroup, and the
 // 256 x 256 tile loads half as much for the same outputs.
-DensePlan plan_dense(int64_t n_rows, int64_t dp, int ranges, int out_bytes, size_t part_cap) {
+DensePlan plan_dense(int64_t n_rows, int64_t dp, int ranges, int in_ring, int out_bytes,
+                     size_t part_cap) {
   struct Tile {
     DenseTile id;
     int side, per_cu;
     double stage_us, least_us, base_us, round_us;
   };
-  static constexpr Tile kTiles[] = {{DenseTile::kSmall, 128, 2, 1.11, 0.81, 5.5, 0.0},
-                                    {DenseTile::kRing128, 128, 1, 0.53, 0.48, 5.6, 1.2},
-                                    {DenseTile::k256, 256, 1, 1.61, 1.37, 6.7, 2.4}};
-  constexpr double kOutBytesPerUs = 6.2e6, kPartBytesPerUs = 7.0e6;
-  constexpr double kLaunchUs = 1.5, kSplitUs = 0.3, kEndUs = 0.37;
+  static constexpr Tile kTiles[] = {{DenseTile::kSmall, 128, 2, 1.26, 0.94, 4.9, 0.2},
+                                    {DenseTile::kRing128, 128, 1, 0.52, 0.48, 5.65, 1.0},
+                                    {DenseTile::k256, 256, 1, 1.52, 1.35, 5.7, 2.1}};
+  constexpr double kOutBytesPerUs = 6.5e6, kPartBytesPerUs = 5.7e6;
+  constexpr double kLaunchUs = 1.3, kSplitUs = 0.29, kEndUs = 0.26, kPreferRing = 1.03;
   const int n_cu = device_cu_count();
   const int64_t stages = dp / 32;
   const double outputs = double(n_rows) * double(dp);
@@ -2571,8 +2593,9 @@ DensePlan plan_dense(int64_t n_rows, int64_t dp, int ranges, int out_bytes, size
           full * t.stage_us + (part > 0.0 ? std::max(t.least_us, part * t.stage_us) : 0.0);
       double us = t.base_us + double(ceil_div(stages, S)) * per_stage + (rounds - 1.0) * t.round_us +
                   outputs * out_bytes / kOutBytesPerUs;
-      if (ring && S < ranges) us += rounds * double(ceil_div(ranges, S) - 1) * kEndUs;
+      if (ring && S < ranges) us += rounds * double(ceil_div(in_ring, S) - 1) * kEndUs;
       if (S > 1) us += outputs * 8.0 * S / kPartBytesPerUs + kLaunchUs + kSplitUs * S;
+      if (!ring && ranges == 1) us *= kPreferRing;
       if (us < best_us) {
         best_us = us;
         best = DensePlan{t.id, S};
@@ -2720,7 +2743,7 @@ bool small_path(int prec, int dp) { return prec != kPrecSparse && dp <= kSmallMa
 optima_status launch_small(const SmallArgs& a, int dp, int prec, hipStream_t s) {
   const dim3 grid(unsigned(ceil_div(a.n_rows, kSmallCols))), block(kSmallThreads);
   static_assert(kSmallMaxDp == 2 * kTile, "dp is 128 or 256");
-  const bool each = a.cuts == (1u << (dp / 32 - 1)) - 1;
+  const bool each = 2 * __builtin_popcount(a.cuts) >= dp / 32;  // more than half
   auto kernel = dp == kTile ? (prec == kPrecBf16x3 ? (each ? k_block_small<kTile, kPrecBf16x3, true>
                                                            : k_block_small<kTile, kPrecBf16x3, false>)
                                                    : (each ? k_block_small<kTile, kPrecF32, true>
@@ -2755,16 +2778,21 @@ optima_status launch_product(const ProductArgs& p, const Layout& l, hipStream_t 
   }
   if constexpr (PREC == kPrecBf16x3) {
     const int ranges = dense_ranges(p.n_rows, p.dp, l.part_elems);
-    const DensePlan plan = plan_dense(p.n_rows, p.dp, ranges, epilogue_bytes(MODE), l.part_elems);
+    const int in_ring = ring_ranges(p.n_rows, p.dp, ranges);
+    const DensePlan plan =
+        plan_dense(p.n_rows, p.dp, ranges, in_ring, epilogue_bytes(MODE), l.part_elems);
     const int bm = plan.tile == DenseTile::k256 ? Tile256::BM : kTile;
     const int tiles_m = int(ceil_div(p.n_rows, bm)), tiles_n = int(ceil_div(p.dp, bm));
     const dim3 grid(unsigned(tiles_m * tiles_n * plan.splits));
     if (plan.tile == DenseTile::k256)
       hipLaunchKernelGGL((k_product256<MODE>), grid, dim3(Tile256::kThreads), 0, s, p, plan.splits,
                          l.part);
+    else if (plan.tile == DenseTile::kRing128 && plan.splits < ranges)
+      hipLaunchKernelGGL((k_product_ring<MODE, true>), grid, dim3(Ring128::kThreads), 0, s, p,
+                         plan.splits, in_ring, l.part);
     else if (plan.tile == DenseTile::kRing128)
-      hipLaunchKernelGGL((k_product_ring<MODE>), grid, dim3(Ring128::kThreads), 0, s, p,
-                         plan.splits, plan.splits < ranges ? ranges : 0, l.part);
+      hipLaunchKernelGGL((k_product_ring<MODE, false>), grid, dim3(Ring128::kThreads), 0, s, p,
+                         plan.splits, 0, l.part);
     else
       hipLaunchKernelGGL((k_product<MODE, PREC>), grid, dim3(ProductTile::kThreads), 0, s, p,
                          plan.splits, l.part);
