@@ -1454,7 +1454,8 @@ __global__ void __launch_bounds__(kSmallThreads, DP == 128 ? 4 : 2) k_block_smal
         const int n = n0 + 16 * b;
         const float gr = 2.f * ((1.f - alpha[e]) * ha[b][e] + alpha[e] * hx[b][e] - hw[b][e]);
         x[b][e] = (keep >> (4 * b + e)) & 1u ? x[b][e] - eta[e] * gr : 0.f;
-        xa[b][e] = (1.f - alpha[e]) * xa[b][e] + alpha[e] * x[b][e];
+        // As the tiles' update is contracted: only the smaller product is rounded.
+        xa[b][e] = __builtin_fmaf(1.f - alpha[e], xa[b][e], alpha[e] * x[b][e]);
         char* q = xb + (4 * g + e) * kPitch;
         if constexpr (kSplit) {
           const uint32_t hi = bf16_rne_bits(x[b][e]);

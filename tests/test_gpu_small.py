@@ -80,6 +80,21 @@ def test_restarted_blocks_reach_the_optimum(L, prec, d, n):
     assert np.all(st["restarts"][1:-1] > 0)
 
 
+# The same columns as part of a 384-wide layer, whose other entries are zero, take a
+# launch per iteration on the tiles: the same sums (a range a 32-wide step, and zeros)
+# and the same update, rounding for rounding.
+@pytest.mark.parametrize("d, n", [(128, 40), (256, 3), (256, 40)])
+def test_blocks_round_as_the_tiles_do(L, d, n):
+    H, W0, M, lam = _problem(d, n, d + n)
+    H2 = np.eye(384, dtype=np.float32)
+    W2, M2 = np.zeros((n, 384), np.float32), np.zeros((n, 384), np.uint8)
+    H2[:d, :d], W2[:, :d], M2[:, :d] = H, W0, M
+    o = L.SolverOpts.default(max_iters=40, fixed_iters=1, precision=L.PREC_FP32)
+    W, _, _ = gpu_solve(L, to_dev(H), to_dev(np.array([lam])), W0, M, o)
+    ref, _, _ = gpu_solve(L, to_dev(H2), to_dev(np.array([lam])), W2, M2, o)
+    np.testing.assert_array_equal(W.cpu().numpy(), ref[:, :d].cpu().numpy())
+
+
 def test_columns_do_not_depend_on_the_batch(L):
     H, W0, M, lam = _problem(192, 50, 3)
     o = L.SolverOpts.default(eps_rel=1e-4, eps_abs=0.0)
