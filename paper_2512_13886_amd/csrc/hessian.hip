@@ -664,15 +664,6 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
     return S == 1 || double(S) * double(d) * double(d) * 4.0 <= double(int64_t(1) << 32);
   };
   const int max_s = std::min(dt::kMaxSplits, stages);
-  int least = 1;
-  double best_cost = 1e30;
-  for (int S = 1; S <= max_s && affordable(S); ++S) {
-    const double c = double(ceil_div(share * S, int64_t(dt::kCus / 8))) / S * (1.0 + 0.01 * S);
-    if (c < best_cost - 1e-12) {
-      least = S;
-      best_cost = c;
-    }
-  }
   // More than that only where tiles spread over all CUs gain from it, and from
   // 32 stages a split on: d = 256 with 32768 tokens in 64 splits instead of 32
   // gained nothing and was off by 1.17e-7 instead of 1.06e-7; d = 1024 in 25
@@ -686,37 +677,58 @@ DirectPlan direct_plan(int64_t n_tok, int64_t d) {
   const double stage_us = double(stages) * 1.6;
   const double split_us =
       std::max(0.01 * double(units) / dt::kCus * stage_us, tri_bytes * 2.0 / 5.2e6);
-  p.splits = least;
-  best_cost = 1e30;
-  const int most = stages >= 32 * least ? max_s : least;
-  for (int S = least; S <= most && affordable(S); ++S) {
-    const double rounds = double(ceil_div(units * S, int64_t(dt::kCus)));
-    const double c = rounds / S * stage_us + S * split_us + 5.0;
-    if (c < best_cost * (1.0 - 1e-12)) {
-      p.splits = S;
-      best_cost = c;
+  struct Splits {
+    int least, best;
+    double best_us;
+  };
+  const auto splits_from = [&](int first) {  // at least `first`
+    Splits s{first, first, 1e30};
+    double least_cost = 1e30;
+    for (int S = first; S <= max_s && affordable(S); ++S) {
+      const double c = double(ceil_div(share * S, int64_t(dt::kCus / 8))) / S * (1.0 + 0.01 * S);
+      if (c < least_cost - 1e-12) {
+        s.least = S;
+        least_cost = c;
+      }
     }
-  }
+    const int most = stages >= 32 * s.least ? max_s : s.least;
+    for (int S = s.least; S <= most && affordable(S); ++S) {
+      const double rounds = double(ceil_div(units * S, int64_t(dt::kCus)));
+      const double c = rounds / S * stage_us + S * split_us + 5.0;
+      if (c < s.best_us * (1.0 - 1e-12)) {
+        s.best = S;
+        s.best_us = c;
+      }
+    }
+    return s;
+  };
+  // A range with last rows takes two splits at least: the widths that fill the chip
+  // with one (5632, 7936 and others) are then off by 1.6e-7 of fp64 instead of
+  // 2.5e-7 at 2000 tokens, which take 118 us instead of 104. Whole stages keep their
+  // one chain: 2048 tokens 85 us.
+  const int tails = p.full_stages > 0 && p.tail_rows > 0;
+  const Splits two = splits_from(max_s > 1 && affordable(2) ? 2 : 1);
+  const Splits plan = tails ? two : splits_from(1);
+  p.splits = plan.best;
   // FUSED: every tile's ranges in one workgroup, kRangeUs between two of them
   // and kEndUs for the stores to H. Short ranges of many tiles, where the
   // partial sums outweigh the idle CUs: d = 4096 with 512 tokens 83 us instead
   // of 105, 2048 tokens 145 instead of 206.
   constexpr double kRangeUs = 8.0, kEndUs = 13.0;
-  const int tails = p.full_stages > 0 && p.tail_rows > 0;
   const double rounds = double(ceil_div(8 * share, int64_t(dt::kCus)));
   const double fused_cost =
-      rounds * (double(stages + tails) * 1.6 + (least - 1 + tails) * kRangeUs + kEndUs);
-  const double split_cost = best_cost + tails * (tri_bytes * 2.0 / 5.2e6 + 3.0);
+      rounds * (double(stages + tails) * 1.6 + (plan.least - 1 + tails) * kRangeUs + kEndUs);
+  const double split_cost = plan.best_us + tails * (tri_bytes * 2.0 / 5.2e6 + 3.0);
   p.fused = p.tiles >= 32 && fused_cost < 0.9 * split_cost;
   // One [d][d] partial per split and one for the last rows, which are no stage:
   // a chain of sums of their own, as a longer one would be less precise (3000
   // tokens of d = 3072 off by 1.54e-7 instead of 1.51e-7). The running sums of
   // FUSED (d (d + 256) / 2 entries) fit one partial. The size stays that of the
-  // split plan, which never takes fewer splits for more stages, and from the first
-  // token beyond a stage on has room for last rows: a workspace for more tokens
-  // always holds fewer.
-  p.part_elems = size_t(p.splits + (n_tok > dt::kRows)) * size_t(d) * size_t(d);
-  if (p.fused) p.splits = least;
+  // split plan with last rows, which never takes fewer splits for more stages, from
+  // the first token beyond a stage on: a workspace for more tokens always holds
+  // fewer.
+  p.part_elems = size_t(std::max(two.best, p.splits) + (n_tok > dt::kRows)) * size_t(d) * size_t(d);
+  if (p.fused) p.splits = plan.least;
   return p;
 }
 

@@ -51,6 +51,24 @@ def test_sum_and_accumulation(n_tok, d):
     assert torch.equal(H, before + Z)
 
 
+# Widths whose tiles fill the chip once take whole stages in one chain of sums, and
+# token counts with last rows in two at least. The error of a chain grows as the root
+# of its length or faster: at 2000 tokens it is at most 1 / sqrt(2) of that of one
+# chain, and one part in eight more for the scatter of the two.
+@pytest.mark.parametrize("d", [5632, 7936])
+def test_last_rows_come_with_two_chains(d):
+    X = _x(2000, d, d)
+
+    def error(n_tok):
+        H = torch.empty((d, d), device="cuda")
+        L.optima_hessian_accumulate(X[:n_tok], H)
+        X64 = X[:n_tok].double()
+        ref = X64.T @ X64
+        return float((H.double() - ref).norm() / ref.norm())
+
+    assert error(2000) <= 2 ** -0.5 * 1.125 * error(1984)
+
+
 @pytest.mark.parametrize("d", [256, 1024, 2048, 4096, 6144, 14336])
 def test_workspace_never_shrinks_with_more_tokens(d):
     need = [L.optima_hessian_workspace_bytes(n, d, L.DTYPE_BF16)
